@@ -13,16 +13,13 @@
 // atomics when they push their entry-column adjoint to their neighbours.
 // dL/dn_HI goes to an FP64 N^3 accumulator with hardware atomics; dL/dQ is
 // reduced over the wave and added once per piece.
+#include <stddef.h>
+
 #include "asora_dev.h"
 #include "asora_internal.h"
+#include "asora_sweep.h"
 
 namespace asora {
-
-// Layer adjoint work-groups: up to kAdjLayerNarrow waves the kernel may hold
-// 168 VGPRs per lane (three waves per SIMD); the wide build, up to
-// kAdjLayerWaves waves, is held to 128 (four per SIMD) and spills the rest.
-// Which wins depends on the workload: the work-group size is tuned.
-constexpr int kAdjLayerNarrow = 12;
 
 struct AdjArgs {
     int N;
@@ -32,7 +29,7 @@ struct AdjArgs {
     int reading;
     TabParams tp;
     const TabNode *tab;
-    const double *m64;       // FP64 node slopes
+    const Node64 *n64;       // the table in FP64
     const double *nHI;
     const double *gbar;      // dL/dGamma, N^3
     double *nbar;            // dL/dn_HI accumulator, N^3
@@ -56,9 +53,9 @@ struct AdjArgs {
     int Mcap, lay_S;         // largest layer index, row stride of the layer buffers
     const char *kept;        // column records kept by the forward (per source and pyramid), or NULL
     size_t rec_piece_bytes;  // bytes of one pyramid's column record
-    size_t rec_rk_off;       // kept records: offset of the rate coefficients
-    long rec_cap;            // cells (and listed cells) per pyramid record
+    long rec_cap;            // cells per pyramid record
     int early_exit;          // layer pieces: stop at the first opaque layer
+    LayerConst lc;
     int sq_n;                // layer pieces: entries of the work-group's LDS table of sqrt(r^2); 0: none
 };
 
@@ -102,7 +99,8 @@ __device__ void adjoint_piece_wave(const AdjArgs &A, const TabNode *T, char *reg
     X.half_col = n_s * A.alpha * 0.5;
     X.coef = Q * A.coef_unit;
     X.tab = T;
-    X.m64 = A.m64;
+    X.m64 = nullptr;
+    X.n64 = A.n64;
     X.tp = A.tp;
     X.ring = ring;
     X.rowbase = rowbase;
@@ -174,7 +172,7 @@ __device__ void adjoint_piece_wave(const AdjArgs &A, const TabNode *T, char *reg
     const bool src_owner = (pc.kind == 0) || (pc.oct == 0 && (pc.dom < 0 || pc.dom == 2));
     if (src_owner && lane == 0) {
         double nb, q1;
-        source_cell_adjoint(T, A.m64, A.tp, A.sigma0, A.alpha, Q, n_s, A.gbar[cs], &nb, &q1);
+        source_cell_adjoint_nodes<false>(NodeArray{A.n64}, A.tp, A.sigma0, A.alpha, Q, n_s, A.gbar[cs], &nb, &q1);
         nb_src += nb;
         qb += q1;
     }
@@ -195,16 +193,10 @@ __global__ __launch_bounds__(512) void adj_wave(AdjArgs A)
 {
     extern __shared__ __align__(16) char smem[];
     if (A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
-    TabNode *T = (TabNode *)smem;
-    {
-        const int4 *s = (const int4 *)A.tab;
-        int4 *d = (int4 *)smem;
-        for (int k = threadIdx.x; k < A.tp.n; k += blockDim.x) d[k] = s[k];
-    }
-    __syncthreads();
+    const TabNode *T = A.tab;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int waves = blockDim.x >> 6;
-    char *region = smem + (size_t)A.tp.n * sizeof(TabNode) + (size_t)wave * A.region_bytes;
+    char *region = smem + (size_t)wave * A.region_bytes;
     double *store = A.store + (size_t)(blockIdx.x * waves + wave) * A.store_stride;
     constexpr int npieces = TYPE == 0 ? 1 : (TYPE == 1 ? 8 : 24);
     const int base = A.seg[TYPE];
@@ -224,26 +216,25 @@ __global__ __launch_bounds__(512) void adj_wave(AdjArgs A)
 //  (F) Unless the forward kept the pyramid's column record: the columns layer
 //      by layer, in place in the LDS buffer as in the forward kernel, every
 //      cell's layer-buffer entry written to the record in the wave's scratch
-//      together with each chunk's mask of cells with a rate.  The cells with
-//      a rate (SPLIT: only those in sparse chunks, fewer than kDenseChunk of
-//      them) go to an LDS queue with their entry optical depth, and 64 at a
-//      time, with every lane busy, get the FP64 rate derivatives, the rate's
-//      in-cell term of dL/dn_HI, its share of dL/dQ, and its entry-column
-//      term g_in, kept per cell in the wave's scratch.  With SPLIT, dense
-//      chunks leave theirs to (R), which has the interpolation at hand;
-//      without, the kernel holds fewer registers (more waves per SIMD).
+//      together with each chunk's mask of cells with a rate.
 //  (R) Layers from the outermost inward, each layer's rectangle in chunks
 //      from the first to the last: every cell takes and clears its slot in
 //      the LDS adjoint buffer (the adjoint of its exit column, pushed by its
-//      consumers), adds its g_in if it has a rate (from (F), or evaluated
-//      here in a dense chunk), adds alpha ds times the sum (and, in a dense
-//      chunk, the rate's in-cell term) to dL/dn_HI with one atomic and pushes
-//      it through the interpolation weights, read
-//      from the record's entries of layer m - 1, to its neighbours' slots
-//      with LDS atomics.  A neighbour slot precedes the pushing cell in (u, v)
-//      order, so it was already taken in this layer.  Chunks with no rate and
-//      all slots zero (cells no rate depends on) skip the arithmetic.
-// The table is read from global memory (only cells with a rate use it),
+//      consumers).  The cells with work (an adjoint, or a rate) are gathered
+//      into full batches of 64 by an LDS queue.  A batch recomputes the cells'
+//      interpolation from the record's entries of layer m - 1, evaluates the
+//      FP64 rate derivatives of those with a rate, adds alpha ds times the
+//      total adjoint to dL/dn_HI with one atomic, and pushes the entry
+//      column's adjoint through the interpolation weights to the neighbours'
+//      slots with LDS atomics.  A neighbour slot precedes the pushing cell in
+//      (u, v) order, so it was already taken in this layer.  A layer without
+//      a rate that no cell pushed to is left out at once: no rate depends on
+//      its cells.
+// Evaluating the rate's terms where the interpolation is at hand needs one
+// evaluation and one atomic per cell; evaluating them in (F) or in the
+// forward took a second queue, a second atomic, and 8 (in the forward: 24)
+// more bytes per cell with a rate out and back.
+// The tables are read through the caches (only cells with a rate use them),
 // which leaves the LDS to the per-wave buffers.
 __device__ __forceinline__ void wave_sync_global()
 {
@@ -254,7 +245,7 @@ __device__ __forceinline__ void wave_sync_global()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-constexpr int kAdjQueue = 128;   // queue entries per wave ((F) rate terms, (R) batches)
+constexpr int kAdjQueue = 128;   // queue entries per wave
 
 // The rate masks of chunks c0 .. c0 + 63 of a layer (first chunk at choff),
 // one per lane, held in registers.
@@ -278,335 +269,249 @@ __device__ __forceinline__ uint64_t mask_of_chunk(uint64_t masks, int c)
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)masks, c & 63);
 }
 
-template <bool KEPT, bool SPLIT>
-__device__ void adjoint_layer_piece(const AdjArgs &A, const TabNode *T, const double *sq, double *buf, Geo *geo,
-                                    uint32_t *iu, uint32_t *iv, int *qk, int *qm, double *qT, char *scratch, int src,
-                                    int p, int lane)
+// LDS of a wave: one buffer (the columns in (F), the adjoint slots in (R)),
+// the queue of cells with work, the table of factors and index terms; sq: the
+// work-group's table of roots.
+struct AdjLds {
+    SweepLds sweep;
+    const double *sq;
+    double *buf;
+    double *qT;     // adjoint of the cell's exit column
+    int *quv;       // u | v << 8, bit 16: the cell has a rate
+    GeoRow *geo;
+};
+
+template <bool KEPT, bool FAST>
+__device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjLds &W, char *scratch, int src, int p,
+                                                    int lane)
 {
     const int N = A.N;
-    const int si = A.ijk[3 * src], sj = A.ijk[3 * src + 1], sk = A.ijk[3 * src + 2];
+    const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
     const float R = A.R ? A.R[src] : A.R_cap;
     if (!(R >= 0.f && R <= A.R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 ||
         sk >= N) {
         if (lane == 0) atomicOr(A.err, 1);
         return;
     }
-    const double Q = A.Q[src];
-    const int Rsq = (int)floor((double)R * (double)R);
+    const double Q = uniform(A.Q[src]);
+    const int Rsq = uniform((int)floor((double)R * (double)R));
     const LayerPiece L = make_layer_piece(p, si, sj, sk, N, A.ex);
     const uint32_t cs = ((uint32_t)si * (uint32_t)N + (uint32_t)sj) * (uint32_t)N + (uint32_t)sk;
-    const double n_s = A.nHI[cs];
+    const double n_s = uniform(A.nHI[cs]);
     LayerX X;
     X.N = N;
     X.reading = A.reading;
     X.tau_w = A.tau_w;
     X.sigma0 = A.sigma0;
     X.alpha = A.alpha;
-    X.half_col = n_s * A.alpha * 0.5;
+    layer_x_source(X, A.lc, n_s);
     X.nHI = L.transposed ? A.nHI_T : A.nHI;
-    layer_x_weights(X);
     const double *gbar = L.transposed ? A.gbar_T : A.gbar;
     double *nbar = L.transposed ? A.nbar_T : A.nbar;
-    const double coef = Q * A.coef_unit;
+    const double coef = uniform(Q * A.coef_unit);
     const int S = A.lay_S;
     const LayerRecord rec = layer_record_at(
-        KEPT ? (char *)A.kept + ((size_t)src * 24 + p) * A.rec_piece_bytes : scratch, A.rec_cap,
-        KEPT ? A.rec_rk_off : 0);
-    double *gin = KEPT ? nullptr : (double *)(scratch + A.rec_piece_bytes);   // g_in by record cell
-    const int Mx = min(isqrt_floor(Rsq), L.ext_d);
-    constexpr int dense_at = SPLIT ? kDenseChunk : 65;   // popcount of a dense chunk
-    // (R) queues the cells with work into full batches, except in the split
-    // form (most cells have a rate there, and most lanes work anyway)
-    constexpr bool QUEUE = KEPT || !SPLIT;
-
+        KEPT ? (char *)A.kept + ((size_t)src * 24 + p) * A.rec_piece_bytes : scratch, A.rec_cap, 0);
+    const int Mx = min(uniform(isqrt_floor(Rsq)), L.ext_d);
+    double *buf = W.buf;
+    GeoRow *geo = W.geo;
     // the pyramid's index terms along u and v (every pass)
     for (int k = lane; k < S; k += 64) {
-        iu[k] = layer_idx_u(L, N, k);
-        iv[k] = layer_idx_v(L, N, k);
+        geo[k].iu = layer_idx_u(L, N, k);
+        geo[k].iv = layer_idx_v(L, N, k);
     }
     wave_sync();
 
     // ---- (F), every layer; with the early exit only up to the first layer
     // whose cells all leave opaque (layer_opaque): later layers have no rate
     // and no adjoint.  Kept records hold the layers their forward swept.
-    // Unless the forward kept the rate's coefficients, (F) also evaluates the
-    // rate's terms (g_in by record cell, dL/dn_HI and dL/dQ shares) of the
-    // cells with a rate that (R) does not take in place (all of them in the
-    // gathered form, those of sparse chunks in the split one): such cells go
-    // to the wave's queue with their entry optical depth and place (m, g),
-    // and every full 64 are evaluated by all lanes together.
     double nb_src = 0.0, qb = 0.0;
     long off = 0, choff = 0;   // the record's cells and chunks of layers 1 .. Mt
     int Mt = Mx;   // the last layer (R) visits
     if (KEPT) {
-        const int ml = (int)((const uint64_t *)rec.rk)[3 * A.rec_cap + 1];
+        const int ml = uniform((int)rec.lit[A.rec_cap / 64 + A.Mcap]);
         Mt = ml < Mx ? ml : Mx;
         for (int m = 1; m <= Mt; ++m) {
-            const int t = layer_rect(L.ext_u, L.ext_v, Rsq, m).total;
+            const int t = layer_rect_uniform(L.ext_u, L.ext_v, Rsq, m).total;
             off += t;
             choff += (t + 63) / 64;
         }
-    } else {
-        const bool watch = A.early_exit != 0;
-        const int P = S + 1;   // row stride of the padded layer buffer
-        for (int k = lane; k < P * P; k += 64) buf[k] = 0.0;   // finite everywhere it is read
-        wave_sync();
-        const double opaque = layer_opaque(A.tp.tau_hi);
-        // the queue: record cell (qk), (m << 16) | g (qm), entry optical depth (qT)
-        int head = 0, tail = 0;
-        auto batch = [&](int count) {
-            if (lane < count) {
-                const int q = (head + lane) & (kAdjQueue - 1);
-                const int k = qk[q], mg = qm[q];
-                const double ta = qT[q];
-                const int m = mg >> 16, g = mg & 0xffff;
-                int u, v;
-                rect_cell(layer_rect(L.ext_u, L.ext_v, Rsq, m), g, u, v);
-                // the cell's index, distance and in-cell column as (F) formed them
-                const uint32_t cp = layer_idx_d(L, N, m) + iu[u] + iv[v];
-                const int r2 = mul24(m, m) + mul24(u, u) + mul24(v, v);
-                const double rt = A.sq_n ? sq[r2] : sqrt_fast((double)r2);
-                const double ds = rt * rcp_f64((double)m);
-                const double gb = gbar[cp];
-                double gi = 0.0;
-                if (gb != 0.0) {
-                    const double dN = X.nHI[cp] * X.alpha * ds;
-                    double ne, gG;
-                    layer_rate_adjoint_t(T, A.m64, A.tp, A.sigma0, coef, ta, A.sigma0 * dN, X.alpha * ds, r2, gb,
-                                         &gi, &ne, &gG);
-                    if (ne != 0.0) unsafeAtomicAdd(&nbar[cp], ne);
-                    qb += gG;
-                }
-                gin[k] = gi;
-            }
-        };
-        for (int m = 1; m <= Mx; ++m) {
-            const LayerRect r = layer_rect(L.ext_u, L.ext_v, Rsq, m);
-            const double inv_m = rcp_f64((double)m);
-            const int nch = (r.total + 63) / 64;
-            for (int k = lane; k < S; k += 64) geo[k] = layer_geo(m, inv_m, k);
-            wave_sync();
-            RectWalk w;
-            w.init(r, (nch - 1) * 64 + lane);
-            bool opq = true;   // every cell of layer m so far leaves opaque
-            const int m2 = mul24(m, m);
-            const uint32_t idx_d = layer_idx_d(L, N, m);
-            for (int c = nch - 1; c >= 0; --c, w.down()) {
-                const int g = c * 64 + lane;
-                const int u = w.u, v = w.v;
-                const int uv2 = mul24(u, u) + mul24(v, v);
-                const bool act = g < r.total && uv2 <= r.rem;
-                const int pos = layer_slot(u, v, P);
-                LayerCell lc;
-                lc.Nin = 0.0;
-                lc.Nout = 0.0;
-                lc.owned = false;
-                if (act) {
-                    const uint32_t cp = idx_d + iu[u] + iv[v];
-                    const int r2 = m2 + uv2;   // <= Rsq < sq_n when the table is there
-                    const double rt = A.sq_n ? sq[r2] : sqrt_fast((double)r2);
-                    layer_cell_core(L, X, m, u, v, geo[u], geo[v], rt * inv_m, r2, cp, X.nHI[cp], buf[pos],
-                                    buf[pos - P], buf[pos - 1], buf[pos - P - 1], lc);
-                }
-                wave_sync();
-                bool lit = false;
-                if (act) {
-                    buf[pos] = lc.h;
-                    rec.h[off + g] = lc.h;
-                    lit = lc.owned && A.sigma0 * lc.Nin < A.tp.tau_hi;
-                }
-                const uint64_t mask = __ballot(lit);
-                if (lane == 0) rec.lit[choff + c] = mask;
-                if (watch) opq = opq && __ballot(act && !(A.sigma0 * lc.Nout >= opaque)) == 0;
-                if (mask && __popcll(mask) < dense_at) {   // (R) does not take these in place
-                    if (lit) {
-                        const int q = (tail + (int)__builtin_amdgcn_mbcnt_hi(
-                                                  (uint32_t)(mask >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))) &
-                                      (kAdjQueue - 1);
-                        qk[q] = (int)(off + g);
-                        qm[q] = (m << 16) | g;
-                        qT[q] = A.sigma0 * lc.Nin;
-                    }
-                    tail += __popcll(mask);
-                    if (tail - head >= 64) {
-                        wave_sync();
-                        batch(64);
-                        head += 64;
-                    }
-                }
-                wave_sync();
-            }
-            off += r.total;
-            choff += nch;
-            if (watch && opq) {
-                Mt = m;
-                break;
-            }
-        }
-        if (tail > head) {
-            wave_sync();
-            batch(tail - head);
-            wave_sync();
-        }
+    } else if (Mx >= 1) {
+        bool opq = true;   // every cell of layer m so far leaves opaque
+        sweep_layers(
+            L, X, W.sweep, Rsq, Mx, Mt, A.tp.tau_hi, A.lc.inv_hi, lane,
+            [&](const SweepChunk &k) {
+                if (k.in) rec.h[off + k.c * 64 + lane] = k.h;
+                const uint64_t mask = ballot(k.in & k.below & layer_owned(L, k.m, k.u, k.v));
+                if (lane == 0) rec.lit[choff + k.c] = mask;
+                if (A.early_exit) opq = opq && ballot(k.in && entry_below(k.h, A.lc.opaque, A.lc.inv_opq)) == 0;
+            },
+            [&](int m, int total) {
+                off += total;
+                choff += (total + 63) / 64;
+                if (A.early_exit && opq) Mt = m;
+                opq = true;
+            });
         wave_sync_global();
     }
     for (int k = lane; k < S * S; k += 64) buf[k] = 0.0;   // the adjoint slots
     wave_sync_global();
 
     // ---- (R)
-    {
-        // kept records: the cells with a rate were evaluated layer by layer
-        // from the first, a layer's chunks from the last, a chunk's lanes in
-        // order; lit_end counts those of layers <= m
-        long lit_end = KEPT ? (long)((const uint64_t *)rec.rk)[3 * A.rec_cap] : 0;
-        for (int m = Mt; m >= 1; --m) {
-            const LayerRect r = layer_rect(L.ext_u, L.ext_v, Rsq, m);
-            const int nch = (r.total + 63) / 64;
-            off -= r.total;    // first cell of layer m in the record
-            choff -= nch;      // its first chunk
-            // entries of layer m - 1 (its rectangle precedes layer m's)
-            const LayerRect rp = layer_rect(L.ext_u, L.ext_v, Rsq, m >= 2 ? m - 1 : 1);
-            const double *Hprev = rec.h + (m >= 2 ? off - rp.total : 0);
-            // this layer's geometry (the previous layer's readers are done)
-            const double inv_m = rcp_f64((double)m);
-            const int m2 = mul24(m, m);
-            const uint32_t idx_d = layer_idx_d(L, N, m);
-            for (int k = lane; k < S; k += 64) geo[k] = layer_geo(m, inv_m, k);
-            wave_sync();
-            auto interp = [&](int u, int v, LayerInterp &I) {
-                const int r2 = m2 + mul24(u, u) + mul24(v, v);
-                const double rt = A.sq_n ? sq[r2] : sqrt_fast((double)r2);
-                layer_interp_core(X, m, u, v, idx_d + iu[u] + iv[v], r2, rt * inv_m, geo[u], geo[v], Hprev, rp, I);
-            };
-            // a batch of queued cells of layer m; every slot a cell pushes to
-            // precedes it in (u, v) order, so its chunk was taken before the
-            // cell was queued
-            int qh = 0, qt = 0;
-            auto rbatch = [&](int count) {
-                if (lane < count) {
-                    const int q = (qh + lane) & (kAdjQueue - 1);
-                    const int g = qk[q], li = qm[q];
-                    double Tin = qT[q];
-                    int u, v;
-                    rect_cell(r, g, u, v);
-                    LayerInterp I;
-                    interp(u, v, I);
-                    double nbx = 0.0;
-                    if (KEPT && li >= 0) {   // the rate's terms, from its coefficients
-                        const double gbc = gbar[I.cp] * coef;
-                        Tin += gbc * rec.rk[li];
-                        nbx = gbc * rec.rk[A.rec_cap + li] * X.alpha * I.ds;
-                        qb += gbc * rec.rk[2 * A.rec_cap + li];
-                    }
-                    LayerRev lr;
-                    layer_cell_reverse(X, m, I, Tin, lr);
-                    if (m >= 2) {
-#pragma unroll
-                        for (int n = 0; n < 4; ++n)
-                            if (lr.Mbar[n] != 0.0)
-                                atomicAdd(&buf[mul24(u - (n & 1), S) + (v - (n >> 1))], lr.Mbar[n]);
-                    }
-                    const double nb = lr.nbar + nbx;
-                    if (nb != 0.0) unsafeAtomicAdd(&nbar[lr.cp], nb);
-                    nb_src += lr.nbar_src;
-                }
-            };
-            RectWalk w;
-            w.init(r, lane);
-            uint64_t masks = 0;
-            long run = 0;   // cells with a rate in chunks 0 .. c of this layer
-            for (int c = 0; c < nch; ++c, w.up()) {
-                if ((c & 63) == 0) masks = load_masks(rec, choff, c, nch, lane);
-                const int g = c * 64 + lane;
+    const NodeArray nodes{A.n64};
+    bool pushed = false;   // a cell of layer m + 1 pushed to layer m's slots
+    for (int m = Mt; m >= 1; --m) {
+        const LayerRect r = layer_rect_uniform(L.ext_u, L.ext_v, Rsq, m);
+        const int nch = (r.total + 63) / 64;
+        off -= r.total;    // first cell of layer m in the record
+        choff -= nch;      // its first chunk
+        uint64_t masks = load_masks(rec, choff, 0, nch, lane);
+        if (!pushed && nch <= 64 && __ballot(masks != 0) == 0) continue;   // no rate depends on this layer
+        // entries of layer m - 1 (its rectangle precedes layer m's)
+        const LayerRect rp = layer_rect_uniform(L.ext_u, L.ext_v, Rsq, m >= 2 ? m - 1 : 1);
+        const double *Hprev = rec.h + (m >= 2 ? off - rp.total : 0);
+        // this layer's geometry (the previous layer's readers are done)
+        const double inv_m = rcp_f64((double)m), am = X.alpha * inv_m;
+        const int m2 = m * m;
+        const uint32_t idx_d = layer_idx_d(L, N, m);
+        for (int k = lane; k < S; k += 64) geo[k].g = layer_geo(m, inv_m, k);
+        wave_sync();
+        int qh = 0, qn = 0;   // the queue: qn cells from ring position qh
+        bool any = false;
+        RectWalk w;
+        w.init(r, lane);
+        // chunks 0 .. nch - 1, then a last round for the cells left in the queue
+        for (int c = 0; c <= nch; ++c) {
+            if (c < nch) {
+                if (c > 0 && (c & 63) == 0) masks = load_masks(rec, choff, c, nch, lane);
                 const int u = w.u, v = w.v;
-                const bool act = g < r.total && mul24(u, u) + mul24(v, v) <= r.rem;
-                const uint64_t litmask = mask_of_chunk(masks, c);
-                const bool lit = (litmask >> lane) & 1;
-                run += __popcll(litmask);
+                const bool act = (u < r.nu) & (mul24(u, u) + mul24(v, v) <= r.rem);
+                const bool lit = act && ((mask_of_chunk(masks, c) >> lane) & 1);
                 double Tin = 0.0;
-                if (act) {
-                    Tin = buf[mul24(u, S) + v];
-                    buf[mul24(u, S) + v] = 0.0;
+                if (pushed && act) {
+                    double *slot = buf + mul24(u, S) + v;
+                    Tin = *slot;
+                    *slot = 0.0;
                 }
+                w.up();
+                const uint64_t need = __ballot(lit || Tin != 0.0);
+                if (need == 0) continue;
+                any = true;
                 wave_sync();
-                if (QUEUE) {
-                    // the cells with work go to the queue with their entry-column
-                    // adjoint (gathered form: with the rate's g_in from (F)) and,
-                    // with kept records, the place of their rate's coefficients;
-                    // full batches run with every lane busy
-                    if (!KEPT && lit) Tin += gin[off + g];
-                    const bool need = Tin != 0.0 || (KEPT && lit);
-                    const uint64_t nm = __ballot(need);
-                    if (need) {
-                        const int q = (qt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
-                                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u))) &
-                                      (kAdjQueue - 1);
-                        long li = -1;
-                        if (KEPT && lit) {
-                            li = lit_end - run +
-                                 (long)__builtin_amdgcn_mbcnt_hi((uint32_t)(litmask >> 32),
-                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)litmask, 0u));
-                            // in range for any record contents (records of inputs changed since the
-                            // forward give wrong gradients, never reads outside the record)
-                            li = li < 0 ? 0 : (li >= A.rec_cap ? A.rec_cap - 1 : li);
-                        }
-                        qk[q] = g;
-                        qm[q] = (int)li;
-                        qT[q] = Tin;
-                    }
-                    qt += __popcll(nm);
-                    if (qt - qh >= 64) {
-                        wave_sync();
-                        rbatch(64);
-                        qh += 64;
-                        wave_sync();
-                    }
-                } else if (__ballot(Tin != 0.0) | litmask) {
-                    // the split form, where most cells have a rate: each chunk
-                    // in place (queueing would only add work)
-                    const bool dense = __popcll(litmask) >= dense_at;
-                    if (lit && !dense) Tin += gin[off + g];
-                    if (Tin != 0.0 || (lit && dense)) {
-                        LayerInterp I;
-                        interp(u, v, I);
-                        double extra = 0.0;
-                        if (lit && dense) {
-                            const double gb = gbar[I.cp];
-                            if (gb != 0.0) {
-                                double gi, gG;
-                                layer_rate_adjoint(T, A.m64, A.tp, X, coef, I, X.nHI[I.cp], gb, &gi, &extra,
-                                                   &gG);
-                                Tin += gi;
-                                qb += gG;
-                            }
-                        }
-                        LayerRev lr;
-                        layer_cell_reverse(X, m, I, Tin, lr);
-                        if (m >= 2) {
-#pragma unroll
-                            for (int n = 0; n < 4; ++n)
-                                if (lr.Mbar[n] != 0.0)
-                                    atomicAdd(&buf[mul24(u - (n & 1), S) + (v - (n >> 1))], lr.Mbar[n]);
-                        }
-                        const double nb = lr.nbar + extra;
-                        if (nb != 0.0) unsafeAtomicAdd(&nbar[lr.cp], nb);
-                        nb_src += lr.nbar_src;
-                    }
-                    wave_sync();
+                if (lit || Tin != 0.0) {
+                    const unsigned k = (unsigned)(qh + qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u))) &
+                                       (unsigned)(kAdjQueue - 1);
+                    W.qT[k] = Tin;
+                    W.quv[k] = u | (v << 8) | (lit ? 1 << 16 : 0);
                 }
-            }
-            if (QUEUE && qt > qh) {   // the layer's remaining cells, before layer m - 1 takes its slots
+                qn += __popcll(need);
                 wave_sync();
-                rbatch(qt - qh);
-                wave_sync();
+                if (qn < 64) continue;
             }
-            lit_end -= run;
+            const int cnt = qn < 64 ? qn : 64;
+            const bool run = lane < cnt;
+            double Tin = 0.0;
+            int u = 0, v = 0;
+            bool lit = false;
+            if (run) {
+                const unsigned k = (unsigned)(qh + lane) & (unsigned)(kAdjQueue - 1);
+                const int uv = W.quv[k];
+                Tin = W.qT[k];
+                u = uv & 0xff;
+                v = (uv >> 8) & 0xff;
+                lit = (uv >> 16) != 0;
+            }
+            qh = (qh + cnt) & (kAdjQueue - 1);
+            qn -= cnt;
+            if (run) {
+                const int r2 = m2 + mul24(u, u) + mul24(v, v);
+                const double ads = (A.sq_n ? W.sq[r2] : sqrt_fast((double)r2)) * am;   // alpha ds
+                const uint32_t cp = idx_d + geo[u].iu + geo[v].iv;
+                const Geo gu = geo[u].g, gv = geo[v].g;
+                // the neighbours (u, v), (u - 1, v), (u, v - 1), (u - 1, v - 1) of
+                // layer m - 1; one of zero weight may lie outside it and is
+                // replaced by the one next to it
+                const int ua = u < m ? u : m - 1, ub = u > 0 ? u - 1 : 0;
+                const int va = v < m ? v : m - 1, vb = v > 0 ? v - 1 : 0;
+                double e0 = 0.0, e1 = 0.0, e2 = 0.0, e3 = 0.0;
+                if (m >= 2) {
+                    const double *ra = Hprev + mul24(ua, rp.wv), *rb = Hprev + mul24(ub, rp.wv);
+                    e0 = ra[va];
+                    e1 = rb[va];
+                    e2 = ra[vb];
+                    e3 = rb[vb];
+                }
+                double gb = 0.0, nhi = 0.0;
+                if (lit) {
+                    gb = gbar[cp];
+                    nhi = X.nHI[cp];
+                }
+                const double s0 = gu.om * gv.om, s1 = gu.a * gv.om, s2 = gu.om * gv.a, s3 = gu.a * gv.a;
+                // t_in, and the derivatives b_n of t_in by the neighbours' t
+                double t, b0, b1, b2, b3;
+                if (m == 1) {
+                    t = X.reading == 0 ? X.half_n * (X.sigma0 * ads) : X.half_tau;
+                    b0 = b1 = b2 = b3 = 0.0;
+                } else if (__ballot(!all_thick(e0, e1, e2, e3)) == 0) {
+                    // all thick: t_in = 1 / W, W = sum s e; b = s e^2 / W^2
+                    b0 = s0 * e0;
+                    b1 = s1 * e1;
+                    b2 = s2 * e2;
+                    b3 = s3 * e3;
+                    t = rcp_f64((b0 + b1) + (b2 + b3));
+                    const double k = t * t;
+                    b0 *= e0 * k;
+                    b1 *= e1 * k;
+                    b2 *= e2 * k;
+                    b3 *= e3 * k;
+                } else {
+                    // f = e or 1 / tau_w; b = s f / W, for a thick neighbour times t_in f
+                    const double f0 = e0 > 0.0 ? e0 : X.inv_tw, f1 = e1 > 0.0 ? e1 : X.inv_tw;
+                    const double f2 = e2 > 0.0 ? e2 : X.inv_tw, f3 = e3 > 0.0 ? e3 : X.inv_tw;
+                    b0 = s0 * f0;
+                    b1 = s1 * f1;
+                    b2 = s2 * f2;
+                    b3 = s3 * f3;
+                    const double iW = rcp_f64((b0 + b1) + (b2 + b3));
+                    t = iW * (s0 * (e0 > 0.0 ? 1.0 : -e0 * X.inv_tw) + s1 * (e1 > 0.0 ? 1.0 : -e1 * X.inv_tw) +
+                              s2 * (e2 > 0.0 ? 1.0 : -e2 * X.inv_tw) + s3 * (e3 > 0.0 ? 1.0 : -e3 * X.inv_tw));
+                    b0 *= iW * (e0 > 0.0 ? t * e0 : 1.0);
+                    b1 *= iW * (e1 > 0.0 ? t * e1 : 1.0);
+                    b2 *= iW * (e2 > 0.0 ? t * e2 : 1.0);
+                    b3 *= iW * (e3 > 0.0 ? t * e3 : 1.0);
+                }
+                // N_out = N_in + dN: both receive the exit column's adjoint,
+                // and the rate adds its own parts
+                double Tn = Tin;
+                if (gb != 0.0) {
+                    double D, Da, Ddt;
+                    const TabParams tp = reload_arg<TabParams>(offsetof(AdjArgs, tp));
+                    rate_derivs_nodes<FAST>(nodes, tp, t, nhi * (X.sigma0 * ads), &D, &Da, &Ddt);
+                    const double k = -gb * coef * rcp_f64((double)r2);
+                    qb += k * D;
+                    Tin += k * Da * X.sigma0;
+                    Tn += k * Ddt * X.sigma0;
+                }
+                if (m >= 2) {
+                    double *ra = buf + mul24(ua, S), *rb = buf + mul24(ub, S);
+                    atomicAdd(&ra[va], Tin * b0);
+                    atomicAdd(&rb[va], Tin * b1);
+                    atomicAdd(&ra[vb], Tin * b2);
+                    atomicAdd(&rb[vb], Tin * b3);
+                } else {
+                    nb_src += Tin * (X.reading == 0 ? ads * 0.5 : X.alpha * 0.5);
+                }
+                const double nb = Tn * ads;
+                if (nb != 0.0) unsafeAtomicAdd(&nbar[cp], nb);
+            }
+            wave_sync();
         }
+        pushed = any;
     }
     if (p == 3 * 0 + 2 && lane == 0) {   // the source cell, once per source
         double nb, q1;
-        source_cell_adjoint(T, A.m64, A.tp, A.sigma0, A.alpha, Q, n_s, A.gbar[cs], &nb, &q1);
+        source_cell_adjoint_nodes<FAST>(nodes, A.tp, A.sigma0, A.alpha, Q, n_s, A.gbar[cs], &nb, &q1);
         nb_src += nb;
         qb += q1;
     }
@@ -621,29 +526,30 @@ __device__ void adjoint_layer_piece(const AdjArgs &A, const TabNode *T, const do
     }
 }
 
-template <bool KEPT, bool SPLIT, int MAXW>
-__global__ __launch_bounds__(64 * MAXW) void adj_layer(AdjArgs A)
+template <bool KEPT, bool FAST>
+__global__ __launch_bounds__(64 * kAdjLayerWaves) void adj_layer(AdjArgs A)
 {
     extern __shared__ __align__(16) char smem[];
     constexpr int TYPE = 3, npieces = 24;
     if (A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
-    const TabNode *T = A.tab;
     // the work-group's table of square roots, when the launch gives one
     // (every pass takes a cell's root from it)
     double *sq = (double *)smem;
     for (int k = threadIdx.x; k < A.sq_n; k += blockDim.x) sq[k] = sqrt((double)k);
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int waves = blockDim.x >> 6;
-    // per wave: one buffer, the columns in (F) and the adjoints in (R), the
-    // queue, the tables of (F)
-    double *buf = (double *)(smem + (A.sq_n ? layer_sqrt_bytes(A.sq_n - 1) : 0) + (size_t)wave * A.region_bytes);
-    int *qk = (int *)(buf + (size_t)(A.lay_S + 1) * (A.lay_S + 1));
-    int *qm = qk + kAdjQueue;
-    double *qT = (double *)(qm + kAdjQueue);
-    Geo *geo = (Geo *)(qT + kAdjQueue);
-    uint32_t *iu = (uint32_t *)(geo + A.lay_S);
-    uint32_t *iv = iu + A.lay_S;
+    AdjLds W;
+    W.sq = sq;
+    W.buf = (double *)(smem + (A.sq_n ? layer_sqrt_bytes(A.sq_n - 1) : 0) + (size_t)wave * A.region_bytes);
+    W.qT = W.buf + (size_t)(A.lay_S + 1) * (A.lay_S + 1);
+    W.quv = (int *)(W.qT + kAdjQueue);
+    W.geo = (GeoRow *)(W.quv + kAdjQueue);
+    W.sweep.S = A.lay_S;
+    W.sweep.sq = 0;
+    W.sweep.sq_n = A.sq_n;
+    W.sweep.lay = (A.sq_n ? (int)layer_sqrt_bytes(A.sq_n - 1) : 0) + wave * A.region_bytes;
+    W.sweep.geo = W.sweep.lay + 8 * (A.lay_S + 1) * (A.lay_S + 1) + kAdjQueue * (int)(sizeof(double) + sizeof(int));
     char *scratch = (char *)(A.store + (size_t)(blockIdx.x * waves + wave) * A.store_stride);
     const int base = A.seg[TYPE];
     const int nitems = (A.seg[TYPE + 1] - base) * npieces;
@@ -652,9 +558,8 @@ __global__ __launch_bounds__(64 * MAXW) void adj_layer(AdjArgs A)
     for (;;) {
         const int item = next_item(A.counter, nitems, home, chunk, lane);
         if (item >= nitems) break;
-        const int src = A.order[base + item / npieces];
-        adjoint_layer_piece<KEPT, SPLIT>(A, T, sq, buf, geo, iu, iv, qk, qm, qT, scratch, src, item % npieces,
-                                         lane);
+        const int src = uniform(A.order[base + item / npieces]);
+        adjoint_layer_piece<KEPT, FAST>(A, W, scratch, src, item % npieces, lane);
     }
 }
 
@@ -763,17 +668,11 @@ static const void *adj_fn(int type)
                      : (type == 1 ? (const void *)adj_wave<1> : (const void *)adj_wave<2>);
 }
 
-// The layer adjoint's instantiation: kept records (no rate terms to split),
-// split rate terms or gathered ones; the wide build above kAdjLayerNarrow waves.
-static const void *adj_layer_fn(bool kept, bool split, bool wide)
+// fast: a fine and tame table (the general evaluations compiled out)
+static const void *adj_layer_fn(bool kept, bool fast)
 {
-    if (wide)
-        return kept ? (const void *)adj_layer<true, false, kAdjLayerWaves>
-                    : (split ? (const void *)adj_layer<false, true, kAdjLayerWaves>
-                             : (const void *)adj_layer<false, false, kAdjLayerWaves>);
-    return kept ? (const void *)adj_layer<true, false, kAdjLayerNarrow>
-                : (split ? (const void *)adj_layer<false, true, kAdjLayerNarrow>
-                         : (const void *)adj_layer<false, false, kAdjLayerNarrow>);
+    return kept ? (fast ? (const void *)adj_layer<true, true> : (const void *)adj_layer<true, false>)
+                : (fast ? (const void *)adj_layer<false, true> : (const void *)adj_layer<false, false>);
 }
 
 hipError_t adj_configure(size_t max_lds)
@@ -781,10 +680,8 @@ hipError_t adj_configure(size_t max_lds)
     const int dyn = (int)max_lds - 64;
     for (int t = 0; t < 3; ++t)
         (void)hipFuncSetAttribute(adj_fn(t), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    for (bool wide : {false, true})
-        for (int v = 0; v < 3; ++v)
-            (void)hipFuncSetAttribute(adj_layer_fn(v == 2, v == 1, wide), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      dyn);
+    for (int f = 0; f < 4; ++f)
+        (void)hipFuncSetAttribute(adj_layer_fn(f & 2, f & 1), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipGetLastError();
     return hipSuccess;
 }
@@ -815,7 +712,7 @@ static AdjArgs make_adj_args(const AdjLaunch &L)
     A.reading = L.reading;
     A.tp = L.tp;
     A.tab = L.tab;
-    A.m64 = L.m64;
+    A.n64 = L.n64;
     A.nHI = L.nHI;
     A.gbar = L.gbar;
     A.nbar = L.nbar;
@@ -841,9 +738,9 @@ static AdjArgs make_adj_args(const AdjLaunch &L)
     A.lay_S = 0;
     A.kept = L.kept;
     A.rec_piece_bytes = L.rec_piece_bytes;
-    A.rec_rk_off = L.rec_rk_off;
     A.rec_cap = L.rec_cap;
     A.early_exit = L.early_exit ? 1 : 0;
+    A.lc = make_layer_const(L.sigma0, L.alpha, L.tau_w, L.tp.tau_hi);
     A.sq_n = 0;
     return A;
 }
@@ -852,7 +749,7 @@ hipError_t launch_adj_wave(hipStream_t st, const AdjLaunch &L)
 {
     AdjArgs A = make_adj_args(L);
     A.region_bytes = (int)adj_region_bytes(L.ring_cap, L.row_cap, L.shell_cap);
-    const size_t lds = (size_t)L.tp.n * sizeof(TabNode) + (size_t)L.waves * A.region_bytes;
+    const size_t lds = (size_t)L.waves * A.region_bytes;
     switch (L.type) {
     case 0: hipLaunchKernelGGL(adj_wave<0>, dim3(L.grid), dim3(64 * L.waves), lds, st, A); break;
     case 1: hipLaunchKernelGGL(adj_wave<1>, dim3(L.grid), dim3(64 * L.waves), lds, st, A); break;
@@ -863,19 +760,17 @@ hipError_t launch_adj_wave(hipStream_t st, const AdjLaunch &L)
 
 // Per-wave LDS of the layer adjoint: the buffer (the padded (S + 1) x (S + 1)
 // layer buffer in (F), the S x S adjoint slots in (R)), the queue of cells
-// with work and the table of bilinear factors of (F).
+// with work, the table of factors and index terms.
 size_t adj_layer_region_bytes(int S)
 {
-    return ((size_t)(S + 1) * (S + 1) * sizeof(double) + kAdjQueue * (2 * sizeof(int) + sizeof(double)) +
-            (size_t)S * sizeof(Geo) + 2 * (size_t)S * sizeof(uint32_t) + 15) &
+    return ((size_t)(S + 1) * (S + 1) * sizeof(double) + kAdjQueue * (sizeof(int) + sizeof(double)) +
+            (size_t)S * sizeof(GeoRow) + 15) &
            ~(size_t)15;
 }
 
-hipError_t adj_layer_occupancy(bool kept, bool split, int waves, size_t lds, int *blocks_per_cu)
+hipError_t adj_layer_occupancy(bool kept, int waves, size_t lds, int *blocks_per_cu)
 {
-    // kept records carry the rate's coefficients: no rate terms to split
-    const void *f = adj_layer_fn(kept, !kept && split, waves > kAdjLayerNarrow);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, waves * 64, lds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, adj_layer_fn(kept, true), waves * 64, lds);
 }
 
 hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S)
@@ -888,18 +783,8 @@ hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S)
     const size_t sqb = L.sq_table ? layer_sqrt_bytes(Rsq) : 0;
     A.sq_n = sqb ? Rsq + 1 : 0;
     const size_t lds = sqb + (size_t)L.waves * A.region_bytes;
-    const dim3 grid(L.grid), block(64 * L.waves);
-    constexpr int W = kAdjLayerWaves, Wn = kAdjLayerNarrow;
-    if (L.waves > Wn) {
-        if (A.kept) hipLaunchKernelGGL((adj_layer<true, false, W>), grid, block, lds, st, A);
-        else if (L.split) hipLaunchKernelGGL((adj_layer<false, true, W>), grid, block, lds, st, A);
-        else hipLaunchKernelGGL((adj_layer<false, false, W>), grid, block, lds, st, A);
-    } else {
-        if (A.kept) hipLaunchKernelGGL((adj_layer<true, false, Wn>), grid, block, lds, st, A);
-        else if (L.split) hipLaunchKernelGGL((adj_layer<false, true, Wn>), grid, block, lds, st, A);
-        else hipLaunchKernelGGL((adj_layer<false, false, Wn>), grid, block, lds, st, A);
-    }
-    return hipGetLastError();
+    void *args[] = {&A};
+    return hipLaunchKernel(adj_layer_fn(A.kept != nullptr, A.tp.fine && A.tp.tame), dim3(L.grid), dim3(64 * L.waves), args, lds, st);
 }
 
 hipError_t launch_adj_transpose_prologue(hipStream_t st, const float *nH, const float *xHI,

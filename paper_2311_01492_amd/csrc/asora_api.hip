@@ -29,8 +29,7 @@ struct Plan {
     long scratch;       // adjoint: doubles of scratch per wave
     int Mcap;           // layer pieces: largest layer index
     long rec_cap;       // layer pieces: cells per pyramid record
-    size_t rec_bytes;   // layer pieces: bytes of one pyramid record (the adjoint's own)
-    size_t keep_bytes;  // layer pieces: bytes of one record kept by the forward (with rate coefficients)
+    size_t rec_bytes;   // layer pieces: bytes of one pyramid record
     int wave_mode;   // 1: one wave per piece (waves per work-group below); 0: one work-group per piece
     int waves;
     size_t lds;
@@ -52,7 +51,7 @@ struct asora_ctx {
     int reading;
     TabParams tp;
     TabNode *d_tab;
-    double *d_m64;          // FP64 node slopes for the adjoint
+    Node64 *d_n64;          // the table in FP64, in the same buffer (adjoint, and the rate of a forward that keeps records)
     double lg_lo, lg_hi;    // log10 of the first and last table node
     TabNode *d_tab_h;       // photo-heating table on the same nodes (NULL until set)
     float dP0_h;            // its slope at the first node
@@ -299,10 +298,19 @@ extern "C" asora_status asora_init(asora_ctx **out, int32_t N, double cell_cm, d
     c->adj_waves = 4;
     c->adj_split = 1;
 
-    // table in the kernels' form
-    std::vector<TabNode> nodes(n_tab);
-    std::vector<double> m64(n_tab);
-    prepare_table(n_tab, lg_tau_lo, lg_tau_hi, P, dPdtau, &c->tp, nodes.data(), m64.data());
+    // the table in the kernels' forms, FP32 then FP64, in one buffer: one
+    // allocation and one copy
+    const size_t tab_bytes = sizeof(TabNode) * n_tab, tab_off64 = (tab_bytes + 255) & ~(size_t)255;
+    const size_t tab_total = tab_off64 + sizeof(Node64) * n_tab;
+    std::vector<unsigned char> tab(tab_total);
+    {
+        TabNode *nodes = (TabNode *)tab.data();
+        Node64 *n64 = (Node64 *)(tab.data() + tab_off64);
+        std::vector<double> m64(n_tab);
+        prepare_table(n_tab, lg_tau_lo, lg_tau_hi, P, dPdtau, &c->tp, nodes, m64.data());
+        for (int k = 0; k + 1 < n_tab; ++k) n64[k] = make_node64(nodes, m64.data(), c->tp, k);
+        n64[n_tab - 1] = n64[n_tab - 2];   // (intervals end at the last node: never looked up)
+    }
     c->lg_lo = lg_tau_lo;
     c->lg_hi = lg_tau_hi;
 
@@ -325,17 +333,15 @@ extern "C" asora_status asora_init(asora_ctx **out, int32_t N, double cell_cm, d
             if (ch == ' ' || ch == '/') ch = '_';
     }
     const long n3 = (long)N * N * N;
-    if (hipMalloc(&c->d_tab, sizeof(TabNode) * n_tab) != hipSuccess ||
-        hipMalloc(&c->d_m64, sizeof(double) * n_tab) != hipSuccess ||
+    if (hipMalloc(&c->d_tab, tab_total) != hipSuccess ||
         hipMalloc(&c->d_nhi, sizeof(double) * n3) != hipSuccess ||
         hipMalloc(&c->d_gacc, sizeof(double) * n3) != hipSuccess ||
         hipMalloc(&c->d_ctl, sizeof(int) * kCtlSize) != hipSuccess ||
         hipMalloc(&c->d_err, sizeof(int)) != hipSuccess)
         return bail(fail(nullptr, ASORA_ENOMEM, "asora_init: device allocation of %.1f MB failed",
                          16.0 * n3 / 1e6));
-    if (hipMemcpy(c->d_tab, nodes.data(), sizeof(TabNode) * n_tab, hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemcpy(c->d_m64, m64.data(), sizeof(double) * n_tab, hipMemcpyHostToDevice) != hipSuccess ||
+    c->d_n64 = (Node64 *)((unsigned char *)c->d_tab + tab_off64);
+    if (hipMemcpy(c->d_tab, tab.data(), tab_total, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(c->d_err, 0, sizeof(int)) != hipSuccess ||
         hipMemset(c->d_ctl, 0, sizeof(int) * kCtlSize) != hipSuccess)
         return bail(fail(nullptr, ASORA_EHIP, "asora_init: copy to device failed"));
@@ -366,7 +372,6 @@ extern "C" asora_status asora_free(asora_ctx *c)
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
     (void)hipFree(c->d_tab);
-    (void)hipFree(c->d_m64);
     (void)hipFree(c->d_tab_h);
     (void)hipFree(c->d_hacc);
     (void)hipFree(c->d_hacc_T);
@@ -470,21 +475,19 @@ static asora_status get_plan(asora_ctx *c, int type, float R_cap, Plan *out, boo
     P.ring_cap = ring;
     P.row_cap = (type == 0 ? 8 : 1) * (Qmax + 1);
     P.Qmax = Qmax;
-    // one wave per piece when at least c->min_waves per-wave regions fit next to
-    // the table; else a whole work-group per piece
-    const size_t tab = (size_t)c->tp.n * sizeof(TabNode);
+    // one wave per piece when at least c->min_waves per-wave regions fit; else a whole work-group per piece
     const size_t region = wave_region_bytes(P.ring_cap, P.row_cap);
-    const long fit = c->max_lds > tab + 64 ? (long)((c->max_lds - tab - 64) / region) : 0;
+    const long fit = (long)((c->max_lds - 64) / region);
     int bpc = 0;
     if (fit >= c->min_waves && P.row_cap <= 256) {
         P.wave_mode = 1;
         P.waves = (int)(fit < c->max_waves ? fit : c->max_waves);
-        P.lds = tab + (size_t)P.waves * region;
+        P.lds = (size_t)P.waves * region;
         HIPCHK(c, wave_occupancy(type, P.waves, P.lds, &bpc));
     } else {
         P.wave_mode = 0;
         P.waves = 4;
-        P.lds = fwd_lds_bytes(c->tp.n, P.ring_cap, P.row_cap);
+        P.lds = fwd_lds_bytes(P.ring_cap, P.row_cap);
         if (P.lds + 64 > c->max_lds)
             return fail(c, ASORA_ENOSYS,
                         "R_max=%.1f needs %zu bytes of LDS per work-group (limit %zu) for this "
@@ -517,7 +520,7 @@ static int layer_waves(const asora_ctx *c, size_t wg, size_t sqb, size_t region,
 static asora_status get_layer_plan(asora_ctx *c, float R_cap, Plan *out, bool store)
 {
     const int Rsq = (int)std::floor((double)R_cap * (double)R_cap);
-    const PlanKey key{c->tab_lds ? 3 : 5, Rsq};
+    const PlanKey key{3, Rsq};
     auto it = c->plans.find(key);
     if (it != c->plans.end()) {
         *out = it->second;
@@ -534,23 +537,21 @@ static asora_status get_layer_plan(asora_ctx *c, float R_cap, Plan *out, bool st
     P.rec_cap = layer_piece_capacity(Rsq, ex);
     if (P.rec_cap < 1) P.rec_cap = 1;
     P.rec_bytes = layer_record_bytes(P.rec_cap, P.Mcap, false);
-    P.keep_bytes = layer_record_bytes(P.rec_cap, P.Mcap, true);
     P.wave_mode = 1;
-    // the work-group's LDS: the table (if placed there), the table of square
-    // roots (if it costs no wave), one region per wave
-    const size_t tab = c->tab_lds ? (size_t)c->tp.n * sizeof(TabNode) : 0;
+    // the work-group's LDS: the table of square roots (if it costs no wave),
+    // one region per wave
     const size_t sqb = layer_sqrt_bytes(Rsq);
     for (bool keep : {false, true}) {
         const size_t region = layer_region_bytes(P.S, keep);
         bool sq = false;
-        const int waves = layer_waves(c, tab, sqb, region, c->max_waves, &sq);
+        const int waves = layer_waves(c, 0, sqb, region, c->max_waves, &sq);
         if (waves < 1 || Rsq > 65535)   // the rate queue holds r^2 in 16 bits
             return fail(c, ASORA_ENOSYS,
                         "R_max=%.1f needs %zu bytes of LDS per wave (limit %zu) for this table and grid",
-                        R_cap, region + tab, c->max_lds);
-        const size_t lds = tab + (sq ? sqb : 0) + (size_t)waves * region;
+                        R_cap, region, c->max_lds);
+        const size_t lds = (sq ? sqb : 0) + (size_t)waves * region;
         int bpc = 0;
-        HIPCHK(c, layer_occupancy(keep, c->tab_lds != 0, waves, lds, &bpc));
+        HIPCHK(c, layer_occupancy(keep, waves, lds, &bpc));
         const int grid = c->n_cu * (bpc > 0 ? bpc : 1);
         if (keep) {
             P.kwaves = waves, P.kgrid = grid, P.ksq_table = sq;
@@ -774,11 +775,10 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
     F.nHI_T = B.nhi_T;
     F.gacc_T = B.gacc_T;
     F.keep = keep ? c->d_keep : nullptr;
-    F.keep_piece_bytes = layers ? plans[3].keep_bytes : 0;
+    F.keep_piece_bytes = layers ? plans[3].rec_bytes : 0;
     F.keep_cap = layers ? plans[3].rec_cap : 0;
-    F.keep_rk_off = layers ? plans[3].rec_bytes : 0;
-    F.m64 = c->d_m64;
-    F.tab_lds = c->tab_lds;
+    F.keep_Mcap = layers ? plans[3].Mcap : 0;
+    F.n64 = c->d_n64;
     F.sq_table = layers && (keep ? plans[3].ksq_table : plans[3].sq_table);
     F.early_exit = (flags & ASORA_EARLY_EXIT) != 0;
     F.tab_h = heating ? c->d_tab_h : nullptr;
@@ -880,7 +880,7 @@ static asora_status forward(asora_ctx *c, const float *n_H, const float *x_HI, i
     bool keep = false;
     if (flags & ASORA_STORE) {
         c->keep_valid = false;
-        c->keep_need = layers ? (size_t)n_src * 24 * plans[3].keep_bytes : 0;
+        c->keep_need = layers ? (size_t)n_src * 24 * plans[3].rec_bytes : 0;
         if ((st = reserve_keep(c, c->keep_need, &keep))) return st;
     }
     // n_HI and the source order are rewritten from here on (even if a launch fails)
@@ -1206,18 +1206,17 @@ static asora_status get_adj_plan(asora_ctx *c, int type, float R_cap, Plan *out)
     if (P.row_cap > 256)
         return fail(c, ASORA_ENOSYS,
                     "asora_raytrace_backward: R_max=%.1f too large for the shell adjoint", R_cap);
-    const size_t tab = (size_t)c->tp.n * sizeof(TabNode);
     const size_t region = adj_region_bytes(P.ring_cap, P.row_cap, P.Qmax);
-    const long fit = c->max_lds > tab + 64 ? (long)((c->max_lds - tab - 64) / region) : 0;
+    const long fit = (long)((c->max_lds - 64) / region);
     if (fit < 1)
         return fail(c, ASORA_ENOSYS,
                     "asora_raytrace_backward: R_max=%.1f needs %zu bytes of LDS per wave (limit %zu)",
-                    R_cap, region + tab, c->max_lds);
+                    R_cap, region, c->max_lds);
     P.wave_mode = 1;
     P.scratch = 2 * P.piece_cells;   // exit and in-cell columns of a piece
     const int cap = c->max_waves < 8 ? c->max_waves : 8;   // adjoint work-groups: <= 512 threads
     P.waves = (int)(fit < cap ? fit : cap);
-    P.lds = tab + (size_t)P.waves * region;
+    P.lds = (size_t)P.waves * region;
     int bpc = 0;
     HIPCHK(c, adj_occupancy(type, P.waves, P.lds, &bpc));
     P.grid = c->n_cu * (bpc > 0 ? bpc : 1);
@@ -1250,13 +1249,13 @@ static asora_status get_adj_layer_plan(asora_ctx *c, float R_cap, bool kept, Pla
                     R_cap, region, c->max_lds);
     P.lds = (P.sq_table ? sqb : 0) + (size_t)P.waves * region;
     int bpc = 0;
-    HIPCHK(c, adj_layer_occupancy(kept, c->adj_split != 0, P.waves, P.lds, &bpc));
+    HIPCHK(c, adj_layer_occupancy(kept, P.waves, P.lds, &bpc));
     P.grid = c->n_cu * (bpc > 0 ? bpc : 1);
     P.piece_cells = P.rec_cap;
-    // the record, then g_in per cell (unused when the forward kept the records,
-    // but sized alike, so that both forms run on the same buffers: a recorded
-    // graph of one leaves room for eager calls of the other)
-    P.scratch = (long)(P.rec_bytes / sizeof(double)) + P.rec_cap;
+    // the record (unused when the forward kept the records, but sized alike, so
+    // that both forms run on the same buffers: a recorded graph of one leaves
+    // room for eager calls of the other)
+    P.scratch = (long)(P.rec_bytes / sizeof(double));
     c->adj_plans[key] = P;
     *out = P;
     return ASORA_OK;
@@ -1364,7 +1363,7 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
         L.reading = c->reading;
         L.tp = c->tp;
         L.tab = c->d_tab;
-        L.m64 = c->d_m64;
+        L.n64 = c->d_n64;
         L.nHI = c->d_nhi;
         L.gbar = dL_dgamma;
         L.nbar = c->d_nbar;
@@ -1380,10 +1379,8 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
         L.gbar_T = c->d_gbar_T;
         L.nbar_T = c->d_nbar_T;
         L.kept = kept ? c->d_keep : nullptr;
-        L.rec_piece_bytes = layers ? (kept ? plans[3].keep_bytes : plans[3].rec_bytes) : 0;
-        L.rec_rk_off = kept ? plans[3].rec_bytes : 0;
+        L.rec_piece_bytes = layers ? plans[3].rec_bytes : 0;
         L.rec_cap = layers ? plans[3].rec_cap : 0;
-        L.split = c->adj_split != 0;
         L.early_exit = early;
         L.sq_table = layers && plans[3].sq_table;
         for (int t = tmax; t >= 0; --t) {

@@ -3,6 +3,7 @@
 // the short-characteristics cell update.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace asora {
@@ -141,19 +142,59 @@ __host__ __device__ __forceinline__ double log_f64(double a)
     return 2.0 * s * p + (double)e * 0.69314718055994530942;
 }
 
+// log2(x) in FP32: the hardware instruction on the GPU (about 1 ulp).
+__host__ __device__ __forceinline__ float log2_fast(float x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_logf(x);
+#else
+    return log2f(x);
+#endif
+}
+
+// ln(1 + z) / z for z in [-4e-4, 0.0357], relative error 4e-9 (least-squares
+// Chebyshev fit of degree 3).
+__host__ __device__ __forceinline__ float log1p_ratio(float z)
+{
+    return 1.f + z * (-0.499998027f + z * (0.333041105f + z * -0.236445958f));
+}
+
+// (e^x - 1) / x for x in [-0.5, 0.02], relative error 9e-9 (fit of degree 5).
+__host__ __device__ __forceinline__ float expm1_ratio(float x)
+{
+    return 1.f + x * (0.499999934f + x * (0.166663813f +
+                      x * (0.0416367197f + x * (0.00820327023f + x * 0.00113352495f))));
+}
+
 // --------------------------------------------------------------------------
 // Photoionization table P(tau) (eq. tables, Section 2.2, normalised to P(0)=1)
 // in the form the kernels read it.  Node k sits at x_k = x_lo + k h, x = ln tau.
 // Between nodes ln P is the cubic Hermite spline with node values y_k = ln P_k
 // and node slopes m_k = d ln P / d ln tau = tau_k P'_k / P_k.  Below the first
 // node P is the tangent line there; above the last node it is constant.
+//
+// Node k holds all that interval [x_k, x_k+1] needs, in one aligned 32-byte
+// line: a lookup is two adjacent 16-byte loads, and the cubic needs no
+// arithmetic to set up.  A position within the interval follows from
+// z = tau / tau_k - 1 (one FP64 multiply-add, exact to 1e-16) as
+// f = ln(1 + z) / h, a short polynomial because z < e^h - 1: no logarithm in
+// FP64, only an FP32 one to find k.
 // --------------------------------------------------------------------------
-struct TabNode {
-    double y;   // ln P_k (FP64: differences of y across many nodes must stay exact)
-    float m;    // d ln P / d ln tau at node k
-    float P;    // P_k (FP32: only multiplied, never subtracted)
+struct alignas(16) TabNode {
+    double y;            // ln P_k (FP64: differences of y across many nodes must stay exact)
+    double it;           // 1 / tau_k
+    float c1, c2, c3;    // ln P(x_k + f h) - y_k = f (c1 + f (c2 + f c3)), f in [0, 1]
+    float P;             // P_k (FP32: only multiplied, never subtracted)
 };
-static_assert(sizeof(TabNode) == 16, "TabNode must be 16 bytes");
+static_assert(sizeof(TabNode) == 32, "TabNode must be 32 bytes");
+
+// A node as the FP64 evaluations read it: as TabNode, the cubic in FP64.
+struct alignas(16) Node64 {
+    double it, P;       // 1 / tau_k, P_k
+    double c1, c2, c3;
+    double pad;
+};
+static_assert(sizeof(Node64) == 48, "Node64 must be 48 bytes");
 
 struct TabParams {
     int n;          // number of nodes
@@ -164,21 +205,28 @@ struct TabParams {
     double tau_lo;  // tau_0
     double tau_hi;  // tau_{n-1}
     float dP0;      // dP/dtau at tau_0 (slope of the linear continuation)
+    // node index of tau: ilog log2(tau) + off (tab_interval); u_in = e^h - 1
+    float ilog, off, u_in;
+    int fine;       // the nodes lie close enough, and within the FP32 range, for tab_interval
+    int tame;       // ln P changes by at most 0.34 within any interval
 };
+
+// A table is fine when its intervals are short enough for the fits above
+// (z <= e^h - 1 <= 0.0357) and its nodes are FP32 normal numbers; every table
+// of about 1600 nodes or more over 24 decades is.  Coarser ones take the
+// general evaluation (divdiff_spline_any, locate64).
+constexpr double kFineStep = 0.035;
 
 struct Cubic {
     float c1, c2, c3;   // ln P(x_j + t h) - y_j = t (c1 + t (c2 + t c3)), t in [0,1]
 };
 
-__host__ __device__ __forceinline__ Cubic cubic_at(const TabNode *T, int j, float h)
+__host__ __device__ __forceinline__ Cubic cubic_at(const TabNode *T, int j)
 {
-    const TabNode a = T[j], b = T[j + 1];
-    const float d = (float)(b.y - a.y);
-    const float hm0 = h * a.m, hm1 = h * b.m;
     Cubic c;
-    c.c1 = hm0;
-    c.c2 = 3.f * d - 2.f * hm0 - hm1;
-    c.c3 = -2.f * d + hm0 + hm1;
+    c.c1 = T[j].c1;
+    c.c2 = T[j].c2;
+    c.c3 = T[j].c3;
     return c;
 }
 
@@ -194,21 +242,70 @@ __host__ __device__ __forceinline__ float cubic_dd(const Cubic &c, float t1, flo
     return c.c1 + c.c2 * (t1 + t2) + c.c3 * (t1 * t1 + t1 * t2 + t2 * t2);
 }
 
+// Interval of tau in a fine table, tau_lo <= tau <= tau_hi.  The FP32 position
+// (off by up to 3e-4 of an interval) can name the neighbouring interval when
+// tau is that close to a node; the cubic, C1 across nodes, then continues into
+// it by that much, which changes ln P by less than 1e-10 of an interval's.
+__host__ __device__ __forceinline__ int tab_interval(const TabParams &tp, float tau)
+{
+    const int j = (int)(tp.ilog * log2_fast(tau) + tp.off);
+    return j < 0 ? 0 : (j > tp.n - 2 ? tp.n - 2 : j);
+}
+
+// The spline part of a fine table over [a, a + dt], tau_lo <= a and a + dt <=
+// tau_hi (af, dtf: a and dt in FP32): P(a) and the drop 1 - P(a + dt) / P(a).
+// Formed in log space, 1 - e^dy with dy = delta ln P, so that it keeps full
+// relative accuracy when dt is small against a:
+//  - dt below an interval's width (u = dt / a < e^h - 1): dy from the divided
+//    differences of the one or two cubics between the ends, over
+//    dx = ln(1 + u) / h, which u gives directly;
+//  - else node values (FP64 difference) plus the ends' cubics.
+// For a zero-width interval (returns true) the drop is -d ln P / d ln tau.
+__host__ __device__ __forceinline__ bool spline_drop(const TabNode *T, const TabParams &tp, double a, double dt,
+                                                     float af, float dtf, float *Pa, float *drop)
+{
+    // both ends' nodes are found first, so that their loads share one latency
+    const float u = dtf * rcp_nr(af);
+    const bool near = u < tp.u_in;
+    const int ja = tab_interval(tp, af);
+    int jb = tab_interval(tp, af + dtf);
+    jb = near && jb > ja + 1 ? ja + 1 : (jb < ja ? ja : jb);
+    const TabNode na = T[ja], nb = T[jb];
+    const Cubic ca = {na.c1, na.c2, na.c3}, cb = {nb.c1, nb.c2, nb.c3};
+    const float za = (float)(a * na.it - 1.0);
+    const float fa = za * tp.inv_hf * log1p_ratio(za);
+    const float va = cubic_val(ca, fa);
+    *Pa = na.P * exp_small(va);
+    if (!(u > 1e-12f)) {
+        *drop = -cubic_dd(ca, fa, fa) * tp.inv_hf;
+        return true;
+    }
+    float dy;
+    if (near) {
+        const float dx = u * tp.inv_hf * log1p_ratio(u);
+        const float d1 = jb > ja ? fminf(dx, fmaxf(1.f - fa, 0.f)) : dx, d2 = dx - d1;
+        dy = d1 * cubic_dd(ca, fa, fa + d1) + d2 * cubic_dd(cb, 0.f, d2);
+    } else {
+        const float zb = (float)((a + dt) * nb.it - 1.0);
+        const float fb = zb * tp.inv_hf * log1p_ratio(zb);
+        dy = (float)(nb.y - na.y) + (cubic_val(cb, fb) - va);
+    }
+    *drop = dy > -0.5f ? -dy * expm1_ratio(dy) : 1.f - exp_small(dy);
+    return false;
+}
+
 // Divided difference [P(a+dt) - P(a)] / dt of the spline part, for
-// tau_lo <= a and a + dt <= tau_hi.  The difference is formed in log space,
-// P(a) expm1(delta ln P), so that it keeps full relative accuracy when dt is
-// small against a; delta ln P is the exact difference of the cubic when both
-// ends share a node interval, the sum over the two pieces when they sit in
-// neighbouring intervals, and node values plus end corrections otherwise.
-__host__ __device__ __forceinline__ float divdiff_spline(const TabNode *T, const TabParams &tp, double a,
-                                                         double dt)
+// tau_lo <= a and a + dt <= tau_hi, for any node spacing: positions from FP64
+// logarithms, the difference in log space as in drop_spline.
+__host__ __device__ __forceinline__ float divdiff_spline_any(const TabNode *T, const TabParams &tp, double a,
+                                                             double dt)
 {
     const double xa = log_fast(a);
     const double ta = (xa - tp.x_lo) * tp.inv_h;
     int ja = (int)floor(ta);
     ja = ja < 0 ? 0 : (ja > tp.n - 2 ? tp.n - 2 : ja);
     const float fa = (float)(ta - (double)ja);
-    const Cubic ca = cubic_at(T, ja, tp.h);
+    const Cubic ca = cubic_at(T, ja);
     const float corr_a = cubic_val(ca, fa);
     const float Pa = T[ja].P * exp_small(corr_a);
     const float u = (float)dt * rcp_nr((float)a);
@@ -228,7 +325,7 @@ __host__ __device__ __forceinline__ float divdiff_spline(const TabNode *T, const
         } else {
             const float d1 = 1.f - fa;
             const float d2 = dtn - d1;
-            const Cubic cb = cubic_at(T, ja + 1, tp.h);
+            const Cubic cb = cubic_at(T, ja + 1);
             dy = d1 * cubic_dd(ca, fa, 1.f) + d2 * cubic_dd(cb, 0.f, d2);
         }
     } else {
@@ -239,10 +336,10 @@ __host__ __device__ __forceinline__ float divdiff_spline(const TabNode *T, const
         if (jb == ja) {
             dy = (float)(tbb - ta) * cubic_dd(ca, fa, fb);
         } else if (jb == ja + 1) {
-            const Cubic cb = cubic_at(T, jb, tp.h);
+            const Cubic cb = cubic_at(T, jb);
             dy = (1.f - fa) * cubic_dd(ca, fa, 1.f) + fb * cubic_dd(cb, 0.f, fb);
         } else {
-            const Cubic cb = cubic_at(T, jb, tp.h);
+            const Cubic cb = cubic_at(T, jb);
             dy = (float)(T[jb].y - T[ja].y) + (cubic_val(cb, fb) - corr_a);
         }
     }
@@ -250,22 +347,55 @@ __host__ __device__ __forceinline__ float divdiff_spline(const TabNode *T, const
 }
 
 // -D = -[P(a+dt) - P(a)] / dt >= 0 of the full interpolant (linear piece,
-// spline, constant piece), for a >= 0 and dt >= 0.  An interval that
-// straddles a piece boundary is split; the pieces' slopes are averaged with
-// their lengths as weights (all of one sign, so nothing cancels).
-__host__ __device__ __forceinline__ float neg_divdiff(const TabNode *T, const TabParams &tp, double a,
-                                             double dt)
+// spline, constant piece), for a >= 0 and dt >= 0, any node spacing.  An
+// interval that straddles a piece boundary is split; the pieces' slopes are
+// averaged with their lengths as weights (all of one sign, so nothing
+// cancels).
+__host__ __device__ __forceinline__ float neg_divdiff_any(const TabNode *T, const TabParams &tp, double a,
+                                                          double dt)
 {
-    if (a >= tp.tau_hi) return 0.f;
     const double b = a + dt;
-    if (b < tp.tau_lo) return -tp.dP0;
-    if (a >= tp.tau_lo && b <= tp.tau_hi) return -divdiff_spline(T, tp, a, dt);
+    if (a >= tp.tau_lo && b <= tp.tau_hi) return -divdiff_spline_any(T, tp, a, dt);
     const double aH = a > tp.tau_lo ? a : tp.tau_lo;
     const double bH = b < tp.tau_hi ? b : tp.tau_hi;
     const double lenL = a < tp.tau_lo ? tp.tau_lo - a : 0.0;
     const double lenH = bH - aH;
-    const double DH = lenH > 0 ? (double)divdiff_spline(T, tp, aH, lenH) : 0.0;
+    const double DH = lenH > 0 ? (double)divdiff_spline_any(T, tp, aH, lenH) : 0.0;
     return (float)(-((double)tp.dP0 * lenL + DH * lenH) * rcp_f64(dt));
+}
+
+// -D of the full interpolant of a fine table.  One evaluation serves every
+// interval: the spline's drop over the part of [a, a + dt] inside the table
+// plus the linear piece's below it, over dt (nothing is absorbed beyond the
+// last node).
+__host__ __device__ __forceinline__ float neg_divdiff_fine(const TabNode *T, const TabParams &tp, double a,
+                                                           double dt)
+{
+    if (a >= tp.tau_hi) return 0.f;
+    float low = 0.f;       // drop of the linear piece
+    double aH = a, len = dt;
+    if (a < tp.tau_lo) {
+        if (a + dt < tp.tau_lo) return -tp.dP0;
+        aH = tp.tau_lo;
+        len = a + dt - aH;
+        low = -tp.dP0 * (float)(aH - a);
+    }
+    const double room = tp.tau_hi - aH;
+    len = len < room ? len : room;
+    const float af = (float)aH;
+    float Pa, drop;
+    const bool flat = spline_drop(T, tp, aH, len, af, (float)len, &Pa, &drop);
+    return (Pa * drop + low) * rcp_nr(flat && low == 0.f ? af : (float)dt);
+}
+
+// -D of the full interpolant, any table.
+__host__ __device__ __forceinline__ float neg_divdiff(const TabNode *T, const TabParams &tp, double a,
+                                             double dt)
+{
+    if (tp.fine) return neg_divdiff_fine(T, tp, a, dt);
+    if (a >= tp.tau_hi) return 0.f;
+    if (a + dt < tp.tau_lo) return -tp.dP0;
+    return neg_divdiff_any(T, tp, a, dt);
 }
 
 // --------------------------------------------------------------------------
@@ -397,6 +527,29 @@ __host__ __device__ __forceinline__ int wrap(int v, int N)
     return v;
 }
 
+// A value that is the same in every lane, in a scalar register: the compiler
+// does not see that a root, or a load it issues as a vector one, is uniform.
+__host__ __device__ __forceinline__ int uniform(int x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readfirstlane(x);
+#else
+    return x;
+#endif
+}
+
+__host__ __device__ __forceinline__ double uniform(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+#else
+    return x;
+#endif
+}
+
 // Everything one cell update needs that is uniform over a piece.
 struct CellCtx {
     Piece pc;
@@ -407,7 +560,8 @@ struct CellCtx {
     double half_col;       // n_HI(s) alpha / 2
     double coef;           // Q sigma0 / (4 pi alpha^2)
     const TabNode *tab;
-    const double *m64;     // FP64 node slopes (adjoint only; may be NULL in the forward)
+    const double *m64;     // FP64 node slopes (adjoint on the host only)
+    const Node64 *n64 = nullptr;   // the table in FP64 (adjoint kernels)
     TabParams tp;
     const double *ring;    // [4][ring_cap] exit columns of shells q-1..q-3
     const int *rowbase;    // [4][row_cap]
@@ -551,12 +705,171 @@ __host__ __device__ __forceinline__ double exp_f64(double x)
     return ldexp(p, (int)k);
 }
 
-// P(tau), dP/dtau and d2P/dtau2 of the interpolant in FP64 (node slopes m64
-// in FP64: gradients can be sums of large terms of both signs), given
-// x = ln tau (used only inside the table).
-__host__ __device__ __forceinline__ void tab_eval64_x(const TabNode *T, const double *m64,
-                                                      const TabParams &tp, double tau, double x, double *P,
-                                                      double *d1, double *d2)
+// A constant in a scalar register pair, written there where it is used.  A
+// polynomial's FP64 coefficients otherwise count as loop invariants: the
+// compiler keeps all of them live across the sweep, runs out of scalar
+// registers and fetches each one back from vector lanes (v_readlane) at every
+// use, which cost the adjoint's rate batch more than the polynomials did.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <uint64_t B>
+__device__ __forceinline__ double scalar_const()
+{
+    uint32_t lo, hi;
+    asm volatile("s_mov_b32 %0, %1" : "=s"(lo) : "i"((uint32_t)B));
+    asm volatile("s_mov_b32 %0, %1" : "=s"(hi) : "i"((uint32_t)(B >> 32)));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// p x + constant.  (The three-operand form: from C++ the compiler makes the
+// two-operand one, with a copy of the constant to vector registers first.)
+template <uint64_t B>
+__device__ __forceinline__ double horner_step(double p, double x)
+{
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(p), "v"(x), "s"(scalar_const<B>()));
+    return d;
+}
+#define ASORA_K64(k) scalar_const<__builtin_bit_cast(uint64_t, (double)(k))>()
+#define ASORA_HORNER(p, x, k) horner_step<__builtin_bit_cast(uint64_t, (double)(k))>(p, x)
+#else
+#define ASORA_K64(k) (k)
+#define ASORA_HORNER(p, x, k) ((p) * (x) + (k))
+#endif
+
+// ln(1 + z) / z for z in [-4e-4, 0.0357] in FP64, relative error 2e-16 (fit of degree 7).
+__host__ __device__ __forceinline__ double log1p_ratio64(double z)
+{
+    double p = ASORA_K64(-0.11043569751386011);
+    p = ASORA_HORNER(p, z, 0.14204542720061356);
+    p = ASORA_HORNER(p, z, -0.16664294348998443);
+    p = ASORA_HORNER(p, z, 0.19999961760275356);
+    p = ASORA_HORNER(p, z, -0.24999999670463968);
+    p = ASORA_HORNER(p, z, 0.33333333331994569);
+    p = ASORA_HORNER(p, z, -0.49999999999998213);
+    return p * z + 1.0;
+}
+
+// (e^x - 1) / x for |x| <= 0.345 in FP64, relative error 2e-16 (fit of degree 10).
+__host__ __device__ __forceinline__ double expm1_ratio64(double x)
+{
+    double p = ASORA_K64(2.5108329700430637e-08);
+    p = ASORA_HORNER(p, x, 2.7625767782798879e-07);
+    p = ASORA_HORNER(p, x, 2.7557246246165012e-06);
+    p = ASORA_HORNER(p, x, 2.4801505749609047e-05);
+    p = ASORA_HORNER(p, x, 0.00019841269884246534);
+    p = ASORA_HORNER(p, x, 0.0013888888931394537);
+    p = ASORA_HORNER(p, x, 0.0083333333333221633);
+    p = ASORA_HORNER(p, x, 0.04166666666657623);
+    p = ASORA_HORNER(p, x, 0.16666666666666677);
+    p = ASORA_HORNER(p, x, 0.50000000000000056);
+    return p * x + 1.0;
+}
+
+// e^x - 1 for x = a change of ln P within one interval of the table: the fit
+// where every interval's is small enough for it (tame), else the general
+// exponential.  FAST (here and below): the caller knows that the table is
+// fine and tame, and the general forms are compiled out.
+template <bool FAST>
+__host__ __device__ __forceinline__ double expm1_step64(const TabParams &tp, double x)
+{
+    if (FAST || tp.tame) return x * expm1_ratio64(x);
+    return fabs(x) <= 0.345 ? x * expm1_ratio64(x) : exp_f64(x) - 1.0;
+}
+
+__host__ __device__ __forceinline__ Node64 make_node64(const TabNode *T, const double *m64, const TabParams &tp,
+                                                       int j)
+{
+    Node64 n;
+    n.it = T[j].it;
+    n.P = exp_f64(T[j].y);
+    n.pad = 0.0;
+    const double d = T[j + 1].y - T[j].y, hm0 = tp.h64 * m64[j], hm1 = tp.h64 * m64[j + 1];
+    n.c1 = hm0;
+    n.c2 = 3.0 * d - 2.0 * hm0 - hm1;
+    n.c3 = -2.0 * d + hm0 + hm1;
+    return n;
+}
+
+// The table's nodes in FP64: an array of them (kernels), or formed from the
+// two tables (nodes 0 .. n - 2).
+struct NodeArray {
+    const Node64 *n;
+    __host__ __device__ __forceinline__ Node64 operator()(int j) const { return n[j]; }
+};
+struct NodeTables {
+    const TabNode *T;
+    const double *m64;
+    const TabParams &tp;
+    __host__ __device__ __forceinline__ Node64 operator()(int j) const { return make_node64(T, m64, tp, j); }
+};
+
+// Position f of tau in interval j of a fine table, whose node is nd (both
+// corrected where the FP32 position of tab_interval named the wrong side of a
+// node: the second derivative jumps there).
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ double fine_position(const Nodes &nodes, const TabParams &tp, double tau, int *j,
+                                                         Node64 *nd)
+{
+    double z = tau * nd->it - 1.0;
+    double f = z * log1p_ratio64(z) * tp.inv_h;
+    const int k = f < 0.0 && *j > 0 ? *j - 1 : (f > 1.0 && *j < tp.n - 2 ? *j + 1 : *j);
+    if (k != *j) {
+        *j = k;
+        *nd = nodes(k);
+        z = tau * nd->it - 1.0;
+        f = z * log1p_ratio64(z) * tp.inv_h;
+    }
+    return f;
+}
+
+// Interval j of tau and the position f in it, tau_lo <= tau <= tau_hi.
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ void locate64(const Nodes &nodes, const TabParams &tp, double tau, int *j,
+                                                  double *f, Node64 *nd)
+{
+    if (FAST || tp.fine) {
+        *j = tab_interval(tp, (float)tau);
+        *nd = nodes(*j);
+        *f = fine_position<FAST>(nodes, tp, tau, j, nd);
+    } else {
+        const double t = (log_f64(tau) - tp.x_lo) * tp.inv_h;
+        const int k = (int)floor(t);
+        *j = k < 0 ? 0 : (k > tp.n - 2 ? tp.n - 2 : k);
+        *nd = nodes(*j);
+        *f = t - (double)*j;
+    }
+}
+
+// ln P(f) - y, d ln P / df and half d2 ln P / df2 of a node's cubic.
+__host__ __device__ __forceinline__ double cubic64(const Node64 &n, double f)
+{
+    return f * (n.c1 + f * (n.c2 + f * n.c3));
+}
+__host__ __device__ __forceinline__ double cubic64_d(const Node64 &n, double f)
+{
+    return n.c1 + f * (2.0 * n.c2 + 3.0 * f * n.c3);
+}
+__host__ __device__ __forceinline__ double cubic64_dd(const Node64 &n, double f1, double f2)
+{
+    return n.c1 + n.c2 * (f1 + f2) + n.c3 * (f1 * f1 + f1 * f2 + f2 * f2);
+}
+
+// P'' of the interpolant at tau.
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ double curvature64(const Nodes &nodes, const TabParams &tp, double tau)
+{
+    if (tau < tp.tau_lo || tau >= tp.tau_hi) return 0.0;
+    int j;
+    double f;
+    Node64 n;
+    locate64<FAST>(nodes, tp, tau, &j, &f, &n);
+    const double yx = cubic64_d(n, f) * tp.inv_h, yxx = (2.0 * n.c2 + 6.0 * f * n.c3) * tp.inv_h * tp.inv_h;
+    const double it = rcp_f64(tau);
+    return (n.P + n.P * expm1_step64<FAST>(tp, cubic64(n, f))) * (yx * yx + yxx - yx) * it * it;
+}
+
+// P(tau), dP/dtau and d2P/dtau2 of the interpolant in FP64.
+__host__ __device__ __forceinline__ void tab_eval64(const TabNode *T, const double *m64, const TabParams &tp,
+                                                    double tau, double *P, double *d1, double *d2)
 {
     if (tau < tp.tau_lo) {
         *P = exp_f64(T[0].y) + (double)tp.dP0 * (tau - tp.tau_lo);
@@ -570,35 +883,90 @@ __host__ __device__ __forceinline__ void tab_eval64_x(const TabNode *T, const do
         *d2 = 0.0;
         return;
     }
-    const double t = (x - tp.x_lo) * tp.inv_h;
-    int j = (int)floor(t);
-    j = j < 0 ? 0 : (j > tp.n - 2 ? tp.n - 2 : j);
-    const double f = t - (double)j;
-    const double h = tp.h64;
-    const double d = T[j + 1].y - T[j].y;
-    const double hm0 = h * m64[j], hm1 = h * m64[j + 1];
-    const double c1 = hm0, c2 = 3.0 * d - 2.0 * hm0 - hm1, c3 = -2.0 * d + hm0 + hm1;
-    const double y = T[j].y + f * (c1 + f * (c2 + f * c3));
-    const double yx = (c1 + f * (2.0 * c2 + 3.0 * f * c3)) * tp.inv_h;
-    const double yxx = (2.0 * c2 + 6.0 * f * c3) * tp.inv_h * tp.inv_h;
-    const double p = exp_f64(y);
-    const double it = rcp_f64(tau);   // tau in [tau_lo, tau_hi): FP32 normal range
+    const NodeTables nodes{T, m64, tp};
+    int j;
+    double f;
+    Node64 n;
+    locate64<false>(nodes, tp, tau, &j, &f, &n);
+    const double p = n.P + n.P * expm1_step64<false>(tp, cubic64(n, f));
     *P = p;
-    *d1 = p * yx * it;
-    *d2 = p * (yx * yx + yxx - yx) * it * it;
+    *d1 = p * cubic64_d(n, f) * tp.inv_h * rcp_f64(tau);
+    *d2 = curvature64<false>(nodes, tp, tau);
 }
 
-__host__ __device__ __forceinline__ void tab_eval64(const TabNode *T, const double *m64,
-                                                    const TabParams &tp, double tau, double *P,
-                                                    double *d1, double *d2)
-{
-    tab_eval64_x(T, m64, tp, tau, tau >= tp.tau_lo ? log_f64(tau) : 0.0, P, d1, d2);
-}
+// The FP64 evaluation of P over [a, a + dt], a < tau_hi: P(a), d ln P / d ln tau
+// at a, the change P(b) - P(a), b = a + dt, and P'(b).  Within an interval's
+// width (near: u = dt / a < e^h - 1) the change is formed in log space,
+// P(a) (e^dy - 1) with dy from the divided differences of the one or two
+// cubics between the ends (see spline_drop); further out, and for a coarse
+// table, as the difference of the two values.
+struct RateEnds {
+    bool in;            // a >= tau_lo
+    double P, ia, yx;   // P(a), 1 / a, d ln P / d ln tau (inside)
+    double change, Pb1;
+};
 
-// ln(1 + e) for |e| <= 1e-4 to 3e-17 absolute (the series to e^3).
-__host__ __device__ __forceinline__ double log1p_small(double e)
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ RateEnds rate_ends(const Nodes &nodes, const TabParams &tp, double a, double dt)
 {
-    return e * (1.0 + e * (-0.5 + e * (1.0 / 3.0)));
+    RateEnds q;
+    q.in = a >= tp.tau_lo;
+    const double aH = q.in ? a : tp.tau_lo;
+    const double b = a + dt, bH = b < tp.tau_hi ? (b > aH ? b : aH) : tp.tau_hi;
+    q.ia = rcp_f64(aH);
+    const double u = (b < tp.tau_hi ? dt : bH - a) * q.ia;
+    const bool near = q.in && (FAST || tp.fine) && u < (double)tp.u_in;
+    int ja, jb;
+    double fa, fb;
+    Node64 na, nb;
+    if (FAST || tp.fine) {
+        // both ends' nodes are found first, so that their loads share one latency
+        ja = tab_interval(tp, (float)aH);
+        jb = tab_interval(tp, (float)bH);
+        jb = near && jb > ja + 1 ? ja + 1 : (jb < ja ? ja : jb);
+        na = nodes(ja);
+        nb = nodes(jb);
+        fa = fine_position<FAST>(nodes, tp, aH, &ja, &na);
+    } else {
+        locate64<FAST>(nodes, tp, aH, &ja, &fa, &na);
+        jb = ja;
+        nb = na;
+    }
+    const double ea = expm1_step64<FAST>(tp, cubic64(na, fa));
+    q.P = na.P + na.P * ea;
+    if (!q.in) q.P += (double)tp.dP0 * (a - tp.tau_lo);
+    q.yx = cubic64_d(na, fa) * tp.inv_h;
+    double x, Pb;
+    if (near) {
+        const double dx = u * log1p_ratio64(u) * tp.inv_h;
+        double d1 = dx, d2 = 0.0;
+        if (fa + dx > 1.0 && ja < tp.n - 2) {
+            d1 = 1.0 - fa;
+            d2 = dx - d1;
+            if (jb != ja + 1) nb = nodes(ja + 1);   // (b's FP32 position was off by one)
+        }
+        x = d1 * cubic64_dd(na, fa, fa + d1);
+        if (d2 > 0.0) {
+            x += d2 * cubic64_dd(nb, 0.0, d2);
+            fb = d2;
+        } else {
+            nb = na;
+            fb = fa + d1;
+        }
+        q.change = q.P * expm1_step64<FAST>(tp, x);
+        Pb = q.P + q.change;
+    } else {
+        if (FAST || tp.fine) fb = fine_position<FAST>(nodes, tp, bH, &jb, &nb);
+        else locate64<FAST>(nodes, tp, bH, &jb, &fb, &nb);
+        Pb = nb.P + nb.P * expm1_step64<FAST>(tp, cubic64(nb, fb));
+        q.change = Pb - q.P;
+    }
+    q.Pb1 = b < tp.tau_hi ? Pb * cubic64_d(nb, fb) * tp.inv_h * rcp_f64(bH) : 0.0;
+    if (b < tp.tau_lo) {
+        q.Pb1 = (double)tp.dP0;
+        q.change = (double)tp.dP0 * dt;
+    }
+    return q;
 }
 
 // D = [P(a+dt) - P(a)] / dt and its partial derivatives dD/da (dt fixed) and
@@ -607,42 +975,60 @@ __host__ __device__ __forceinline__ double log1p_small(double e)
 // the integral forms dD/da = mean of P'' over [a, a+dt] and
 // dD/d(dt) = (1/dt^2) int_0^dt t P''(a+t) dt are taken with two-point Gauss
 // rules (error O((dt/a)^4)).
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ void rate_derivs_nodes(const Nodes &nodes, const TabParams &tp, double a,
+                                                           double dt, double *D, double *dDda, double *dDddt)
+{
+    if (a >= tp.tau_hi) {
+        *D = *dDda = *dDddt = 0.0;
+        return;
+    }
+    const RateEnds q = rate_ends<FAST>(nodes, tp, a, dt);
+    const double Pa1 = q.in ? q.P * q.yx * q.ia : (double)tp.dP0;
+    if (dt > 1e-4 * a && dt > 0.0) {
+        const double idt = dt > 1e-30 ? rcp_f64(dt) : 1.0 / dt;
+        const double d = q.change * idt;
+        *D = d;
+        *dDda = (q.Pb1 - Pa1) * idt;
+        *dDddt = (q.Pb1 - d) * idt;
+        return;
+    }
+    // Gauss-Legendre (mean of P'') and Gauss-Jacobi for the weight t (second);
+    // a loop, not four copies: cells this thin are rare
+    const double w1 = (9.0 + 2.449489742783178) / 36.0, w2 = (9.0 - 2.449489742783178) / 36.0;
+    double da = 0.0, ddt = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) {
+        // nodes (1 -+ 1/sqrt3)/2 and (6 -+ sqrt6)/10
+        const double g = k == 0 ? 0.21132486540518711
+                                : (k == 1 ? 0.78867513459481289 : (k == 2 ? 0.35505102572168219 : 0.84494897427831781));
+        const double c = curvature64<FAST>(nodes, tp, a + g * dt);
+        da += k < 2 ? 0.5 * c : 0.0;
+        ddt += k < 2 ? 0.0 : (k == 2 ? w1 : w2) * c;
+    }
+    *dDda = da;
+    *dDddt = ddt;
+    *D = Pa1 + 0.5 * dt * da;
+}
+
 __host__ __device__ __forceinline__ void rate_derivs64(const TabNode *T, const double *m64,
                                                        const TabParams &tp, double a, double dt,
                                                        double *D, double *dDda, double *dDddt)
 {
-    const bool in = a >= tp.tau_lo;   // then a > 0
-    const double xa = in ? log_f64(a) : 0.0;
-    double Pa, Pa1, Pa2;
-    tab_eval64_x(T, m64, tp, a, xa, &Pa, &Pa1, &Pa2);
-    if (dt > 1e-4 * a && dt > 0.0) {
-        double Pb, Pb1, Pb2;
-        tab_eval64(T, m64, tp, a + dt, &Pb, &Pb1, &Pb2);
-        const double idt = dt > 1e-30 ? rcp_f64(dt) : 1.0 / dt;
-        const double d = (Pb - Pa) * idt;
-        *D = d;
-        *dDda = (Pb1 - Pa1) * idt;
-        *dDddt = (Pb1 - d) * idt;
-        return;
-    }
-    // Gauss-Legendre (mean of P'') and Gauss-Jacobi for the weight t (second)
-    const double g1 = 0.21132486540518711, g2 = 0.78867513459481289;
-    const double j1 = 0.35505102572168219, j2 = 0.84494897427831781;   // (6 -+ sqrt6)/10
-    const double w1 = (9.0 + 2.449489742783178) / 36.0, w2 = (9.0 - 2.449489742783178) / 36.0;
-    // the nodes lie within a relative 1e-4 of a: inside the table their
-    // logarithms are ln a + ln(1 + g dt / a) (a node can enter the table only
-    // from an a just below its start: it takes its own logarithm)
-    const double ea = in ? dt * rcp_f64(a) : 0.0;
-    auto d2_at = [&](double g) {
-        double P_, d1_, d2_;
-        if (in) tab_eval64_x(T, m64, tp, a + g * dt, xa + log1p_small(g * ea), &P_, &d1_, &d2_);
-        else tab_eval64(T, m64, tp, a + g * dt, &P_, &d1_, &d2_);
-        return d2_;
-    };
-    const double q1 = d2_at(g1), q2 = d2_at(g2), r1 = d2_at(j1), r2 = d2_at(j2);
-    *dDda = 0.5 * (q1 + q2);
-    *dDddt = w1 * r1 + w2 * r2;
-    *D = Pa1 + 0.5 * dt * (*dDda);
+    const NodeTables nodes{T, m64, tp};
+    rate_derivs_nodes<false>(nodes, tp, a, dt, D, dDda, dDddt);
+}
+
+// -D in FP64 alone (the rate of a forward that keeps records).
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ double neg_divdiff64(const Nodes &nodes, const TabParams &tp, double a, double dt)
+{
+    if (a >= tp.tau_hi) return 0.0;
+    const RateEnds q = rate_ends<FAST>(nodes, tp, a, dt);
+    if (dt > 1e-4 * a || (q.in && (FAST || tp.fine) && dt > 1e-12 * a))
+        return -q.change * (dt > 1e-30 ? rcp_f64(dt) : 1.0 / dt);
+    const double Pa1 = q.in ? q.P * q.yx * q.ia : (double)tp.dP0;
+    return -(Pa1 + 0.5 * dt * curvature64<FAST>(nodes, tp, a + 0.5 * dt));
 }
 
 // Reverse-mode update of one cell (not the source).  Given the total adjoint
@@ -755,7 +1141,11 @@ __host__ __device__ __forceinline__ void cell_adjoint(const CellCtx &X, int q, i
     const double gbar = (owned && ta < X.tp.tau_hi) ? gbar_grid[cp] : 0.0;
     if (gbar != 0.0) {
         double D, Da, Ddt;
+#if defined(__HIP_DEVICE_COMPILE__)
+        rate_derivs_nodes<false>(NodeArray{X.n64}, X.tp, ta, X.sigma0 * dN, &D, &Da, &Ddt);
+#else
         rate_derivs64(X.tab, X.m64, X.tp, ta, X.sigma0 * dN, &D, &Da, &Ddt);
+#endif
         const double k = -X.coef / (double)r2;          // Gamma = k D
         Nin_bar += gbar * k * Da * X.sigma0;
         dN_bar += gbar * k * Ddt * X.sigma0;
@@ -777,27 +1167,36 @@ __host__ __device__ __forceinline__ void cell_adjoint(const CellCtx &X, int q, i
 }
 
 // Adjoint of the source cell's own rate: d Gamma_s / d n_HI(s) and Gamma_s.
-__host__ __device__ __forceinline__ void source_cell_adjoint(const TabNode *T, const double *m64,
-                                                             const TabParams &tp, double sigma0,
-                                                             double alpha, double Q, double n_s,
-                                                             double gbar, double *nbar, double *qbar)
+template <bool FAST, class Nodes>
+__host__ __device__ __forceinline__ void source_cell_adjoint_nodes(const Nodes &nodes, const TabParams &tp,
+                                                                   double sigma0, double alpha, double Q, double n_s,
+                                                                   double gbar, double *nbar, double *qbar)
 {
     const double tau_s = sigma0 * n_s * alpha * 0.5;
     double D, Da, Ddt;
-    rate_derivs64(T, m64, tp, 0.0, tau_s, &D, &Da, &Ddt);
+    rate_derivs_nodes<FAST>(nodes, tp, 0.0, tau_s, &D, &Da, &Ddt);
     const double k = -Q * sigma0 / (2.0 * alpha * alpha);
     *nbar = gbar * k * Ddt * sigma0 * alpha * 0.5;
     *qbar = gbar * k * D;
 }
 
+__host__ __device__ __forceinline__ void source_cell_adjoint(const TabNode *T, const double *m64,
+                                                             const TabParams &tp, double sigma0,
+                                                             double alpha, double Q, double n_s,
+                                                             double gbar, double *nbar, double *qbar)
+{
+    source_cell_adjoint_nodes<false>(NodeTables{T, m64, tp}, tp, sigma0, alpha, Q, n_s, gbar, nbar, qbar);
+}
+
 // Rate of the source cell itself: entry column 0, path half a cell, volume
 // alpha^3.
+template <bool FINE = false>
 __host__ __device__ __forceinline__ double source_cell_rate(const TabNode *T, const TabParams &tp,
                                                             double sigma0, double alpha, double Q,
                                                             double n_s)
 {
     const double tau_s = sigma0 * n_s * alpha * 0.5;
-    const float nd = neg_divdiff(T, tp, 0.0, tau_s);
+    const float nd = FINE ? neg_divdiff_fine(T, tp, 0.0, tau_s) : neg_divdiff(T, tp, 0.0, tau_s);
     return Q * sigma0 / (2.0 * alpha * alpha) * (double)nd;   // once per source
 }
 
@@ -869,13 +1268,30 @@ __host__ __device__ inline LayerPiece make_layer_piece(int p, int si, int sj, in
     return L;
 }
 
-// Largest r with r * r <= x (0 <= x < 2^24).
+// 24-bit unsigned product (operands below 2^24): a full-rate instruction on
+// the GPU, where a 32-bit integer product is a quarter-rate one.
+__host__ __device__ __forceinline__ int mul24(int a, int b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (int)__umul24((unsigned)a, (unsigned)b);
+#else
+    return a * b;
+#endif
+}
+
+// Largest r with r * r <= x.  On the GPU for 0 <= x < 2^17 (the layer sweeps'
+// squared radii): sqrt(x + 1/2) lies 1 / (4 sqrt(x)) > 6e-4 or more from any
+// integer, far beyond the hardware root's rounding.
 __host__ __device__ __forceinline__ int isqrt_floor(int x)
 {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (int)__builtin_amdgcn_sqrtf((float)x + 0.5f);
+#else
     int r = (int)sqrtf((float)x);
-    if (r * r > x) --r;
-    else if ((r + 1) * (r + 1) <= x) ++r;
+    while (r * r > x) --r;
+    while ((r + 1) * (r + 1) <= x) ++r;
     return r;
+#endif
 }
 
 // Layer m of a pyramid enumerated as a rectangle: rows u = 0..nu-1 of wv
@@ -901,14 +1317,22 @@ __host__ __device__ __forceinline__ LayerRect layer_rect(int ext_u, int ext_v, i
     return r;
 }
 
-// (u, v) of cell g of the rectangle; true if the cell is active.
+// The same for a layer that is the whole wave's, in scalar registers.
+__host__ __device__ __forceinline__ LayerRect layer_rect_uniform(int ext_u, int ext_v, int Rsq, int m)
+{
+    LayerRect r = layer_rect(ext_u, ext_v, Rsq, m);
+    r.nu = uniform(r.nu);
+    r.wv = uniform(r.wv);
+    r.total = r.nu * r.wv;
+    return r;
+}
+
+// (u, v) of cell g of the rectangle (see RectWalk::init); true if the cell is
+// active.
 __host__ __device__ __forceinline__ bool rect_cell(const LayerRect &r, int g, int &u, int &v)
 {
-    int q = (int)((float)g * rcp_approx((float)r.wv));   // off by at most one (g < 2^24)
-    if (q * r.wv > g) --q;
-    else if ((q + 1) * r.wv <= g) ++q;
-    u = q;
-    v = g - q * r.wv;
+    u = (int)(((float)g + 0.5f) * rcp_approx((float)r.wv));
+    v = g - mul24(u, r.wv);
     return g < r.total && u * u + v * v <= r.rem;
 }
 
@@ -935,7 +1359,7 @@ __host__ __device__ inline long layer_piece_capacity(int Rsq, const Extent &ex)
 }
 
 // Column record of one pyramid (a piece of layer kind) in global memory: the
-// exit column of every cell as its layer-buffer entry (layer_entry), layer by
+// exit column of every cell as its layer-buffer entry (tau_entry), layer by
 // layer in rectangle order, and for every chunk of 64 cells (layers in
 // order, chunks of a layer in order) the mask of its cells that carry a rate
 // (owned, entry optical depth inside the table).  Written by the forward
@@ -973,7 +1397,8 @@ __host__ __device__ __forceinline__ LayerRecord layer_record_at(char *base, long
     return s;
 }
 
-// Everything one layer-cell update needs that is uniform over a piece.
+// Everything one layer-cell update needs that is uniform over a piece.  The
+// layer sweeps carry columns as optical depths at 13.6 eV, t = sigma0 N.
 struct LayerX {
     int N;
     int reading;           // 0: directional source half path, 1: scalar
@@ -981,38 +1406,65 @@ struct LayerX {
     double sigma0, alpha;
     double half_col;       // n_HI(s) alpha / 2
     const double *nHI;     // n_HI in the piece's layout
+    double sa;             // sigma0 alpha: t of a cell is n_HI sa ds
+    double half_tau;       // sigma0 half_col
+    double half_n;         // half_col / alpha
     double inv_s0;         // 1 / sigma0
-    double inv_tw;         // 1 / tau_w, or 1 with geometric weights
+    double tw, inv_tw;     // tau_w and 1 / tau_w; with geometric weights infinity and 1
+};
+
+// What a sweep needs of the launch alone, formed once on the host (in scalar
+// registers of the kernel, where values formed in it would take vector ones).
+struct LayerConst {
+    double sa, inv_s0, tw, inv_tw;   // as in LayerX
+    double inv_hi;                   // 1 / tau_hi
+    double opaque, inv_opq;          // layer_opaque(tau_hi) and its inverse
 };
 
 __host__ __device__ __forceinline__ void layer_x_weights(LayerX &X)
 {
+    X.sa = X.sigma0 * X.alpha;
+    X.half_tau = X.sigma0 * X.half_col;
+    X.half_n = X.half_col / X.alpha;
     X.inv_s0 = 1.0 / X.sigma0;
+    X.tw = X.tau_w > 0.f ? (double)X.tau_w : (double)INFINITY;
     X.inv_tw = X.tau_w > 0.f ? 1.0 / (double)X.tau_w : 1.0;
 }
 
-// 24-bit unsigned product (operands below 2^24): a full-rate instruction on
-// the GPU, where a 32-bit integer product is a quarter-rate one.
-__host__ __device__ __forceinline__ int mul24(int a, int b)
+// The layer buffer holds, for every cell of the previous layer, what its
+// consumers need of its exit optical depth t for the weights
+// w = s / max(t, tau_w): the factor f = 1 / max(t, tau_w) and the product
+// g = f t.  A thick cell (t > tau_w) stores e = 1 / t > 0 (then f = e, g = 1);
+// any other cell stores e = -t, sign bit set even for t = 0 (then f = 1 /
+// tau_w, g = t / tau_w).  With geometric weights every cell stores -t (f = 1,
+// g = t).  One reciprocal per cell instead of one per neighbour.
+__host__ __device__ __forceinline__ double tau_entry(const LayerX &X, double t)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return (int)__umul24((unsigned)a, (unsigned)b);
-#else
-    return a * b;
-#endif
+    return t > X.tw ? rcp_f64(t) : -t;
 }
 
-// The layer buffer holds, for every cell of the previous layer, what its
-// consumers need of its exit column M for the optical-depth weights
-// w = s / max(sigma0 M, tau_w): the factor f = 1 / max(sigma0 M, tau_w) and the
-// product g = f M.  A cell with sigma0 M > tau_w stores h = 1 / (sigma0 M) > 0
-// (then f = h, g = 1 / sigma0); any other cell stores h = -M (then
-// f = 1 / tau_w, g = M / tau_w).  With geometric weights every cell stores -M
-// (f = 1, g = M).  One reciprocal per cell instead of one per neighbour.
-__host__ __device__ __forceinline__ double layer_entry(const LayerX &X, double M)
+// The optical depth an entry stands for.
+__host__ __device__ __forceinline__ double entry_tau(double e)
 {
-    const double t = X.sigma0 * M;
-    return (X.tau_w > 0.f && t > (double)X.tau_w) ? rcp_f64(t) : -M;
+    return e > 0.0 ? rcp_f64(e) : -e;
+}
+
+// t < lim for the optical depth of entry e; inv_lim = 1 / lim.
+__host__ __device__ __forceinline__ bool entry_below(double e, double lim, double inv_lim)
+{
+    return (e > inv_lim) | ((e <= 0.0) & (e > -lim));
+}
+
+// No entry of the four has its sign bit set: every one is thick, or the
+// buffer's padding (+0, which only neighbours of zero weight read).
+__host__ __device__ __forceinline__ int sign_word(double e)
+{
+    return (int)(uint32_t)(__builtin_bit_cast(uint64_t, e) >> 32);
+}
+
+__host__ __device__ __forceinline__ bool all_thick(double h0, double h1, double h2, double h3)
+{
+    return (sign_word(h0) | sign_word(h1) | sign_word(h2) | sign_word(h3)) >= 0;
 }
 
 // A layer whose every cell leaves with sigma0 N_out >= layer_opaque(tau_hi)
@@ -1027,35 +1479,71 @@ __host__ __device__ __forceinline__ double layer_opaque(double tau_hi)
     return tau_hi * (1.0 + 1e-12);
 }
 
+inline LayerConst make_layer_const(double sigma0, double alpha, float tau_w, double tau_hi)
+{
+    LayerX X;
+    X.sigma0 = sigma0;
+    X.alpha = alpha;
+    X.tau_w = tau_w;
+    X.half_col = 0.0;
+    layer_x_weights(X);
+    return LayerConst{X.sa, X.inv_s0, X.tw, X.inv_tw, 1.0 / tau_hi, layer_opaque(tau_hi), 1.0 / layer_opaque(tau_hi)};
+}
+
+// The sweep constants of a source of density n_s.
+__host__ __device__ __forceinline__ void layer_x_source(LayerX &X, const LayerConst &c, double n_s)
+{
+    X.sa = c.sa;
+    X.inv_s0 = c.inv_s0;
+    X.tw = c.tw;
+    X.inv_tw = c.inv_tw;
+    X.half_n = uniform(0.5 * n_s);
+    X.half_col = uniform(X.alpha * (0.5 * n_s));
+    X.half_tau = uniform(X.sigma0 * X.half_col);
+}
+
 struct LayerCell {
     uint32_t cp;    // cell index in the piece's layout
-    double Nin, Nout, dN;
-    double h;       // layer-buffer entry of the cell (layer_entry of Nout)
+    double e_in;    // entry optical depth, as an entry (entry_tau)
+    double dt;      // in-cell optical depth
+    double h;       // layer-buffer entry of the exit optical depth
+    double Nin, Nout, dN;   // the columns themselves (cm^-2): layer_cell only
     int r2;
     bool owned;
 };
+
+// Whether the pyramid owns its cell (u, v) of layer m (see LayerPiece): u and v
+// within [neg, m - tie].
+__host__ __device__ __forceinline__ bool layer_owned(const LayerPiece &L, int m, int u, int v)
+{
+    const int u0 = L.neg_u ? 1 : 0, v0 = L.neg_v ? 1 : 0;
+    return ((unsigned)(u - u0) < (unsigned)(m + 1 - u0 - (L.tie_u ? 1 : 0))) &
+           ((unsigned)(v - v0) < (unsigned)(m + 1 - v0 - (L.tie_v ? 1 : 0)));
+}
 
 // Walks the cells of a layer rectangle 64 at a time: every lane holds cell
 // g = c * 64 + lane of chunk c, and down() / up() move all lanes to chunk
 // c - 1 / c + 1 without a division (64 = q64 * wv + r64).
 struct RectWalk {
     int u, v, wv, q64, r64;
+    // Quotients by wv from its FP32 reciprocal, taken at the middle between
+    // integers: (g + 1/2) / wv lies 1 / (2 wv) or more from any integer, and
+    // its error is below 4e-7 times the quotient, so both are exact for rows
+    // and widths up to 1000.
     __host__ __device__ __forceinline__ void init(const LayerRect &r, int g)
     {
         wv = r.wv;
-        q64 = 64 / wv;
+        const float inv = rcp_approx((float)wv);
+        q64 = uniform((int)(64.5f * inv));
         r64 = 64 - q64 * wv;
-        int q = (int)((float)g * rcp_approx((float)wv));   // off by at most one (g < 2^24)
-        if (mul24(q, wv) > g) --q;
-        else if (mul24(q + 1, wv) <= g) ++q;
-        u = q;
-        v = g - mul24(q, wv);
+        u = (int)(((float)g + 0.5f) * inv);
+        v = g - mul24(u, wv);
     }
     __host__ __device__ __forceinline__ void down()
     {
         const bool b = v < r64;
-        u -= q64 + (b ? 1 : 0);
-        v += b ? wv - r64 : -r64;
+        v = v + (b ? wv : 0) - r64;
+        u = u - q64 - (b ? 1 : 0);
     }
     __host__ __device__ __forceinline__ void up()
     {
@@ -1123,6 +1611,14 @@ struct Geo {
     double om, a;
 };
 
+// Row u of a sweep's table: the factors of offset u in the current layer and
+// the pyramid's index terms of u (layer_idx_u) and of v = u (layer_idx_v).
+struct GeoRow {
+    Geo g;
+    uint32_t iu, iv;
+};
+static_assert(sizeof(GeoRow) == 24, "GeoRow must be 24 bytes");
+
 __host__ __device__ __forceinline__ Geo layer_geo(int m, double inv_m, int u)
 {
     Geo g;
@@ -1133,42 +1629,54 @@ __host__ __device__ __forceinline__ Geo layer_geo(int m, double inv_m, int u)
 
 // The short-characteristics update of cell (u, v) of layer m of a pyramid
 // (eqs. 9-12): entry column interpolated from the layer-buffer entries
-// (layer_entry) h0 .. h3 of its four neighbours in layer m - 1, (u, v),
+// (tau_entry) h0 .. h3 of its four neighbours in layer m - 1, (u, v),
 // (u - 1, v), (u, v - 1), (u - 1, v - 1), with bilinear geometric weights
 // from gu = layer_geo(u), gv = layer_geo(v) times the optical-depth factors
 // (for m = 1 the only neighbour of non-zero weight is the source, whose
-// column the cell sees directly); in-cell column n_HI alpha ds with
-// ds = r / m; ownership.  The weights must be finite wherever they are zero.
-__host__ __device__ __forceinline__ void layer_cell_core(const LayerPiece &L, const LayerX &X, int m, int u,
-                                                         int v, const Geo &gu, const Geo &gv, double ds, int r2,
-                                                         uint32_t cp, double nhi, double h0, double h1,
-                                                         double h2, double h3, LayerCell &out)
+// column the cell sees directly); in-cell optical depth dt = n_HI ads with
+// ads = sigma0 alpha ds, ds = r / m.  The weights must be finite wherever they
+// are zero.
+// Returns the entry optical depth as an entry (e_in) and the exit one's (h);
+// true if the entry one is below lim (inv_lim = 1 / lim).
+//
+// thick: all four neighbours of the cell, and on the GPU of the wave's other
+// cells, are thick (all_thick), as nearly everywhere (a cell of neutral gas
+// holds t ~ 4e3 and one of gas ionized to 1e-3 t ~ 4, so the first cell
+// already passes tau_w = 0.6).  Then the factors f are the entries themselves
+// and every g is 1: t_in = 1 / W with W = sum s e, and the exit entry is
+// 1 / (1/W + t) = W / (1 + t W), one reciprocal for the cell and no select.
+__host__ __device__ __forceinline__ bool layer_cell_core(const LayerX &X, int m, bool thick, const Geo &gu,
+                                                         const Geo &gv, double ads, double dt, double h0, double h1,
+                                                         double h2, double h3, double lim, double inv_lim,
+                                                         double *e_in, double *h)
 {
-    double Nin;
     if (m == 1) {
-        Nin = X.reading == 0 ? X.half_col * ds : X.half_col;
-    } else {
-        const double h[4] = {h0, h1, h2, h3};
-        const double sw[4] = {gu.om * gv.om, gu.a * gv.om, gu.om * gv.a, gu.a * gv.a};
-        double num = 0.0, W = 0.0;
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            const bool thick = h[n] > 0.0;
-            const double f = thick ? h[n] : X.inv_tw;
-            const double g = thick ? X.inv_s0 : -h[n] * X.inv_tw;
-            num += sw[n] * g;
-            W += sw[n] * f;
-        }
-        Nin = num * rcp_f64(W);
+        const double t = X.reading == 0 ? X.half_n * ads : X.half_tau;
+        *e_in = -t;
+        *h = tau_entry(X, t + dt);
+        return t < lim;
     }
-    const double dN = nhi * X.alpha * ds;
-    out.cp = cp;
-    out.Nin = Nin;
-    out.Nout = Nin + dN;
-    out.h = layer_entry(X, out.Nout);
-    out.dN = dN;
-    out.r2 = r2;
-    out.owned = !(L.neg_u && u == 0) && !(L.neg_v && v == 0) && !(L.tie_u && u == m) && !(L.tie_v && v == m);
+    if (thick) {
+        const double W = gv.om * (gu.om * h0 + gu.a * h1) + gv.a * (gu.om * h2 + gu.a * h3);
+        *e_in = W;
+        *h = W * rcp_f64(1.0 + dt * W);
+        return W > inv_lim;
+    }
+    const double hn[4] = {h0, h1, h2, h3};
+    const double sw[4] = {gu.om * gv.om, gu.a * gv.om, gu.om * gv.a, gu.a * gv.a};
+    double num = 0.0, W = 0.0;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const bool tk = hn[n] > 0.0;
+        const double f = tk ? hn[n] : X.inv_tw;
+        const double g = tk ? 1.0 : -hn[n] * X.inv_tw;
+        num += sw[n] * g;
+        W += sw[n] * f;
+    }
+    const double t = num * rcp_f64(W);
+    *e_in = -t;
+    *h = tau_entry(X, t + dt);
+    return t < lim;
 }
 
 // The same update from the padded layer buffer lay (row stride P = S + 1) of
@@ -1181,9 +1689,17 @@ __host__ __device__ __forceinline__ void layer_cell(const LayerPiece &L, const L
     const double inv_m = rcp_f64((double)m);
     const int r2 = mul24(m, m) + mul24(u, u) + mul24(v, v);
     const int pos = layer_slot(u, v, P);
-    layer_cell_core(L, X, m, u, v, layer_geo(m, inv_m, u), layer_geo(m, inv_m, v),
-                    sqrt_fast((double)r2) * inv_m, r2, cp, X.nHI[cp], lay[pos], lay[pos - P], lay[pos - 1],
-                    lay[pos - P - 1], out);
+    const double ads = sqrt_fast((double)r2) * (X.sa * inv_m);
+    const double h0 = lay[pos], h1 = lay[pos - P], h2 = lay[pos - 1], h3 = lay[pos - P - 1];
+    out.cp = cp;
+    out.r2 = r2;
+    out.owned = layer_owned(L, m, u, v);
+    out.dt = X.nHI[cp] * ads;
+    layer_cell_core(X, m, all_thick(h0, h1, h2, h3), layer_geo(m, inv_m, u), layer_geo(m, inv_m, v), ads, out.dt, h0,
+                    h1, h2, h3, 0.0, INFINITY, &out.e_in, &out.h);
+    out.Nin = entry_tau(out.e_in) * X.inv_s0;
+    out.dN = out.dt * X.inv_s0;
+    out.Nout = out.Nin + out.dN;
 }
 
 // Cell (i, j, k) of layer cell (m, u, v), in the standard layout.
@@ -1199,10 +1715,10 @@ __host__ __device__ __forceinline__ uint32_t layer_std_index(const LayerPiece &L
 }
 
 // The entry column of layer cell (u, v) of layer m recomputed from the
-// layer-buffer entries (layer_entry) of layer m - 1, kept as Hprev[u' * wvp +
+// layer-buffer entries (tau_entry) of layer m - 1, kept as Hprev[u' * wvp +
 // v'] (its rectangle), with what the adjoint needs: the geometric weights s,
 // the weight factors f, which neighbours are optically thick, W = sum s f
-// (as 1/W) and N_in = sum s g / W.  For m = 1 the entry column is the
+// (as 1/W) and t_in = sum s g / W.  For m = 1 the entry column is the
 // source's.
 // A chunk of 64 layer cells with at least this many cells with a rate has
 // their rate terms evaluated in the reverse pass itself (the lanes are mostly
@@ -1213,7 +1729,7 @@ constexpr int kDenseChunk = 32;
 struct LayerInterp {
     uint32_t cp;
     int r2;
-    double ds, Nin, iW;
+    double ds, tin, iW;   // tin: entry optical depth
     double sw[4], f[4];
     bool thick[4];
 };
@@ -1238,7 +1754,7 @@ __host__ __device__ __forceinline__ void layer_interp_core(const LayerX &X, int 
     I.sw[3] = gu.a * gv.a;
     I.iW = 1.0;
     if (m == 1) {
-        I.Nin = X.reading == 0 ? X.half_col * I.ds : X.half_col;
+        I.tin = X.reading == 0 ? X.half_tau * I.ds : X.half_tau;
 #pragma unroll
         for (int n = 0; n < 4; ++n) { I.f[n] = 0.0; I.thick[n] = false; }
         return;
@@ -1249,12 +1765,12 @@ __host__ __device__ __forceinline__ void layer_interp_core(const LayerX &X, int 
         const double h = I.sw[n] > 0.0 ? Hprev[(u - (n & 1)) * rp.wv + (v - (n >> 1))] : 0.0;
         I.thick[n] = h > 0.0;
         I.f[n] = I.thick[n] ? h : X.inv_tw;
-        const double g = I.thick[n] ? X.inv_s0 : -h * X.inv_tw;
+        const double g = I.thick[n] ? 1.0 : -h * X.inv_tw;
         num += I.sw[n] * g;
         W += I.sw[n] * I.f[n];
     }
     I.iW = rcp_f64(W);
-    I.Nin = num * I.iW;
+    I.tin = num * I.iW;
 }
 
 // The same with the cell's geometry computed in place (the reference form of
@@ -1300,9 +1816,8 @@ __host__ __device__ __forceinline__ void layer_rate_adjoint(const TabNode *T, co
                                                             double *gG)
 {
     // the same from the cell's interpolation I and n_HI, dt formed as the
-    // column sweep forms it: sigma0 (n_HI alpha ds)
-    layer_rate_adjoint_t(T, m64, tp, X.sigma0, coef, X.sigma0 * I.Nin, X.sigma0 * (nhi * X.alpha * I.ds),
-                         X.alpha * I.ds, I.r2, gbar, g_in, nbar_extra, gG);
+    // column sweep forms it: n_HI sigma0 alpha ds
+    layer_rate_adjoint_t(T, m64, tp, X.sigma0, coef, I.tin, nhi * X.sa * I.ds, X.alpha * I.ds, I.r2, gbar, g_in, nbar_extra, gG);
 }
 
 // The rate's coefficients of a cell with a rate for the adjoint, from its
@@ -1330,9 +1845,9 @@ __host__ __device__ __forceinline__ void layer_rate_coefs(const TabNode *T, cons
 // rate's entry-column term g_in.  Since N_out = N_in + dN, the exit-column
 // adjoint flows unchanged into N_in and dN, so the cell's dL/dn_HI is
 // Tin alpha ds here (the rate's remaining part comes from layer_rate_adjoint).
-// With N_in = sum s g / sum s f (f, g as in layer_entry),
-// dN_in/dM_n = s_n sigma0 N_in f_n^2 / W for a neighbour with
-// sigma0 M_n > tau_w (f_n = 1/(sigma0 M_n)) and s_n f_n / W for any other
+// With t_in = sum s g / sum s f (f, g as in tau_entry),
+// dN_in/dM_n = s_n t_in f_n^2 / W for a neighbour with
+// t_n > tau_w (f_n = 1/t_n) and s_n f_n / W for any other
 // (f_n constant), W = sum s f: the entries alone suffice.  Returns the
 // adjoints to push to the four neighbours of layer m - 1 (Mbar[n] for
 // neighbour (u - (n & 1), v - (n >> 1)); zero where the weight is zero; for
@@ -1357,7 +1872,7 @@ __host__ __device__ __forceinline__ void layer_cell_reverse(const LayerX &X, int
         out.nbar_src = Tin * (X.reading == 0 ? X.alpha * I.ds * 0.5 : X.alpha * 0.5);
         return;
     }
-    const double tk = Tin * I.iW, tt = tk * X.sigma0 * I.Nin;
+    const double tk = Tin * I.iW, tt = tk * I.tin;
 #pragma unroll
     for (int n = 0; n < 4; ++n) out.Mbar[n] = I.sw[n] * I.f[n] * (I.thick[n] ? tt * I.f[n] : tk);
 }
@@ -1381,6 +1896,26 @@ __host__ __device__ inline int build_rows(const Piece &pc, const Extent &ex, int
 }
 
 #if defined(__HIPCC__)
+// A part of the kernel's argument (its first, a struct; `offset` bytes in),
+// read from the argument segment here and now.  Like a polynomial's constants
+// (scalar_const), arguments that only the rate batch uses would otherwise
+// occupy scalar registers through the whole sweep.
+template <class T>
+__device__ __forceinline__ T reload_arg(size_t offset)
+{
+    typedef const __attribute__((address_space(4))) char *Segment;
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    Segment p = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    Words w = (Words)(p + offset);
+    struct Raw {
+        uint32_t v[sizeof(T) / 4];
+    } raw;
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) raw.v[i] = w[i];
+    return __builtin_bit_cast(T, raw);
+}
+
 constexpr int kRowsPerLane = 4;   // wave sweeps: rows per shell <= 64 * kRowsPerLane
 
 // Order LDS traffic of one wave: its own writes before its later reads.
@@ -1398,20 +1933,25 @@ __device__ __forceinline__ void wave_sync()
 // following chunks once theirs is used up.  Returns nitems when no chunk has
 // work left.
 //
-// Every lane takes part in each atomic (lane 0 adds 1, the others 0) and the
-// result is lane 0's, read into a scalar register.  There is no branch on the
-// lane index: with `if (lane == 0) fetch` followed by a broadcast, the compiler
-// may merge that branch with a lane-0 branch at the end of the previous item
-// and run lane 0 and lanes 1..63 around separate loops, so that the broadcast
-// runs without lane 0 and lanes 1..63 never see the end of the work.  The
-// scalar result also makes everything derived from the item wave-uniform.
+// Every lane takes part in each atomic: the counters count lanes, 64 to an
+// item, and the first lane's result over 64 is the item whichever order the
+// lanes' additions are made in.  There is no branch on the lane index: with
+// `if (lane == 0) fetch` followed by a broadcast, the compiler may merge that
+// branch with a lane-0 branch at the end of the previous item and run lane 0
+// and lanes 1..63 around separate loops, so that the broadcast runs without
+// lane 0 and lanes 1..63 never see the end of the work.  The addend is the
+// same in every lane, so the compiler makes it one addition of 64 (for an
+// addend that differs it first sums the lanes one by one, hundreds of
+// instructions).  The scalar result also makes everything derived from the
+// item wave-uniform.
 __device__ __forceinline__ int next_item(int *counters, int nitems, int home, int &chunk, int lane)
 {
+    (void)lane;
     for (;;) {
         const int lo = (int)((long)nitems * chunk / kXcds);
         const int hi = (int)((long)nitems * (chunk + 1) / kXcds);
-        const int got = atomicAdd(&counters[chunk * kCounterPad], lane == 0 ? 1 : 0);
-        const int k = __builtin_amdgcn_readfirstlane(got);
+        const unsigned long long got = atomicAdd((unsigned long long *)&counters[chunk * kCounterPad], 1ull);
+        const int k = uniform((int)(got >> 6));
         if (lo + k < hi) return lo + k;
         chunk = chunk + 1 == kXcds ? 0 : chunk + 1;
         if (chunk == home) return nitems;

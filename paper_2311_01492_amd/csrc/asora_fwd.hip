@@ -6,10 +6,13 @@
 // the rate of every owned cell added to an FP64 N^3 accumulator with one
 // hardware atomic per source-cell.  The persistent kernel pulls
 // (source, piece) items from a global counter, largest radius first.
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "asora_dev.h"
 #include "asora_internal.h"
+#include "asora_sweep.h"
 
 namespace asora {
 
@@ -44,14 +47,15 @@ struct FwdArgs {
     int lay_S;              // row stride of the per-wave layer buffer (layer pieces)
     char *keep;             // layer pieces: column records, per (source, pyramid); NULL = none
     size_t keep_piece_bytes;
-    long keep_cap;          // cells (and listed cells) per pyramid record
-    size_t keep_rk_off;     // offset of the rate coefficients in a kept record
-    const double *m64;      // FP64 node slopes of the table (rate coefficients of kept records)
+    long keep_cap;          // cells per pyramid record
+    int keep_Mcap;          // largest layer of the plan
+    const Node64 *n64;      // the table in FP64 (the rate of a forward that keeps records)
     int early_exit;         // layer pieces: stop after the first opaque layer
     const TabNode *tab_h;   // photo-heating table on the same node grid (read through the
                             // caches), or NULL: no heating
     double *hacc, *hacc_T;  // heating accumulators, in the layouts of gacc and gacc_T
     float dP0_h;            // dH/dtau at the first node (slope of the heating table's continuation)
+    LayerConst lc;
     int sq_n;               // layer pieces: entries of the work-group's LDS table of sqrt(r^2)
                             // (r^2 < sq_n); 0: roots computed per cell
 };
@@ -75,7 +79,7 @@ __device__ __forceinline__ void add_heating(const FwdArgs &A, double *hacc, uint
 }
 
 struct Lds {
-    TabNode *tab;
+    const TabNode *tab;   // read through the caches
     double *ring;      // [4][ring_cap]
     int *rowbase;      // [4][row_cap]: slot of (row, B) = rowbase[row] + B
     int *rowstart;     // [row_cap + 1] of the current shell
@@ -326,16 +330,10 @@ __device__ __forceinline__ void fwd_wave_body(const FwdArgs &A, char *smem)
     constexpr int npieces0 = TYPE == 0 ? 1 : (TYPE == 1 ? 8 : 24);
     if (A.plain_src < 0 && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
     (void)npieces0;
-    TabNode *T = (TabNode *)smem;
-    {
-        const int4 *s = (const int4 *)A.tab;
-        int4 *d = (int4 *)smem;
-        for (int k = threadIdx.x; k < A.tp.n; k += blockDim.x) d[k] = s[k];
-    }
-    __syncthreads();
+    const TabNode *T = A.tab;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int waves = blockDim.x >> 6;
-    char *region = smem + (size_t)A.tp.n * sizeof(TabNode) + (size_t)wave * A.region_bytes;
+    char *region = smem + (size_t)wave * A.region_bytes;
     double *ring = (double *)region;
     RateQueue Qa;
     Qa.ta = ring + 4 * (size_t)A.ring_cap;
@@ -379,263 +377,190 @@ __global__ __launch_bounds__(1024) void fwd_wave_heat(FwdArgs A)
 }
 
 // ---- layer pieces --------------------------------------------------------
-// One wave sweeps one pyramid layer by layer (see LayerPiece).  Layer m is
-// the rectangle of LayerRect, covered in chunks of 64 consecutive cells; the
-// previous layer lives in the wave's LDS buffer and is overwritten in place:
-// chunks go from the last to the first, and a cell reads only slots at or
-// before its own (u, v) in lexicographic order, so every slot a chunk reads
-// still holds layer m - 1 (the chunk's own writes follow its reads).  Rates go
-// through the same per-wave queue as the shell sweep.  With KEEP the sweep
-// also writes the pyramid's column record (the cells' layer-buffer entries and
-// the chunks' masks of cells with a rate) for a later adjoint.
-// The rate queue of the layer kernel: as RateQueue, with the squared distance
-// in 16 bits (a layer buffer that fits the LDS bounds the radius: R^2 stays
-// below 2^16, which the plan checks).  The in-cell optical depth is rounded to
-// FP32 as in RateQueue (a relative change of 6e-8 in one argument of the
-// rate), except with KEEP: the rate coefficients of kept records are FP64
-// derivatives that the adjoint combines with cancellation, so they are taken
-// at the same point as the adjoint's own.
+// One wave sweeps one pyramid layer by layer (sweep_layers).  Cells whose rate
+// is non-zero (owned, entry optical depth below the table end) go to the
+// wave's queue, and every full 64 queued rates are evaluated by all lanes
+// together.  With KEEP the sweep also writes the pyramid's column record (the
+// cells' layer-buffer entries and the chunks' masks of cells with a rate) for a
+// later adjoint.
+//
+// The queue, in LDS (byte offsets): per cell its entry optical depth as an
+// entry (entry_tau), the cell index, the in-cell optical depth and the squared
+// distance in 16 bits (a layer buffer that fits the LDS bounds the radius: R^2
+// stays below 2^16, which the plan checks).  The in-cell optical depth is
+// rounded to FP32 as in RateQueue (a relative change of 6e-8 in one argument of
+// the rate), except with KEEP, whose rate is evaluated in FP64.
 template <bool KEEP>
 struct LayerQueue {
     using dt_t = typename std::conditional<KEEP, double, float>::type;
-    double *ta;     // entry optical depth
-    dt_t *dt;       // in-cell optical depth
-    uint32_t *cp;   // cell index
-    uint16_t *r2;   // squared distance (cells)
+    static constexpr int kBytes = kQueue * (int)(sizeof(double) + sizeof(dt_t) + sizeof(uint32_t) + sizeof(uint16_t));
+    int e, dt, cp, r2;
+    __device__ __forceinline__ explicit LayerQueue(int base)
+        : e(base), dt(base + 8 * kQueue), cp(dt + (int)sizeof(dt_t) * kQueue), r2(cp + 4 * kQueue)
+    {
+    }
 };
 
-// One batch of queued cells: the rate added to Gamma.  Without KEEP the
-// rate comes from the FP32 divided difference; with KEEP from the FP64 one
-// that also gives the rate's coefficients for the adjoint (one evaluation
-// instead of two), which are stored in the record at the cells' places in
-// the order of evaluation (head + lane).
-template <bool KEEP, bool HEAT>
-__device__ __forceinline__ void layer_rate_batch(const FwdArgs &A, const TabNode *T, const LayerQueue<KEEP> &Qa,
-                                                 int head, int lane, double coef, double *acc,
-                                                 double *hacc, const LayerRecord &rec)
+// One batch of queued cells, from ring position head: the rate added to Gamma,
+// from the FP32 divided difference, with KEEP from the FP64 one.
+template <bool KEEP, bool HEAT, bool EXTRA>
+__device__ __forceinline__ void layer_rate_batch(const FwdArgs &A, const LayerQueue<KEEP> &Qa, int head, int lane,
+                                                 double coef, double *acc, double *hacc)
 {
     const int pos = (head + lane) & (kQueue - 1);
-    const double ta = Qa.ta[pos], dt = (double)Qa.dt[pos];
-    const int r2 = Qa.r2[pos];
+    const double ta = entry_tau(lds<double>(Qa.e + 8 * pos));
+    const double dt = (double)lds<typename LayerQueue<KEEP>::dt_t>(Qa.dt + (int)sizeof(typename LayerQueue<KEEP>::dt_t) * pos);
+    const uint32_t cp = lds<uint32_t>(Qa.cp + 4 * pos);
+    const int r2 = lds<uint16_t>(Qa.r2 + 2 * pos);
     if (!KEEP) {
-        const float nd = neg_divdiff(T, A.tp, ta, dt);
+        const float nd = EXTRA ? neg_divdiff(A.tab, A.tp, ta, dt) : neg_divdiff_fine(A.tab, A.tp, ta, dt);
         if (nd > 0.f) {
             const double G = coef * (double)(nd * rcp_approx((float)r2));
-            unsafeAtomicAdd(&acc[Qa.cp[pos]], G);
+            unsafeAtomicAdd(&acc[cp], G);
         }
     } else {
-        double c[3];
-        layer_rate_coefs(T, A.m64, A.tp, A.sigma0, ta, dt, r2, c);
-        const double G = coef * c[2];   // Gamma = coef (-D) / r2
-        if (G != 0.0) unsafeAtomicAdd(&acc[Qa.cp[pos]], G);
-        const long q = head + lane;
-        rec.rk[q] = c[0];
-        rec.rk[A.keep_cap + q] = c[1];
-        rec.rk[2 * A.keep_cap + q] = c[2];
+        const TabParams tp = reload_arg<TabParams>(offsetof(FwdArgs, tp));
+        const double G = coef * rcp_f64((double)r2) * neg_divdiff64<!EXTRA>(NodeArray{A.n64}, tp, ta, dt);
+        if (G > 0.0) unsafeAtomicAdd(&acc[cp], G);
     }
-    if (HEAT) add_heating(A, hacc, Qa.cp[pos], ta, dt, r2, coef);
+    if (HEAT) add_heating(A, hacc, cp, ta, dt, r2, coef);
 }
 
-template <bool KEEP, bool HEAT>
-__device__ void sweep_layer_piece(const FwdArgs &A, const TabNode *T, const double *sq, double *lay, Geo *geo,
-                                  uint32_t *iu, uint32_t *iv, const LayerQueue<KEEP> &Qa, int src, int p, int lane)
+// EXTRA: with the entry-column output, the early exit or a coarse table;
+// without, those are compiled out (fewer registers for the common sweep).
+template <bool KEEP, bool HEAT, bool EXTRA>
+__device__ __forceinline__ void sweep_layer_piece(const FwdArgs &A, const SweepLds &W, const LayerQueue<KEEP> &Qa,
+                                                  int src, int p, int lane)
 {
     const int N = A.N;
-    const int si = A.ijk[3 * src], sj = A.ijk[3 * src + 1], sk = A.ijk[3 * src + 2];
+    const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
     const float R = A.R ? A.R[src] : A.R_cap;
     if (!(R >= 0.f && R <= A.R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 ||
         sk >= N) {
         if (lane == 0) atomicOr(A.err, 1);
         return;
     }
-    const double Q = A.Q[src];
-    const int Rsq = (int)floor((double)R * (double)R);
+    const double Q = uniform(A.Q[src]);
+    const int Rsq = uniform((int)floor((double)R * (double)R));
     const LayerPiece L = make_layer_piece(p, si, sj, sk, N, A.ex);
     const uint32_t cs = ((uint32_t)si * (uint32_t)N + (uint32_t)sj) * (uint32_t)N + (uint32_t)sk;
-    const double n_s = A.nHI[cs];
+    const double n_s = uniform(A.nHI[cs]);
     LayerX X;
     X.N = N;
     X.reading = A.reading;
     X.tau_w = A.tau_w;
     X.sigma0 = A.sigma0;
     X.alpha = A.alpha;
-    X.half_col = n_s * A.alpha * 0.5;
+    layer_x_source(X, A.lc, n_s);
     X.nHI = L.transposed ? A.nHI_T : A.nHI;
-    layer_x_weights(X);
     double *acc = L.transposed ? A.gacc_T : A.gacc;
     double *hacc = HEAT ? (L.transposed ? A.hacc_T : A.hacc) : nullptr;
-    const double coef = Q * A.coef_unit;
-    const int S = A.lay_S;
+    const double coef = uniform(Q * A.coef_unit);
     LayerRecord rec;
     if (KEEP)
-        rec = layer_record_at(A.keep + ((size_t)src * 24 + p) * A.keep_piece_bytes, A.keep_cap,
-                              A.keep_rk_off);
+        rec = layer_record_at(A.keep + ((size_t)src * 24 + p) * A.keep_piece_bytes, A.keep_cap, 0);
 
     if (p == 3 * 0 + 2 && lane == 0) {   // the source cell, once per source
-        const double G = source_cell_rate(T, A.tp, A.sigma0, A.alpha, Q, n_s);
+        const double G = source_cell_rate<!EXTRA>(A.tab, A.tp, A.sigma0, A.alpha, Q, n_s);
         if (G != 0.0) unsafeAtomicAdd(&A.gacc[cs], G);
-        if (A.coldens) A.coldens[cs] = 0.0;
+        if (EXTRA && A.coldens) A.coldens[cs] = 0.0;
         if (HEAT) {
-            const double H = source_cell_rate(A.tab_h, heat_params(A), A.sigma0, A.alpha, Q, n_s);
+            const double H = source_cell_rate<!EXTRA>(A.tab_h, heat_params(A), A.sigma0, A.alpha, Q, n_s);
             if (H != 0.0) unsafeAtomicAdd(&A.hacc[cs], H);
         }
     }
-    const int Mx = min(isqrt_floor(Rsq), L.ext_d);
-    const int P = S + 1;   // row stride of the padded layer buffer
-    for (int k = lane; k < P * P; k += 64) lay[k] = 0.0;   // finite everywhere it is read
-    for (int k = lane; k < S; k += 64) {                   // the pyramid's index terms
-        iu[k] = layer_idx_u(L, N, k);
-        iv[k] = layer_idx_v(L, N, k);
-    }
-    wave_sync();
-    int head = 0, tail = 0;
-    long off = 0;     // first cell of layer m in the record
-    long choff = 0;   // first chunk of layer m in the record
-    const double opaque = layer_opaque(A.tp.tau_hi);
+    const int Mx = min(uniform(isqrt_floor(Rsq)), L.ext_d);
     // the last layer swept, recorded and visited by the adjoint: every layer,
     // unless the early exit stops the pyramid at its first opaque layer
     int m_last = Mx;
-    const bool watch = A.early_exit;
-    for (int m = 1; m <= Mx; ++m) {
-        const LayerRect r = layer_rect(L.ext_u, L.ext_v, Rsq, m);
-        const double inv_m = rcp_f64((double)m);
-        const int nch = (r.total + 63) / 64;
-        // the bilinear factors of this layer's offsets (the previous layer's
-        // readers are done: every chunk ends with a wave barrier)
-        for (int k = lane; k < S; k += 64) geo[k] = layer_geo(m, inv_m, k);
+    if (Mx >= 1) {
+        for (int k = lane; k < W.S; k += 64) {   // the pyramid's index terms
+            lds<uint32_t>(W.geo + (int)sizeof(GeoRow) * k + (int)offsetof(GeoRow, iu)) = layer_idx_u(L, N, k);
+            lds<uint32_t>(W.geo + (int)sizeof(GeoRow) * k + (int)offsetof(GeoRow, iv)) = layer_idx_v(L, N, k);
+        }
         wave_sync();
-        RectWalk w;
-        w.init(r, (nch - 1) * 64 + lane);
-        bool opq = true;   // every cell of layer m so far leaves opaque
-        const int m2 = mul24(m, m);
-        const uint32_t idx_d = layer_idx_d(L, N, m);
-        for (int c = nch - 1; c >= 0; --c, w.down()) {
-            const int g = c * 64 + lane;
-            const int u = w.u, v = w.v;
-            const int uv2 = mul24(u, u) + mul24(v, v);
-            const bool act = g < r.total && uv2 <= r.rem;
-            const int pos = layer_slot(u, v, P);
-            LayerCell lc;
-            lc.Nin = 0.0;
-            lc.owned = false;
-            if (act) {
-                const uint32_t cp = idx_d + iu[u] + iv[v];
-                const int r2 = m2 + uv2;   // <= Rsq < sq_n when the table is there
-                const double rt = A.sq_n ? sq[r2] : sqrt_fast((double)r2);
-                layer_cell_core(L, X, m, u, v, geo[u], geo[v], rt * inv_m, r2, cp, X.nHI[cp], lay[pos],
-                                lay[pos - P], lay[pos - 1], lay[pos - P - 1], lc);
-            }
-            wave_sync();   // every read of layer m - 1 before the writes below
-            bool want = false;
-            if (act) {
-                lay[pos] = lc.h;
-                if (KEEP) rec.h[off + g] = lc.h;
-                if (lc.owned) {
-                    if (A.coldens) A.coldens[layer_std_index(L, N, m, u, v)] = lc.Nin;
-                    want = A.sigma0 * lc.Nin < A.tp.tau_hi;
+        // the rate queue: `pend` cells from ring position `head`
+        int head = 0, pend = 0;
+        long off = 0, choff = 0;   // first cell and chunk of layer m in the record
+        bool opq = true;           // every cell of layer m so far leaves opaque
+        sweep_layers(
+            L, X, W, Rsq, Mx, m_last, A.tp.tau_hi, A.lc.inv_hi, lane,
+            [&](const SweepChunk &k) {
+                const bool owned = k.in & layer_owned(L, k.m, k.u, k.v);
+                const bool want = owned & k.below;
+                if (KEEP && k.in) rec.h[off + k.c * 64 + lane] = k.h;
+                if (EXTRA && A.coldens && owned)
+                    A.coldens[layer_std_index(L, N, k.m, k.u, k.v)] = entry_tau(k.e_in) * X.inv_s0;
+                const uint64_t mask = ballot(want);
+                if (KEEP && lane == 0) rec.lit[choff + k.c] = mask;
+                if (EXTRA && A.early_exit)
+                    opq = opq && ballot(k.in && entry_below(k.h, A.lc.opaque, A.lc.inv_opq)) == 0;
+                if (want) {
+                    const int q = (head + pend + rank_in(mask)) & (kQueue - 1);
+                    lds<double>(Qa.e + 8 * q) = k.e_in;
+                    lds<typename LayerQueue<KEEP>::dt_t>(Qa.dt + (int)sizeof(typename LayerQueue<KEEP>::dt_t) * q) =
+                        (typename LayerQueue<KEEP>::dt_t)k.dt;
+                    lds<uint32_t>(Qa.cp + 4 * q) = k.cell;
+                    lds<uint16_t>(Qa.r2 + 2 * q) = (uint16_t)k.r2;
                 }
-            }
-            const uint64_t mask = __ballot(want);
-            if (KEEP && lane == 0) rec.lit[choff + c] = mask;
-            if (watch) opq = opq && __ballot(act && !(A.sigma0 * lc.Nout >= opaque)) == 0;
-            if (want) {
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                const int qpos = (tail + rank) & (kQueue - 1);
-                Qa.ta[qpos] = A.sigma0 * lc.Nin;
-                Qa.dt[qpos] = (typename LayerQueue<KEEP>::dt_t)(A.sigma0 * lc.dN);
-                Qa.cp[qpos] = lc.cp;
-                Qa.r2[qpos] = (uint16_t)lc.r2;
-            }
-            tail += __popcll(mask);
-            if (tail - head >= 64) {
-                wave_sync();
-                layer_rate_batch<KEEP, HEAT>(A, T, Qa, head, lane, coef, acc, hacc, rec);
-                head += 64;
-            }
-            wave_sync();
-        }
-        off += r.total;
-        choff += nch;
-        if (watch && opq) {
-            m_last = m;
-            break;   // every later cell has a zero rate
-        }
-    }
-    if (tail > head) {
+                pend += __popcll(mask);
+                if (pend >= 64) {
+                    wave_sync();
+                    layer_rate_batch<KEEP, HEAT, EXTRA>(A, Qa, head, lane, coef, acc, hacc);
+                    head = (head + 64) & (kQueue - 1);
+                    pend -= 64;
+                }
+            },
+            [&](int m, int total) {
+                off += total;
+                choff += (total + 63) / 64;
+                if (EXTRA && A.early_exit && opq) m_last = m;   // every later cell has a zero rate
+                opq = true;
+            });
         wave_sync();
-        if (lane < tail - head) layer_rate_batch<KEEP, HEAT>(A, T, Qa, head, lane, coef, acc, hacc, rec);
+        if (lane < pend) layer_rate_batch<KEEP, HEAT, EXTRA>(A, Qa, head, lane, coef, acc, hacc);
         wave_sync();
     }
-    if (KEEP && lane == 0) {
-        ((uint64_t *)rec.rk)[3 * A.keep_cap] = (uint64_t)tail;   // cells with a rate
-        ((uint64_t *)rec.rk)[3 * A.keep_cap + 1] = (uint64_t)m_last;
-    }
+    if (KEEP && lane == 0) rec.lit[A.keep_cap / 64 + A.keep_Mcap] = (uint64_t)m_last;
 }
 
-// TLDS: the table is copied to LDS once per work-group; otherwise the rate
-// batches read it through the caches, which leaves the LDS to more waves.
-// The work-group also holds the table of square roots when the launch gives
+// The work-group shares only the table of square roots, when the launch gives
 // one (sq_n > 0: the plan adds it only where it costs no wave); every wave
-// its own region (rate queue, layer buffer, per-layer and per-pyramid tables).
-template <bool KEEP, bool TLDS, bool HEAT>
-__device__ __forceinline__ void fwd_layer_body(const FwdArgs &A, char *smem)
+// has its own region (rate queue, layer buffer, table of factors).  The rate
+// tables are read through the caches: 32-byte nodes in LDS would take the room
+// of three to six waves.
+// KEEP: writes the column records; HEAT: adds the photo-heating of every cell
+// to hacc / hacc_T.
+template <bool KEEP, bool HEAT, bool EXTRA>
+__global__ __launch_bounds__(1024) void fwd_layer(FwdArgs A)
 {
     constexpr int TYPE = 3, npieces = 24;
     if (A.plain_src < 0 && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
-    const TabNode *T = TLDS ? (const TabNode *)smem : A.tab;
-    if (TLDS) {
-        const int4 *s = (const int4 *)A.tab;
-        int4 *d = (int4 *)smem;
-        for (int k = threadIdx.x; k < A.tp.n; k += blockDim.x) d[k] = s[k];
-    }
-    char *wg = smem + (TLDS ? (size_t)A.tp.n * sizeof(TabNode) : 0);
-    double *sq = (double *)wg;
-    for (int k = threadIdx.x; k < A.sq_n; k += blockDim.x) sq[k] = sqrt((double)k);
+    for (int k = threadIdx.x; k < A.sq_n; k += blockDim.x) lds<double>(8 * k) = sqrt((double)k);
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int waves = blockDim.x >> 6;
-    char *region = wg + (A.sq_n ? layer_sqrt_bytes(A.sq_n - 1) : 0) + (size_t)wave * A.region_bytes;
-    LayerQueue<KEEP> Qa;
-    Qa.ta = (double *)region;
-    Qa.dt = (typename LayerQueue<KEEP>::dt_t *)(Qa.ta + kQueue);
-    Qa.cp = (uint32_t *)(Qa.dt + kQueue);
-    Qa.r2 = (uint16_t *)(Qa.cp + kQueue);
-    double *lay = (double *)(Qa.r2 + kQueue);   // kQueue is a multiple of 4: aligned
-    Geo *geo = (Geo *)(lay + (size_t)(A.lay_S + 1) * (A.lay_S + 1));
-    uint32_t *iu = (uint32_t *)(geo + A.lay_S);
-    uint32_t *iv = iu + A.lay_S;
-    if (A.plain_src >= 0) {
-        const int item = blockIdx.x * waves + wave;
-        if (item < npieces) sweep_layer_piece<KEEP, HEAT>(A, T, sq, lay, geo, iu, iv, Qa, A.plain_src, item, lane);
-        return;
-    }
-    const int base = A.seg[TYPE];
-    const int nitems = (A.seg[TYPE + 1] - base) * npieces;
+    const int region = (A.sq_n ? (int)layer_sqrt_bytes(A.sq_n - 1) : 0) + wave * A.region_bytes;
+    const LayerQueue<KEEP> Qa(region);
+    SweepLds W;
+    W.S = A.lay_S;
+    W.sq = 0;
+    W.sq_n = A.sq_n;
+    W.lay = region + LayerQueue<KEEP>::kBytes;
+    W.geo = W.lay + 8 * (W.S + 1) * (W.S + 1);
+    // persistent: items from the counters; plain: wave w's item is pyramid w
+    const bool plain = A.plain_src >= 0;
+    const int base = plain ? 0 : A.seg[TYPE];
+    const int nitems = plain ? npieces : (A.seg[TYPE + 1] - base) * npieces;
     const int home = (int)(blockIdx.x % kXcds);
     int chunk = home;
     for (;;) {
-        const int item = next_item(A.counter, nitems, home, chunk, lane);
+        const int item = plain ? (int)blockIdx.x * waves + wave : next_item(A.counter, nitems, home, chunk, lane);
         if (item >= nitems) break;
-        const int src = A.order[base + item / npieces];
-        sweep_layer_piece<KEEP, HEAT>(A, T, sq, lay, geo, iu, iv, Qa, src, item % npieces, lane);
+        const int src = plain ? A.plain_src : uniform(A.order[base + item / npieces]);
+        sweep_layer_piece<KEEP, HEAT, EXTRA>(A, W, Qa, src, item % npieces, lane);
+        if (plain) break;
     }
-}
-
-template <bool KEEP, bool TLDS>
-__global__ __launch_bounds__(1024) void fwd_layer(FwdArgs A)
-{
-    extern __shared__ __align__(16) char smem[];
-    fwd_layer_body<KEEP, TLDS, false>(A, smem);
-}
-
-// The same sweep, adding the photo-heating of every cell to hacc / hacc_T
-// (both tables through the caches).
-template <bool KEEP>
-__global__ __launch_bounds__(1024) void fwd_layer_heat(FwdArgs A)
-{
-    extern __shared__ __align__(16) char smem[];
-    fwd_layer_body<KEEP, false, true>(A, smem);
 }
 
 // Per-wave LDS of the layer kernel: the rate queue (its in-cell optical depths
@@ -643,18 +568,24 @@ __global__ __launch_bounds__(1024) void fwd_layer_heat(FwdArgs A)
 // table of bilinear factors and the pyramid's index terms along u and v.
 size_t layer_region_bytes(int S, bool keep)
 {
-    const size_t dt = keep ? sizeof(double) : sizeof(float);
-    const size_t b = (size_t)kQueue * (sizeof(double) + dt + sizeof(uint32_t) + sizeof(uint16_t)) +
-                     (size_t)(S + 1) * (S + 1) * sizeof(double) + (size_t)S * sizeof(Geo) +
-                     2 * (size_t)S * sizeof(uint32_t);
+    const size_t b = (size_t)(keep ? LayerQueue<true>::kBytes : LayerQueue<false>::kBytes) +
+                     (size_t)(S + 1) * (S + 1) * sizeof(double) + (size_t)S * sizeof(GeoRow);
     return (b + 15) & ~(size_t)15;
 }
 
-hipError_t layer_occupancy(bool keep, bool tab_lds, int waves, size_t lds, int *blocks_per_cu)
+static const void *layer_fn(bool keep, bool heat, bool extra)
 {
-    const void *f = keep ? (tab_lds ? (const void *)fwd_layer<true, true> : (const void *)fwd_layer<true, false>)
-                         : (tab_lds ? (const void *)fwd_layer<false, true> : (const void *)fwd_layer<false, false>);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, waves * 64, lds);
+    static const void *const f[8] = {
+        (const void *)fwd_layer<false, false, false>, (const void *)fwd_layer<false, false, true>,
+        (const void *)fwd_layer<false, true, false>,  (const void *)fwd_layer<false, true, true>,
+        (const void *)fwd_layer<true, false, false>,  (const void *)fwd_layer<true, false, true>,
+        (const void *)fwd_layer<true, true, false>,   (const void *)fwd_layer<true, true, true>};
+    return f[(keep ? 4 : 0) + (heat ? 2 : 0) + (extra ? 1 : 0)];
+}
+
+hipError_t layer_occupancy(bool keep, int waves, size_t lds, int *blocks_per_cu)
+{
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, layer_fn(keep, false, false), waves * 64, lds);
 }
 
 hipError_t launch_fwd_layer(hipStream_t st, const FwdLaunch &F, int S, int waves, int grid,
@@ -667,17 +598,12 @@ hipError_t launch_fwd_layer(hipStream_t st, const FwdLaunch &F, int S, int waves
     const int Rsq = (int)floor((double)F.R_cap * (double)F.R_cap);
     const size_t sqb = F.sq_table ? layer_sqrt_bytes(Rsq) : 0;
     A.sq_n = sqb ? Rsq + 1 : 0;
-    const bool tab_lds = F.tab_lds && !F.hacc;   // the heating sweep reads both tables through the caches
-    const size_t lds = (tab_lds ? (size_t)F.tp.n * sizeof(TabNode) : 0) + sqb + (size_t)waves * A.region_bytes;
+    const size_t lds = sqb + (size_t)waves * A.region_bytes;
     if (plain_src >= 0) grid = (24 + waves - 1) / waves;
-    const dim3 g(grid), b(64 * waves);
-    if (F.hacc && A.keep) hipLaunchKernelGGL((fwd_layer_heat<true>), g, b, lds, st, A);
-    else if (F.hacc) hipLaunchKernelGGL((fwd_layer_heat<false>), g, b, lds, st, A);
-    else if (A.keep && F.tab_lds) hipLaunchKernelGGL((fwd_layer<true, true>), g, b, lds, st, A);
-    else if (A.keep) hipLaunchKernelGGL((fwd_layer<true, false>), g, b, lds, st, A);
-    else if (F.tab_lds) hipLaunchKernelGGL((fwd_layer<false, true>), g, b, lds, st, A);
-    else hipLaunchKernelGGL((fwd_layer<false, false>), g, b, lds, st, A);
-    return hipGetLastError();
+    const bool extra = F.coldens || F.early_exit || !F.tp.fine || (A.keep && !F.tp.tame);
+    void *args[] = {&A};
+    return hipLaunchKernel(layer_fn(A.keep != nullptr, F.hacc != nullptr, extra), dim3(grid), dim3(64 * waves), args,
+                           lds, st);
 }
 
 size_t wave_region_bytes(int ring_cap, int row_cap)
@@ -699,7 +625,7 @@ hipError_t launch_fwd_wave(hipStream_t st, const FwdLaunch &F, int waves, int gr
     FwdArgs A = make_args(F);
     A.plain_src = plain_src;
     A.region_bytes = (int)wave_region_bytes(F.ring_cap, F.row_cap);
-    const size_t lds = (size_t)F.tp.n * sizeof(TabNode) + (size_t)waves * A.region_bytes;
+    const size_t lds = (size_t)waves * A.region_bytes;
     if (plain_src >= 0) grid = (pieces_of_type(F.type) + waves - 1) / waves;
     if (F.hacc) {
         switch (F.type) {
@@ -720,18 +646,11 @@ hipError_t launch_fwd_wave(hipStream_t st, const FwdLaunch &F, int waves, int gr
 __device__ Lds carve_lds(char *smem, const FwdArgs &A)
 {
     Lds L;
-    L.tab = (TabNode *)smem;
-    L.ring = (double *)(smem + (size_t)A.tp.n * sizeof(TabNode));
+    L.tab = A.tab;
+    L.ring = (double *)smem;
     L.rowbase = (int *)(L.ring + 4 * (size_t)A.ring_cap);
     L.rowstart = L.rowbase + 4 * A.row_cap;
     return L;
-}
-
-__device__ void load_table(const FwdArgs &A, TabNode *dst)
-{
-    const int4 *s = (const int4 *)A.tab;
-    int4 *d = (int4 *)dst;
-    for (int k = threadIdx.x; k < A.tp.n; k += kWG) d[k] = s[k];
 }
 
 __global__ __launch_bounds__(kWG) void fwd_persistent(FwdArgs A)
@@ -739,7 +658,6 @@ __global__ __launch_bounds__(kWG) void fwd_persistent(FwdArgs A)
     extern __shared__ __align__(16) char smem[];
     __shared__ int sh_item, sh_total;
     const Lds L = carve_lds(smem, A);
-    load_table(A, L.tab);
     const int base = A.seg[A.type];
     const long nitems = (long)(A.seg[A.type + 1] - base) * A.n_pieces;
     __syncthreads();
@@ -760,7 +678,6 @@ __global__ __launch_bounds__(kWG) void fwd_plain(FwdArgs A)
     extern __shared__ __align__(16) char smem[];
     __shared__ int sh_total;
     const Lds L = carve_lds(smem, A);
-    load_table(A, L.tab);
     __syncthreads();
     sweep_piece(A, L, A.plain_src, blockIdx.x, &sh_total);
 }
@@ -1004,8 +921,8 @@ static FwdArgs make_args(const FwdLaunch &F)
     A.keep = F.keep;
     A.keep_piece_bytes = F.keep_piece_bytes;
     A.keep_cap = F.keep_cap;
-    A.keep_rk_off = F.keep_rk_off;
-    A.m64 = F.m64;
+    A.keep_Mcap = F.keep_Mcap;
+    A.n64 = F.n64;
     A.early_exit = F.early_exit ? 1 : 0;
     A.tab_h = F.tab_h;
     A.hacc = F.hacc;
@@ -1026,13 +943,14 @@ static FwdArgs make_args(const FwdLaunch &F)
     A.plain_src = -1;
     A.region_bytes = 0;
     A.coef_unit = F.sigma0 / (4.0 * M_PI * F.alpha * F.alpha);
+    A.lc = make_layer_const(F.sigma0, F.alpha, F.tau_w, F.tp.tau_hi);
     A.sq_n = 0;
     return A;
 }
 
-size_t fwd_lds_bytes(int n_tab, int ring_cap, int row_cap)
+size_t fwd_lds_bytes(int ring_cap, int row_cap)
 {
-    return (size_t)n_tab * sizeof(TabNode) + 4 * (size_t)ring_cap * sizeof(double) +
+    return 4 * (size_t)ring_cap * sizeof(double) +
            (4 * (size_t)row_cap + row_cap + 1) * sizeof(int);
 }
 
@@ -1048,15 +966,11 @@ hipError_t fwd_configure(size_t max_lds)
     (void)hipFuncSetAttribute((const void *)fwd_wave<0>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave<1>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave<2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    (void)hipFuncSetAttribute((const void *)fwd_layer<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    (void)hipFuncSetAttribute((const void *)fwd_layer<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    (void)hipFuncSetAttribute((const void *)fwd_layer<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    (void)hipFuncSetAttribute((const void *)fwd_layer<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<0>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<1>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    (void)hipFuncSetAttribute((const void *)fwd_layer_heat<false>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    (void)hipFuncSetAttribute((const void *)fwd_layer_heat<true>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    for (int f = 0; f < 8; ++f)
+        (void)hipFuncSetAttribute(layer_fn(f & 4, f & 2, f & 1), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipGetLastError();
     return hipSuccess;
 }
@@ -1070,7 +984,7 @@ hipError_t fwd_occupancy(size_t lds, int *blocks_per_cu)
 hipError_t launch_fwd_persistent(hipStream_t st, const FwdLaunch &F, int grid)
 {
     const FwdArgs A = make_args(F);
-    const size_t lds = fwd_lds_bytes(F.tp.n, F.ring_cap, F.row_cap);
+    const size_t lds = fwd_lds_bytes(F.ring_cap, F.row_cap);
     hipLaunchKernelGGL(fwd_persistent, dim3(grid), dim3(kWG), lds, st, A);
     return hipGetLastError();
 }
@@ -1079,7 +993,7 @@ hipError_t launch_fwd_plain(hipStream_t st, const FwdLaunch &F, int src)
 {
     FwdArgs A = make_args(F);
     A.plain_src = src;
-    const size_t lds = fwd_lds_bytes(F.tp.n, F.ring_cap, F.row_cap);
+    const size_t lds = fwd_lds_bytes(F.ring_cap, F.row_cap);
     hipLaunchKernelGGL(fwd_plain, dim3(A.n_pieces), dim3(kWG), lds, st, A);
     return hipGetLastError();
 }

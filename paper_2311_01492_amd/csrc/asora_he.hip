@@ -45,6 +45,7 @@ struct HeArgs {
     int plain_src;
     int lay_S;
     int region_bytes;
+    LayerConst lc;
     int sq_n;
     double coef_unit;   // 1 / (4 pi alpha^2)
 };
@@ -55,7 +56,7 @@ struct HeArgs {
 // the queue, and so the LDS per wave, small.
 constexpr int kHeQueue = 128;
 struct HeQueue {
-    double *NinH, *NinHe;
+    double *e, *NinHe;   // entry HI optical depth (as a layer-buffer entry), entry HeI column
     uint32_t *cp;
     uint32_t *mr;
 };
@@ -64,9 +65,9 @@ struct HeQueue {
 // shared between the species by their cross-sections.  nH, nHe: the fields
 // in the piece's layout.
 __device__ __forceinline__ void he_rate(const HeArgs &A, const HeQueue &Qa, int pos, double coef, const double *sq,
-                                        const double *nH, const double *nHe, double *gH, double *gHe)
+                                        const double *nH, const double *nHe, double inv_s0, double *gH, double *gHe)
 {
-    const double NH = Qa.NinH[pos], NHe = Qa.NinHe[pos];
+    const double NH = entry_tau(Qa.e[pos]) * inv_s0, NHe = Qa.NinHe[pos];
     const uint32_t cp = Qa.cp[pos], mr = Qa.mr[pos];
     const int r2 = (int)(mr & 0xffffu), m = (int)(mr >> 16);
     const double ds = (A.sq_n ? sq[r2] : sqrt_fast((double)r2)) * rcp_f64((double)m);
@@ -120,14 +121,13 @@ __device__ void sweep_layer_piece_he(const HeArgs &A, const double *sq, double *
     X.tau_w = A.tau_w;
     X.sigma0 = A.sigma0;
     X.alpha = A.alpha;
-    X.half_col = A.nHI[cs] * A.alpha * 0.5;
+    layer_x_source(X, A.lc, uniform(A.nHI[cs]));
     X.nHI = L.transposed ? A.nHI_T : A.nHI;
-    layer_x_weights(X);
     const double half_he = A.nHeI[cs] * A.alpha * 0.5;
     const double *nHe = L.transposed ? A.nHeI_T : A.nHeI;
     double *gH = L.transposed ? A.gH_T : A.gH;
     double *gHe = L.transposed ? A.gHe_T : A.gHe;
-    const double coef = Q * A.coef_unit;
+    const double coef = uniform(Q * A.coef_unit);
     const int S = A.lay_S;
     if (p == 3 * 0 + 2 && lane == 0) he_source_cell(A, cs, Q);   // once per source
     const int Mx = min(isqrt_floor(Rsq), L.ext_d);
@@ -158,16 +158,17 @@ __device__ void sweep_layer_piece_he(const HeArgs &A, const double *sq, double *
             const int uv2 = mul24(u, u) + mul24(v, v);
             const bool act = g < r.total && uv2 <= r.rem;
             const int pos = layer_slot(u, v, P);
-            LayerCell lc;
-            lc.owned = false;
-            double NinHe = 0.0, dNHe = 0.0;
+            double h[4] = {0.0, 0.0, 0.0, 0.0}, e_in = 0.0, hout = 0.0, NinHe = 0.0, dNHe = 0.0;
+            uint32_t cp = 0;
+            const int r2 = m2 + uv2;
+            if (act) h[0] = lay[pos], h[1] = lay[pos - P], h[2] = lay[pos - 1], h[3] = lay[pos - P - 1];
+            const bool thick = __ballot(!all_thick(h[0], h[1], h[2], h[3])) == 0;
             if (act) {
-                const uint32_t cp = idx_d + iu[u] + iv[v];
-                const int r2 = m2 + uv2;
+                cp = idx_d + iu[u] + iv[v];
                 const double ds = (A.sq_n ? sq[r2] : sqrt_fast((double)r2)) * inv_m;
-                const double h[4] = {lay[pos], lay[pos - P], lay[pos - 1], lay[pos - P - 1]};
-                layer_cell_core(L, X, m, u, v, geo[u], geo[v], ds, r2, cp, X.nHI[cp], h[0], h[1], h[2], h[3],
-                                lc);
+                const double ads = X.sa * ds;
+                layer_cell_core(X, m, thick, geo[u], geo[v], ads, X.nHI[cp] * ads, h[0], h[1], h[2], h[3], 0.0,
+                                INFINITY, &e_in, &hout);
                 // the helium column with the same weights: N_He = sum s f M_He / sum s f
                 if (m == 1) {
                     NinHe = X.reading == 0 ? half_he * ds : half_he;
@@ -189,26 +190,28 @@ __device__ void sweep_layer_piece_he(const HeArgs &A, const double *sq, double *
             wave_sync();   // every read of layer m - 1 before the writes below
             bool want = false;
             if (act) {
-                lay[pos] = lc.h;
+                lay[pos] = hout;
                 layHe[pos] = NinHe + dNHe;
-                if (lc.owned)
+                if (layer_owned(L, m, u, v)) {
+                    const double Nin = entry_tau(e_in) * X.inv_s0;
                     for (int b = 0; b < A.nb; ++b)
-                        want = want || A.sH[b] * lc.Nin + A.sHe[b] * NinHe < A.tp[b].tau_hi;
+                        want = want || A.sH[b] * Nin + A.sHe[b] * NinHe < A.tp[b].tau_hi;
+                }
             }
             const uint64_t mask = __ballot(want);
             if (want) {
                 const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
                 const int q = (tail + rank) & (kHeQueue - 1);
-                Qa.NinH[q] = lc.Nin;
+                Qa.e[q] = e_in;
                 Qa.NinHe[q] = NinHe;
-                Qa.cp[q] = lc.cp;
-                Qa.mr[q] = ((uint32_t)m << 16) | (uint32_t)lc.r2;
+                Qa.cp[q] = cp;
+                Qa.mr[q] = ((uint32_t)m << 16) | (uint32_t)r2;
             }
             tail += __popcll(mask);
             if (tail - head >= 64) {
                 wave_sync();
-                he_rate(A, Qa, (head + lane) & (kHeQueue - 1), coef, sq, X.nHI, nHe, gH, gHe);
+                he_rate(A, Qa, (head + lane) & (kHeQueue - 1), coef, sq, X.nHI, nHe, X.inv_s0, gH, gHe);
                 head += 64;
             }
             wave_sync();
@@ -216,7 +219,7 @@ __device__ void sweep_layer_piece_he(const HeArgs &A, const double *sq, double *
     }
     if (tail > head) {
         wave_sync();
-        if (lane < tail - head) he_rate(A, Qa, (head + lane) & (kHeQueue - 1), coef, sq, X.nHI, nHe, gH, gHe);
+        if (lane < tail - head) he_rate(A, Qa, (head + lane) & (kHeQueue - 1), coef, sq, X.nHI, nHe, X.inv_s0, gH, gHe);
         wave_sync();
     }
 }
@@ -233,8 +236,8 @@ __global__ __launch_bounds__(1024) void fwd_layer_he(HeArgs A)
     const int waves = blockDim.x >> 6;
     char *region = smem + (A.sq_n ? layer_sqrt_bytes(A.sq_n - 1) : 0) + (size_t)wave * A.region_bytes;
     HeQueue Qa;
-    Qa.NinH = (double *)region;
-    Qa.NinHe = Qa.NinH + kHeQueue;
+    Qa.e = (double *)region;
+    Qa.NinHe = Qa.e + kHeQueue;
     Qa.cp = (uint32_t *)(Qa.NinHe + kHeQueue);
     Qa.mr = Qa.cp + kHeQueue;
     const size_t PP = (size_t)(A.lay_S + 1) * (A.lay_S + 1);
@@ -315,6 +318,7 @@ hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int wav
     A.counter = H.ctl + kCtlCounter + kXcds * kCounterPad * 3;
     A.err = H.err;
     A.plain_src = plain_src;
+    A.lc = make_layer_const(H.sigma0, H.alpha, H.tau_w, 1.0);   // (every band has its own tau_hi)
     A.lay_S = S;
     A.region_bytes = (int)he_region_bytes(S);
     const int Rsq = (int)floor((double)H.R_cap * (double)H.R_cap);

@@ -42,10 +42,9 @@ struct FwdLaunch {
     char *keep;             // layer pieces: column records per (source, pyramid), or NULL
     size_t keep_piece_bytes;
     long keep_cap;
-    size_t keep_rk_off;     // offset of the rate coefficients in a kept record
-    const double *m64;      // FP64 node slopes of the table
+    int keep_Mcap;          // largest layer of the plan
+    const Node64 *n64;      // the table in FP64
     bool early_exit;        // layer pieces: stop after the first opaque layer
-    int tab_lds;            // layer pieces: table in LDS (1) or read through the caches (0)
     bool sq_table;          // layer pieces: the work-group's LDS table of sqrt(r^2) (else per cell)
     const TabNode *tab_h;   // photo-heating table (same node grid), or NULL: no heating
     double *hacc, *hacc_T;  // heating accumulators (layouts of gacc, gacc_T)
@@ -63,7 +62,7 @@ hipError_t launch_transpose_finalize(hipStream_t st, const double *gacc, const d
                                      float *gamma, int N, int accumulate);
 hipError_t launch_zero(hipStream_t st, double *p, long n, int n_cu);
 size_t layer_region_bytes(int S, bool keep);
-hipError_t layer_occupancy(bool keep, bool tab_lds, int waves, size_t lds, int *blocks_per_cu);
+hipError_t layer_occupancy(bool keep, int waves, size_t lds, int *blocks_per_cu);
 
 // hydrogen chemistry step (asora_chem.hip)
 struct ChemLaunch {
@@ -83,7 +82,7 @@ hipError_t launch_chem_prepare(hipStream_t st, long n, const double *y0, double 
 hipError_t launch_chem_clear(hipStream_t st, unsigned long long *cnt);
 hipError_t launch_fwd_layer(hipStream_t st, const FwdLaunch &F, int S, int waves, int grid,
                             int plain_src);
-size_t fwd_lds_bytes(int n_tab, int ring_cap, int row_cap);
+size_t fwd_lds_bytes(int ring_cap, int row_cap);
 hipError_t fwd_configure(size_t max_lds);
 hipError_t fwd_occupancy(size_t lds, int *blocks_per_cu);
 hipError_t launch_fwd_persistent(hipStream_t st, const FwdLaunch &F, int grid);
@@ -101,7 +100,7 @@ struct AdjLaunch {
     int reading;
     TabParams tp;
     const TabNode *tab;
-    const double *m64;
+    const Node64 *n64;
     const double *nHI;
     const double *gbar;
     double *nbar;
@@ -123,9 +122,7 @@ struct AdjLaunch {
     double *nbar_T;
     const char *kept;      // layer pieces: column records kept by the forward, or NULL
     size_t rec_piece_bytes;   // bytes of one pyramid's column record
-    size_t rec_rk_off;        // kept records: offset of the rate coefficients
-    long rec_cap;             // cells (and listed cells) per pyramid record
-    bool split;               // layer pieces: rate terms of dense chunks in the reverse pass
+    long rec_cap;             // cells per pyramid record
     bool early_exit;          // layer pieces: stop at the first opaque layer
     bool sq_table;            // layer pieces: the work-group's LDS table of sqrt(r^2) (else per cell)
 };
@@ -139,7 +136,7 @@ hipError_t launch_adj_prologue(hipStream_t st, const float *nH, const float *xHI
 hipError_t launch_adj_wave(hipStream_t st, const AdjLaunch &L);
 constexpr int kAdjLayerWaves = 16;   // largest work-group of the layer adjoint (waves)
 size_t adj_layer_region_bytes(int S);
-hipError_t adj_layer_occupancy(bool kept, bool split, int waves, size_t lds, int *blocks_per_cu);
+hipError_t adj_layer_occupancy(bool kept, int waves, size_t lds, int *blocks_per_cu);
 hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S);
 hipError_t launch_adj_transpose_prologue(hipStream_t st, const float *nH, const float *xHI,
                                          const double *gbar, double *nHI_T, double *gbar_T,

@@ -139,8 +139,10 @@ int table_blackbody_band(double T_bb, double index, double e_lo_ev, double e_hi_
                      lg_hi, false, P, dP);
 }
 
-// The table in the form the kernels read (see TabNode): node values ln P,
-// log-log slopes tau P'/P, FP32 P, and the parameters of the node grid.
+// The table in the form the kernels read (see TabNode): per node ln P, 1/tau,
+// the cubic of the interval that starts there (from the log-log slopes
+// m = tau P'/P of its two ends, formed in FP64) and P; the parameters of the
+// node grid; the slopes themselves in FP64 (m64, may be NULL).
 void prepare_table(int n, double lg_lo, double lg_hi, const double *P, const double *dP,
                    TabParams *tp, TabNode *nodes, double *m64)
 {
@@ -155,13 +157,28 @@ void prepare_table(int n, double lg_lo, double lg_hi, const double *P, const dou
     tp->tau_lo = std::exp(tp->x_lo);
     tp->tau_hi = std::exp(tp->x_lo + h * (n - 1));
     tp->dP0 = (float)dP[0];
+    tp->ilog = (float)(std::log(2.0) / h);
+    tp->off = (float)(-tp->x_lo / h);
+    tp->u_in = (float)std::expm1(h);
+    tp->fine = h <= kFineStep && tp->tau_lo >= 1e-37 && tp->tau_hi <= 1e37 ? 1 : 0;
+    std::vector<double> m(n);
     for (int k = 0; k < n; ++k) {
         const double tk = std::exp(tp->x_lo + h * k);
         nodes[k].y = std::log(P[k]);
-        const double m = tk * dP[k] / P[k];
-        nodes[k].m = (float)m;
+        nodes[k].it = 1.0 / tk;
         nodes[k].P = (float)P[k];
-        if (m64) m64[k] = m;
+        nodes[k].c1 = nodes[k].c2 = nodes[k].c3 = 0.f;
+        m[k] = tk * dP[k] / P[k];
+        if (m64) m64[k] = m[k];
+    }
+    tp->tame = 1;
+    for (int k = 0; k + 1 < n; ++k) {
+        const double d = nodes[k + 1].y - nodes[k].y, hm0 = h * m[k], hm1 = h * m[k + 1];
+        const double c2 = 3.0 * d - 2.0 * hm0 - hm1, c3 = -2.0 * d + hm0 + hm1;
+        nodes[k].c1 = (float)hm0;
+        nodes[k].c2 = (float)c2;
+        nodes[k].c3 = (float)c3;
+        if (!(std::fabs(hm0) + std::fabs(c2) + std::fabs(c3) <= 0.34)) tp->tame = 0;
     }
 }
 
