@@ -57,6 +57,7 @@ struct AdjArgs {
     int early_exit;          // layer pieces: stop at the first opaque layer
     LayerConst lc;
     int sq_n;                // layer pieces: entries of the work-group's LDS table of sqrt(r^2); 0: none
+    int items;               // layer pieces, direct: the number of pyramids (0: from the counters)
 };
 
 template <int TYPE>
@@ -245,6 +246,18 @@ __device__ __forceinline__ void wave_sync_global()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+template <bool TEAM>
+__device__ __forceinline__ void team_sync_global()
+{
+    if (TEAM) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    } else {
+        wave_sync_global();
+    }
+}
+
 constexpr int kAdjQueue = 128;   // queue entries per wave
 
 // The rate masks of chunks c0 .. c0 + 63 of a layer (first chunk at choff),
@@ -269,6 +282,12 @@ __device__ __forceinline__ uint64_t mask_of_chunk(uint64_t masks, int c)
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)masks, c & 63);
 }
 
+// Bytes of a team's buffers, geometry and flags (the queues follow).
+__host__ __device__ constexpr size_t adj_team_shared_bytes(int S)
+{
+    return (2 * ((size_t)(S + 1) * (S + 1) * sizeof(double) + (size_t)S * sizeof(GeoRow)) + 3 * sizeof(int) + 15) & ~(size_t)15;
+}
+
 // LDS of a wave: one buffer (the columns in (F), the adjoint slots in (R)),
 // the queue of cells with work, the table of factors and index terms; sq: the
 // work-group's table of roots.
@@ -279,18 +298,26 @@ struct AdjLds {
     double *qT;     // adjoint of the cell's exit column
     int *quv;       // u | v << 8, bit 16: the cell has a rate
     GeoRow *geo;
+    int *flag;      // TEAM: see adjoint_layer_piece
 };
 
-template <bool KEPT, bool FAST>
-__device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjLds &W, char *scratch, int src, int p,
-                                                    int lane)
+// TEAM: the work-group's waves take a layer's chunks in turn, in both passes.
+// In (R) a layer's slots are taken from one buffer and the pushes go to the
+// other; W.flag[3] tells all waves that a layer had a push, in turn (a flag is
+// cleared a layer before it is used and two after it was read).
+template <bool KEPT, bool FAST, bool TEAM>
+__device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjLds &W, Team team, char *scratch,
+                                                    int src, int p, int lane)
 {
+    const int w0 = TEAM ? team.w : 0, T = TEAM ? team.T : 1;
+    const int tid = w0 * 64 + lane, nt = T * 64;
+    const bool first = w0 == 0 && lane == 0;
     const int N = A.N;
     const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
     const float R = A.R ? A.R[src] : A.R_cap;
     if (!(R >= 0.f && R <= A.R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 ||
         sk >= N) {
-        if (lane == 0) atomicOr(A.err, 1);
+        if (first) atomicOr(A.err, 1);
         return;
     }
     const double Q = uniform(A.Q[src]);
@@ -315,12 +342,7 @@ __device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjL
     const int Mx = min(uniform(isqrt_floor(Rsq)), L.ext_d);
     double *buf = W.buf;
     GeoRow *geo = W.geo;
-    // the pyramid's index terms along u and v (every pass)
-    for (int k = lane; k < S; k += 64) {
-        geo[k].iu = layer_idx_u(L, N, k);
-        geo[k].iv = layer_idx_v(L, N, k);
-    }
-    wave_sync();
+    sweep_index_terms<TEAM>(L, N, W.sweep, team, lane);   // (every pass)
 
     // ---- (F), every layer; with the early exit only up to the first layer
     // whose cells all leave opaque (layer_opaque): later layers have no rate
@@ -338,24 +360,27 @@ __device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjL
         }
     } else if (Mx >= 1) {
         bool opq = true;   // every cell of layer m so far leaves opaque
-        sweep_layers(
-            L, X, W.sweep, Rsq, Mx, Mt, A.tp.tau_hi, A.lc.inv_hi, lane,
+        sweep_layers<TEAM>(
+            L, X, W.sweep, team, Rsq, Mx, Mt, A.tp.tau_hi, A.lc.inv_hi, lane,
             [&](const SweepChunk &k) {
                 if (k.in) rec.h[off + k.c * 64 + lane] = k.h;
                 const uint64_t mask = ballot(k.in & k.below & layer_owned(L, k.m, k.u, k.v));
-                if (lane == 0) rec.lit[choff + k.c] = mask;
-                if (A.early_exit) opq = opq && ballot(k.in && entry_below(k.h, A.lc.opaque, A.lc.inv_opq)) == 0;
+                if (lane == 0 && k.any) rec.lit[choff + k.c] = mask;
+                if (!TEAM && A.early_exit) opq = opq && ballot(k.in && entry_below(k.h, A.lc.opaque, A.lc.inv_opq)) == 0;
             },
             [&](int m, int total) {
                 off += total;
                 choff += (total + 63) / 64;
-                if (A.early_exit && opq) Mt = m;
+                if (!TEAM && A.early_exit && opq) Mt = m;
                 opq = true;
             });
-        wave_sync_global();
+        team_sync_global<TEAM>();
     }
-    for (int k = lane; k < S * S; k += 64) buf[k] = 0.0;   // the adjoint slots
-    wave_sync_global();
+    const int P2 = (S + 1) * (S + 1);
+    for (int k = tid; k < (TEAM ? 2 * P2 : S * S); k += nt) buf[k] = 0.0;   // the adjoint slots
+    if (TEAM && tid < 3) W.flag[tid] = 0;
+    int turn = 0;   // of the flags
+    team_sync_global<TEAM>();
 
     // ---- (R)
     const NodeArray nodes{A.n64};
@@ -374,22 +399,30 @@ __device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjL
         const double inv_m = rcp_f64((double)m), am = X.alpha * inv_m;
         const int m2 = m * m;
         const uint32_t idx_d = layer_idx_d(L, N, m);
-        for (int k = lane; k < S; k += 64) geo[k].g = layer_geo(m, inv_m, k);
-        wave_sync();
+        for (int k = tid; k < S; k += nt) geo[k].g = layer_geo(m, inv_m, k);
+        double *take = TEAM && (m & 1) ? buf + P2 : buf, *give = TEAM && !(m & 1) ? buf + P2 : buf;
+        const int next = turn == 2 ? 0 : turn + 1;
+        if (TEAM && tid == 0) W.flag[next] = 0;
+        team_sync<TEAM>();
         int qh = 0, qn = 0;   // the queue: qn cells from ring position qh
         bool any = false;
         RectWalk w;
-        w.init(r, lane);
-        // chunks 0 .. nch - 1, then a last round for the cells left in the queue
-        for (int c = 0; c <= nch; ++c) {
-            if (c < nch) {
-                if (c > 0 && (c & 63) == 0) masks = load_masks(rec, choff, c, nch, lane);
+        w.init(r, tid, nt);
+        // the wave's chunks, then a last round for the cells left in the queue
+        int mbase = 0;   // masks: of chunks mbase .. mbase + 63
+        for (int c = w0, last = 0; !last; c += T) {
+            last = c >= nch;
+            if (!last) {
+                if (c >= mbase + 64) {
+                    mbase = c & ~63;
+                    masks = load_masks(rec, choff, mbase, nch, lane);
+                }
                 const int u = w.u, v = w.v;
                 const bool act = (u < r.nu) & (mul24(u, u) + mul24(v, v) <= r.rem);
                 const bool lit = act && ((mask_of_chunk(masks, c) >> lane) & 1);
                 double Tin = 0.0;
                 if (pushed && act) {
-                    double *slot = buf + mul24(u, S) + v;
+                    double *slot = take + mul24(u, S) + v;
                     Tin = *slot;
                     *slot = 0.0;
                 }
@@ -494,7 +527,7 @@ __device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjL
                     Tn += k * Ddt * X.sigma0;
                 }
                 if (m >= 2) {
-                    double *ra = buf + mul24(ua, S), *rb = buf + mul24(ub, S);
+                    double *ra = give + mul24(ua, S), *rb = give + mul24(ub, S);
                     atomicAdd(&ra[va], Tin * b0);
                     atomicAdd(&rb[va], Tin * b1);
                     atomicAdd(&ra[vb], Tin * b2);
@@ -507,9 +540,15 @@ __device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjL
             }
             wave_sync();
         }
+        if (TEAM) {
+            if (any && lane == 0) W.flag[turn] = 1;
+            __syncthreads();
+            any = uniform(W.flag[turn]) != 0;
+            turn = next;
+        }
         pushed = any;
     }
-    if (p == 3 * 0 + 2 && lane == 0) {   // the source cell, once per source
+    if (p == 3 * 0 + 2 && first) {   // the source cell, once per source
         double nb, q1;
         source_cell_adjoint_nodes<FAST>(nodes, A.tp, A.sigma0, A.alpha, Q, n_s, A.gbar[cs], &nb, &q1);
         nb_src += nb;
@@ -531,7 +570,8 @@ __global__ __launch_bounds__(64 * kAdjLayerWaves) void adj_layer(AdjArgs A)
 {
     extern __shared__ __align__(16) char smem[];
     constexpr int TYPE = 3, npieces = 24;
-    if (A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
+    const bool direct = A.items > 0;   // the pyramids in turn, else from the counters
+    if (!direct && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
     // the work-group's table of square roots, when the launch gives one
     // (every pass takes a cell's root from it)
     double *sq = (double *)smem;
@@ -541,36 +581,63 @@ __global__ __launch_bounds__(64 * kAdjLayerWaves) void adj_layer(AdjArgs A)
     const int waves = blockDim.x >> 6;
     AdjLds W;
     W.sq = sq;
-    W.buf = (double *)(smem + (A.sq_n ? layer_sqrt_bytes(A.sq_n - 1) : 0) + (size_t)wave * A.region_bytes);
-    W.qT = W.buf + (size_t)(A.lay_S + 1) * (A.lay_S + 1);
-    W.quv = (int *)(W.qT + kAdjQueue);
-    W.geo = (GeoRow *)(W.quv + kAdjQueue);
     W.sweep.S = A.lay_S;
     W.sweep.sq = 0;
     W.sweep.sq_n = A.sq_n;
     W.sweep.lay = (A.sq_n ? (int)layer_sqrt_bytes(A.sq_n - 1) : 0) + wave * A.region_bytes;
     W.sweep.geo = W.sweep.lay + 8 * (A.lay_S + 1) * (A.lay_S + 1) + kAdjQueue * (int)(sizeof(double) + sizeof(int));
+    W.buf = (double *)(smem + W.sweep.lay);
+    W.qT = W.buf + (size_t)(A.lay_S + 1) * (A.lay_S + 1);
+    W.quv = (int *)(W.qT + kAdjQueue);
+    W.geo = (GeoRow *)(W.quv + kAdjQueue);
+    W.flag = nullptr;
     char *scratch = (char *)(A.store + (size_t)(blockIdx.x * waves + wave) * A.store_stride);
-    const int base = A.seg[TYPE];
-    const int nitems = (A.seg[TYPE + 1] - base) * npieces;
+    const int base = direct ? 0 : A.seg[TYPE];
+    const int nitems = direct ? A.items : (A.seg[TYPE + 1] - base) * npieces;
     const int home = (int)(blockIdx.x % kXcds);
     int chunk = home;
-    for (;;) {
-        const int item = next_item(A.counter, nitems, home, chunk, lane);
+    for (int turn = 0;; ++turn) {
+        const int item = direct ? (turn * (int)gridDim.x + (int)blockIdx.x) * waves + wave
+                                : next_item(A.counter, nitems, home, chunk, lane);
         if (item >= nitems) break;
-        const int src = uniform(A.order[base + item / npieces]);
-        adjoint_layer_piece<KEPT, FAST>(A, W, scratch, src, item % npieces, lane);
+        const int src = direct ? item / npieces : uniform(A.order[base + item / npieces]);
+        adjoint_layer_piece<KEPT, FAST, false>(A, W, Team{0, 1}, scratch, src, item % npieces, lane);
     }
 }
 
-// dL/dn_HI of the layer pieces with dominant axis k is accumulated in the
-// [k][i][j] layout; this kernel builds that layout's n_HI and dL/dGamma and
-// zeroes its accumulator (one 32 x 32 (j, k) tile of one i plane per
-// work-group).
+// One work-group per pyramid (see fwd_team).
+template <bool KEPT, bool FAST>
+__global__ __launch_bounds__(64 * kAdjLayerWaves) void adj_team(AdjArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    const Team team{uniform((int)threadIdx.x >> 6), (int)blockDim.x >> 6};
+    AdjLds W;
+    W.sq = nullptr;
+    W.sweep.S = A.lay_S;
+    W.sweep.sq = 0;
+    W.sweep.sq_n = 0;
+    W.sweep.lay = 0;
+    W.sweep.geo = 2 * 8 * (A.lay_S + 1) * (A.lay_S + 1);
+    W.buf = (double *)smem;
+    W.geo = (GeoRow *)(smem + W.sweep.geo);
+    W.flag = (int *)(W.geo + 2 * A.lay_S);
+    char *queues = smem + adj_team_shared_bytes(A.lay_S);
+    W.qT = (double *)queues + team.w * kAdjQueue;
+    W.quv = (int *)((double *)queues + team.T * kAdjQueue) + team.w * kAdjQueue;
+    char *scratch = (char *)(A.store + (size_t)blockIdx.x * A.store_stride);
+    const int item = blockIdx.x;
+    adjoint_layer_piece<KEPT, FAST, true>(A, W, team, scratch, item / 24, item % 24, threadIdx.x & 63);
+}
+
+// What an adjoint with layer pieces starts from, in one pass over the fields.
+// dL/dn_HI of the pieces with dominant axis k is accumulated in the [k][i][j]
+// layout: that layout's n_HI and dL/dGamma, the zeroed accumulators of both
+// layouts, and the cleared dL/dQ and control block (one 32 x 32 (j, k) tile of
+// one i plane per work-group; the work-groups share the last two).
 constexpr int kTile = 32;
-__global__ __launch_bounds__(256) void adj_transpose_prologue_kernel(
-    const float *__restrict__ nH, const float *__restrict__ xHI, const double *__restrict__ gbar,
-    double *__restrict__ nHI_T, double *__restrict__ gbar_T, double *__restrict__ nbar_T, int N)
+__global__ __launch_bounds__(256) void adj_layer_prologue_kernel(
+    const float *__restrict__ nH, const float *__restrict__ xHI, const double *__restrict__ gbar, AdjBufs B, long nsrc,
+    int *ctl, int nctl, int N)
 {
     __shared__ double tn[kTile][kTile + 1], tg[kTile][kTile + 1];
     const int k0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, i = blockIdx.z;
@@ -579,18 +646,28 @@ __global__ __launch_bounds__(256) void adj_transpose_prologue_kernel(
         const int j = j0 + jj, k = k0 + tx;
         if (j < N && k < N) {
             const size_t c = ((size_t)i * N + j) * N + k;
-            if (nHI_T) tn[jj][tx] = (double)nH[c] * (double)xHI[c];
+            if (B.nHI_T) {   // NULL: both layouts still in place from the forward
+                const double n = (double)nH[c] * (double)xHI[c];
+                tn[jj][tx] = n;
+                B.nHI[c] = n;
+            }
             tg[jj][tx] = gbar[c];
+            B.nbar[c] = 0.0;
         }
     }
+    const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const long threads = (long)gridDim.x * gridDim.y * gridDim.z * 256, me = block * 256 + threadIdx.x;
+    for (long k = me; k < nctl; k += threads) ctl[k] = 0;
+    if (B.qbar)
+        for (long k = me; k < nsrc; k += threads) B.qbar[k] = 0.0;
     __syncthreads();
     for (int kk = ty; kk < kTile; kk += 8) {
         const int k = k0 + kk, j = j0 + tx;
         if (j < N && k < N) {
             const size_t t = ((size_t)k * N + i) * N + j;
-            if (nHI_T) nHI_T[t] = tn[tx][kk];   // NULL: still in place from the forward
-            gbar_T[t] = tg[tx][kk];
-            nbar_T[t] = 0.0;
+            if (B.nHI_T) B.nHI_T[t] = tn[tx][kk];
+            B.gbar_T[t] = tg[tx][kk];
+            B.nbar_T[t] = 0.0;
         }
     }
 }
@@ -669,8 +746,11 @@ static const void *adj_fn(int type)
 }
 
 // fast: a fine and tame table (the general evaluations compiled out)
-static const void *adj_layer_fn(bool kept, bool fast)
+static const void *adj_layer_fn(bool kept, bool fast, bool team = false)
 {
+    if (team)
+        return kept ? (fast ? (const void *)adj_team<true, true> : (const void *)adj_team<true, false>)
+                    : (fast ? (const void *)adj_team<false, true> : (const void *)adj_team<false, false>);
     return kept ? (fast ? (const void *)adj_layer<true, true> : (const void *)adj_layer<true, false>)
                 : (fast ? (const void *)adj_layer<false, true> : (const void *)adj_layer<false, false>);
 }
@@ -680,8 +760,8 @@ hipError_t adj_configure(size_t max_lds)
     const int dyn = (int)max_lds - 64;
     for (int t = 0; t < 3; ++t)
         (void)hipFuncSetAttribute(adj_fn(t), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    for (int f = 0; f < 4; ++f)
-        (void)hipFuncSetAttribute(adj_layer_fn(f & 2, f & 1), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    for (int f = 0; f < 8; ++f)
+        (void)hipFuncSetAttribute(adj_layer_fn(f & 2, f & 1, f & 4), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipGetLastError();
     return hipSuccess;
 }
@@ -742,6 +822,7 @@ static AdjArgs make_adj_args(const AdjLaunch &L)
     A.early_exit = L.early_exit ? 1 : 0;
     A.lc = make_layer_const(L.sigma0, L.alpha, L.tau_w, L.tp.tau_hi);
     A.sq_n = 0;
+    A.items = 0;
     return A;
 }
 
@@ -787,13 +868,31 @@ hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S)
     return hipLaunchKernel(adj_layer_fn(A.kept != nullptr, A.tp.fine && A.tp.tame), dim3(L.grid), dim3(64 * L.waves), args, lds, st);
 }
 
-hipError_t launch_adj_transpose_prologue(hipStream_t st, const float *nH, const float *xHI,
-                                         const double *gbar, double *nHI_T, double *gbar_T,
-                                         double *nbar_T, int N)
+size_t adj_team_bytes(int S, int T)
+{
+    return adj_team_shared_bytes(S) + (size_t)T * kAdjQueue * (sizeof(int) + sizeof(double));
+}
+
+// Every pyramid of the n_src sources, by T waves each: L.grid work-groups, one
+// each if T > 1.
+hipError_t launch_adj_direct(hipStream_t st, const AdjLaunch &L, int Mcap, int S, int T, int n_src)
+{
+    AdjArgs A = make_adj_args(L);
+    A.Mcap = Mcap;
+    A.lay_S = S;
+    A.items = 24 * n_src;
+    A.region_bytes = (int)adj_layer_region_bytes(S);
+    const size_t lds = T > 1 ? adj_team_bytes(S, T) : (size_t)A.region_bytes;
+    void *args[] = {&A};
+    return hipLaunchKernel(adj_layer_fn(A.kept != nullptr, A.tp.fine && A.tp.tame, T > 1), dim3(L.grid), dim3(64 * T),
+                           args, lds, st);
+}
+
+hipError_t launch_adj_layer_prologue(hipStream_t st, const float *nH, const float *xHI, const double *gbar,
+                                     const AdjBufs &B, long nsrc, int *ctl, int nctl, int N)
 {
     const dim3 grid((N + kTile - 1) / kTile, (N + kTile - 1) / kTile, N);
-    hipLaunchKernelGGL(adj_transpose_prologue_kernel, grid, dim3(256), 0, st, nH, xHI, gbar, nHI_T,
-                       gbar_T, nbar_T, N);
+    hipLaunchKernelGGL(adj_layer_prologue_kernel, grid, dim3(256), 0, st, nH, xHI, gbar, B, nsrc, ctl, nctl, N);
     return hipGetLastError();
 }
 

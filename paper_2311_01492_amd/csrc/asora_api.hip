@@ -92,7 +92,7 @@ struct asora_ctx {
     size_t keep_alloc;      // bytes allocated
     size_t keep_need;       // bytes the most recent ASORA_STORE forward needed
     size_t keep_budget;     // 0: half the free device memory at the call
-    bool keep_valid;
+    bool keep_valid, keep_all;
     const void *keep_sig[5];    // n_H, x_HI, src_ijk, src_Q, src_R of that call
     int64_t keep_nsrc;
     float keep_Rmax;
@@ -432,9 +432,19 @@ extern "C" asora_status asora_check(asora_ctx *c, void *stream)
 
 // ---------------------------------------------------------------------------
 // Launch planning: on-chip buffer sizes of one piece type for radii <= R_cap.
+//
+// The radius up to which sources are swept by octants.  The octant kind is for
+// the shell pyramids only: the layer pyramids, one wave each on rectangles
+// with a precomputed factor per row, are as fast from the smallest radius
+// where one octant fills a wave on and faster beyond it (128^3, 6400 sources:
+// radius 8, 534 us by octants, 514 by pyramids; radius 14, 1282 and 857; with
+// the adjoint 2378 and 1724, 6205 and 2858).
+constexpr float kOctPlanned = 24.f;   // radii up to which every plan of the octant kind exists
+static float oct_radius(const asora_ctx *c) { return c->big_kind == 3 ? c->R_whole : c->R_oct; }
+
 static int type_of(const asora_ctx *c, float R)
 {
-    return R <= c->R_whole ? 0 : (R <= c->R_oct ? 1 : 2);
+    return R <= c->R_whole ? 0 : (R <= oct_radius(c) ? 1 : 2);
 }
 
 static asora_status get_layer_plan(asora_ctx *c, float R_cap, Plan *out, bool store = true);
@@ -735,17 +745,63 @@ static asora_status forward_plans(asora_ctx *c, float R_max, bool store, Plan pl
     const int tbig = type_of(c, R_max);
     const int tmax = tbig == 2 ? c->big_kind : tbig;
     for (int t = 0; t <= tmax; ++t) {
-        if (t == 2 && tmax == 3) continue;
-        const float cap = t == tmax ? R_max : (t == 0 ? c->R_whole : c->R_oct);
+        if ((t == 1 || t == 2) && c->big_kind == 3) continue;
+        const float cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
         asora_status st = get_plan(c, t, cap, &plans[t], store);
         if (st) return st;
     }
     *tmax_out = tmax;
+    // an octant radius beyond what octants can be planned for is refused
+    // whether or not the sweep uses them
+    Plan o;
+    if (c->big_kind == 3 && c->R_oct > kOctPlanned && R_max > kOctPlanned)
+        return get_plan(c, 1, std::min(R_max, c->R_oct), &o, store);
     return ASORA_OK;
 }
 
-// The launches of one forward call on buffers B (no allocation).
-static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan plans[4], int tmax,
+// Radii up to which every plan of the whole kind exists.
+static bool team_radii(const asora_ctx *c) { return c->big_kind == 3 && c->R_whole <= 12.f; }
+
+// Calls of few sources.  Sorting the sources, the work counters and the
+// launches of the other kinds then cost as much as the sweeps, and with fewer
+// pyramids than the chip holds waves most of it idles while a layer's chunks
+// wait for each other.  So such a call takes every source as pyramids (also
+// those of a radius that would be swept whole), one work-group each, in one
+// launch, with as many waves to a pyramid as the chip has room for and a layer
+// has chunks.
+//
+// 0: not such a call; else the waves per pyramid.  The line is where the
+// counters catch up: at 64 pyramids per CU (683 sources on 256 CUs; 128^3).
+// 400 sources: radius 4, 46 us against 100; 8, 61 against 126; 30, 316 against
+// 326; radii from 4 to 30, 185 against 216 (pyramids, from the counters).
+// 1600 sources: radius 4, 98 against 99; 30, 933 against 894.  Waves per
+// pyramid for 16 per CU: more wait for each other at the barriers (85 sources
+// of radius 30: 2 waves 116 us, 4 waves 132, 8 waves 183; 1 wave 190).
+//
+// Not for calls that ask for a given sweep (ASORA_PLAIN, the shell pyramids),
+// that stop early (the waves would have to agree on the last layer), or whose
+// radii for the other kinds could be beyond what those kinds' plans allow
+// (such calls are refused).
+constexpr long kDirectPerCu = 64, kTeamWavesPerCu = 16;
+static int team_of(const asora_ctx *c, int64_t n_src, float R_max, uint32_t flags, bool adjoint, bool keep)
+{
+    if (n_src < 1 || (flags & (ASORA_PLAIN | ASORA_EARLY_EXIT)) || !team_radii(c)) return 0;
+    const long pieces = 24 * (long)n_src;
+    if (pieces > kDirectPerCu * c->n_cu) return 0;
+    const int Rsq = (int)std::floor((double)R_max * (double)R_max);
+    if (Rsq > 65535) return 0;
+    const int S = layer_buffer_side(Rsq, make_extent(c->N));
+    const size_t limit = c->max_lds - 64;
+    if ((adjoint ? adj_layer_region_bytes(S) : layer_region_bytes(S, keep)) > limit) return 0;
+    const long room = kTeamWavesPerCu * c->n_cu / pieces, chunks = (S * S + 63) / 64;
+    int T = (int)std::max(1L, std::min(std::min(room, chunks), 16L));
+    while (T > 1 && (adjoint ? adj_team_bytes(S, T) : team_bytes(S, keep, T)) > limit) --T;
+    return T;
+}
+
+// The launches of one forward call on buffers B (no allocation).  team: see
+// team_of.
+static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan plans[4], int tmax, int team,
                                    const float *n_H, const float *x_HI, int64_t n_src, const int32_t *src_ijk,
                                    const double *src_Q, const float *src_R, float R_max, float *gamma,
                                    float *heating, double *coldens_in, uint32_t flags, bool keep,
@@ -754,7 +810,7 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
     const bool prof = (flags & ASORA_PROFILE) != 0;
     hipEvent_t *ev = c->pev[c->prof_count % kProfSlots];
     const long n3 = (long)c->N * c->N * c->N;
-    const bool layers = tmax == 3;
+    const bool layers = tmax == 3 || team > 0;
     FwdLaunch F;
     F.N = c->N;
     F.alpha = c->alpha;
@@ -787,19 +843,24 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
     F.dP0_h = c->dP0_h;
 
     if (prof) HIPCHK(c, hipEventRecord(ev[0], s));
-    HIPCHK(c, launch_prologue(s, n_H, x_HI, B.nhi, B.gacc, coldens_in, n3, B.ctl, kCtlSize, c->n_cu));
-    if (layers) HIPCHK(c, launch_transpose_prologue(s, n_H, x_HI, B.nhi_T, B.gacc_T, c->N));
-    if (heating) {
-        HIPCHK(c, launch_zero(s, c->d_hacc, n3, c->n_cu));
-        if (layers) HIPCHK(c, launch_zero(s, c->d_hacc_T, n3, c->n_cu));
+    const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN) && !team;
+    if (layers) {
+        const FieldBufs f{B.nhi, B.nhi_T, B.gacc, B.gacc_T, F.hacc, F.hacc_T, coldens_in};
+        HIPCHK(c, launch_layer_prologue(s, n_H, x_HI, f, B.ctl, bucketed ? kCtlSize : 0, c->N));
+    } else {
+        HIPCHK(c, launch_prologue(s, n_H, x_HI, B.nhi, B.gacc, coldens_in, n3, B.ctl, kCtlSize, c->n_cu));
+        if (heating) HIPCHK(c, launch_zero(s, c->d_hacc, n3, c->n_cu));
     }
-    const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN);
     if (bucketed)
-        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, c->R_whole, c->R_oct,
+        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, c->R_whole, oct_radius(c),
                                    tmax == 3 ? 3 : 2, B.keys, B.ctl, B.order, c->d_err));
     if (prof) HIPCHK(c, hipEventRecord(ev[1], s));
     if (n_src > 0) {
-        if (flags & ASORA_PLAIN) {
+        if (team > 0) {
+            F.type = 3;
+            F.R_cap = R_max;
+            HIPCHK(c, launch_fwd_direct(s, F, plans[3].S, team, (int)n_src));
+        } else if (flags & ASORA_PLAIN) {
             F.type = tmax;
             F.R_cap = R_max;
             F.ring_cap = plans[tmax].ring_cap;
@@ -815,9 +876,9 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
             }
         } else {
             for (int t = tmax; t >= 0; --t) {
-                if (t == 2 && tmax == 3) continue;
+                if ((t == 1 || t == 2) && c->big_kind == 3) continue;
                 F.type = t;
-                F.R_cap = t == tmax ? R_max : (t == 0 ? c->R_whole : c->R_oct);
+                F.R_cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
                 F.ring_cap = plans[t].ring_cap;
                 F.row_cap = plans[t].row_cap;
                 if (t == 3)
@@ -868,7 +929,9 @@ static asora_status forward(asora_ctx *c, const float *n_H, const float *x_HI, i
     Plan plans[4];
     int tmax = 0;
     if ((st = forward_plans(c, R_max, true, plans, &tmax))) return st;
-    const bool layers = tmax == 3;
+    int team = team_of(c, n_src, R_max, flags, false, (flags & ASORA_STORE) && tmax == 3);
+    if (team && tmax != 3 && get_plan(c, 3, R_max, &plans[3])) team = 0;
+    const bool layers = tmax == 3 || team > 0;
     if ((st = ensure_src_cap(c, n_src))) return st;
     if (layers && (st = ensure_layer_buffers(c))) return st;
     if (heating) {
@@ -880,19 +943,20 @@ static asora_status forward(asora_ctx *c, const float *n_H, const float *x_HI, i
     bool keep = false;
     if (flags & ASORA_STORE) {
         c->keep_valid = false;
-        c->keep_need = layers ? (size_t)n_src * 24 * plans[3].rec_bytes : 0;
+        c->keep_need = tmax == 3 ? (size_t)n_src * 24 * plans[3].rec_bytes : 0;
         if ((st = reserve_keep(c, c->keep_need, &keep))) return st;
     }
     // n_HI and the source order are rewritten from here on (even if a launch fails)
     ++c->nhi_gen;
-    const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN);
+    const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN) && !team;
     if (bucketed) ++c->order_gen;
     const FwdBufs B{c->d_nhi, c->d_gacc, c->d_nhi_T, c->d_gacc_T, c->d_ctl, c->d_keys, c->d_order};
-    if ((st = forward_launch(c, B, plans, tmax, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma, heating,
-                             coldens_in, flags, keep, s)))
+    if ((st = forward_launch(c, B, plans, tmax, team, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma,
+                             heating, coldens_in, flags, keep, s)))
         return st;
     if (keep) {
         c->keep_valid = true;
+        c->keep_all = team > 0 || (flags & ASORA_PLAIN);   // every source has records, not only the large ones
         c->keep_order_gen = bucketed ? c->order_gen : -1;
         c->keep_nhi_gen = c->nhi_gen;
         c->keep_sig[0] = n_H;
@@ -1017,10 +1081,10 @@ extern "C" asora_status asora_raytrace_helium(asora_ctx *c, const float *n_H, co
     // n_HI, n_HeI and zeroed accumulators in both layouts; every source as layer pyramids
     ++c->nhi_gen;
     if (prof) HIPCHK(c, hipEventRecord(ev[0], s));
-    HIPCHK(c, launch_prologue(s, n_H, x_HI, c->d_nhi, c->d_gacc, nullptr, n3, c->d_ctl, kCtlSize, c->n_cu));
-    HIPCHK(c, launch_prologue(s, n_He, x_HeI, c->d_nhe, c->d_ghe, nullptr, n3, c->d_ctl, 0, c->n_cu));
-    HIPCHK(c, launch_transpose_prologue(s, n_H, x_HI, c->d_nhi_T, c->d_gacc_T, c->N));
-    HIPCHK(c, launch_transpose_prologue(s, n_He, x_HeI, c->d_nhe_T, c->d_ghe_T, c->N));
+    const FieldBufs fH{c->d_nhi, c->d_nhi_T, c->d_gacc, c->d_gacc_T, nullptr, nullptr, nullptr};
+    const FieldBufs fHe{c->d_nhe, c->d_nhe_T, c->d_ghe, c->d_ghe_T, nullptr, nullptr, nullptr};
+    HIPCHK(c, launch_layer_prologue(s, n_H, x_HI, fH, c->d_ctl, kCtlSize, c->N));
+    HIPCHK(c, launch_layer_prologue(s, n_He, x_HeI, fHe, c->d_ctl, 0, c->N));
     const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN);
     if (bucketed) {
         HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, -1.f, -1.f, 3, c->d_keys, c->d_ctl,
@@ -1101,12 +1165,14 @@ extern "C" asora_status asora_raytrace_static(asora_ctx *c, const float *n_H, co
     HIPCHK(c, hipSetDevice(c->device));
     Plan plans[4];
     int tmax = 0;
-    if ((st = forward_plans(c, R_max, false, plans, &tmax))) return st;
+    int team = c->R_oct <= kOctPlanned ? team_of(c, n_src, R_max, flags, false, false) : 0;
+    if (team && get_plan(c, 3, R_max, &plans[3], false)) team = 0;
+    if (!team && (st = forward_plans(c, R_max, false, plans, &tmax))) return st;
     char *base = c->d_static;
     const FwdBufs B{(double *)base, (double *)(base + kStaticGrid), (double *)(base + 2 * kStaticGrid),
                     (double *)(base + 3 * kStaticGrid), (int *)(base + kStaticOffCtl), (int *)(base + kStaticOffKeys),
                     (int *)(base + kStaticOffOrder)};
-    return forward_launch(c, B, plans, tmax, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma, nullptr,
+    return forward_launch(c, B, plans, tmax, team, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma, nullptr,
                           coldens_in, flags, false, (hipStream_t)stream);
 }
 
@@ -1299,30 +1365,51 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
     const long n3 = (long)c->N * c->N * c->N;
     const int tbig = type_of(c, R_max);
     const int tmax = tbig == 2 ? c->big_kind : tbig;
-    const bool layers = tmax == 3;
     // ASORA_STORE: the records kept by the forward call with these inputs
     // (and the same early-exit choice: records of an early-exit forward end at
     // the opaque layers)
-    const bool kept = (flags & ASORA_STORE) && layers && c->keep_valid && c->keep_nsrc == n_src &&
+    const bool kept = (flags & ASORA_STORE) && tmax == 3 && c->keep_valid && c->keep_nsrc == n_src &&
                       c->keep_Rmax == R_max && c->keep_sig[0] == n_H && c->keep_sig[1] == x_HI &&
                       c->keep_sig[2] == src_ijk && c->keep_sig[3] == src_Q && c->keep_sig[4] == src_R &&
                       c->keep_early == early;
     Plan plans[4];
     size_t store_need = 0;
-    for (int t = 0; t <= tmax; ++t) {
-        if (t == 2 && layers) continue;
-        const float cap = t == tmax ? R_max : (t == 0 ? c->R_whole : c->R_oct);
-        if ((st = t == 3 ? get_adj_layer_plan(c, cap, kept, &plans[t]) : get_adj_plan(c, t, cap, &plans[t])))
-            return st;
-        size_t need = (size_t)plans[t].grid * plans[t].waves * (size_t)plans[t].scratch;
-        if (t == 3) {   // room for the other form too (kept records or not): see get_adj_layer_plan
-            Plan o;
-            if ((st = get_adj_layer_plan(c, cap, !kept, &o))) return st;
-            const size_t n2 = (size_t)o.grid * o.waves * (size_t)o.scratch;
-            need = n2 > need ? n2 : need;
+    // room for both forms of the layer pieces (kept records or not), see
+    // get_adj_layer_plan
+    auto layer_need = [&](float cap) -> asora_status {
+        Plan o;
+        asora_status e = get_adj_layer_plan(c, cap, kept, &plans[3]);
+        if (e || (e = get_adj_layer_plan(c, cap, !kept, &o))) return e;
+        for (const Plan &q : {plans[3], o}) {
+            const size_t need = (size_t)q.grid * q.waves * (size_t)q.scratch;
+            store_need = need > store_need ? need : store_need;
         }
+        return ASORA_OK;
+    };
+    for (int t = 0; t <= tmax; ++t) {
+        if ((t == 1 || t == 2) && c->big_kind == 3) continue;
+        const float cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
+        if (t == 3) {
+            if ((st = layer_need(cap))) return st;
+            continue;
+        }
+        if ((st = get_adj_plan(c, t, cap, &plans[t]))) return st;
+        const size_t need = (size_t)plans[t].grid * plans[t].waves * (size_t)plans[t].scratch;
         store_need = need > store_need ? need : store_need;
     }
+    if (c->big_kind == 3 && c->R_oct > kOctPlanned && R_max > kOctPlanned &&   // see forward_plans
+        (st = get_adj_plan(c, 1, std::min(R_max, c->R_oct), &plans[1])))
+        return st;
+    // few sources: see team_of.  The records go to the scratch of the
+    // persistent form, which any call up to this radius allocates whatever its
+    // number of sources; records kept by a forward are usable if it kept every
+    // source's.
+    int team = team_of(c, n_src, R_max, flags, true, false);
+    if (tmax < 2 && team_radii(c) && layer_need(R_max)) team = 0;
+    if (kept && !c->keep_all) team = 0;
+    const long slots = team ? (long)plans[3].grid * plans[3].waves : 0;
+    if (team > 1 && 24L * n_src > slots) team = 1;
+    const bool layers = tmax == 3 || team > 0;
     if ((st = ensure_src_cap(c, n_src))) return st;
     if (layers && (st = ensure_adj_layer_buffers(c))) return st;
     if (!c->d_nbar) HIPCHK(c, hipMalloc(&c->d_nbar, sizeof(double) * n3));
@@ -1342,15 +1429,19 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
     // n_HI (both layouts) as the keeping forward left it, if nothing wrote it since
     const bool reuse_nhi = kept && c->keep_nhi_gen == c->nhi_gen;
     // dL/dQ accumulates over pieces: zero it unless the caller accumulates
-    HIPCHK(c, launch_adj_prologue(s, n_H, x_HI, reuse_nhi ? nullptr : c->d_nhi, c->d_nbar, n3, dL_dQ, n_src,
-                                  acc ? 0 : 1, c->d_ctl, reuse_order ? kCtlSeg : kCtlSize, c->n_cu));
-    if (layers)
-        HIPCHK(c, launch_adj_transpose_prologue(s, n_H, x_HI, dL_dgamma, reuse_nhi ? nullptr : c->d_nhi_T,
-                                                c->d_gbar_T, c->d_nbar_T, c->N));
+    const int nctl = team ? 0 : (reuse_order ? kCtlSeg : kCtlSize);
+    if (layers) {
+        const AdjBufs b{reuse_nhi ? nullptr : c->d_nhi, reuse_nhi ? nullptr : c->d_nhi_T, c->d_gbar_T, c->d_nbar,
+                        c->d_nbar_T, acc ? nullptr : dL_dQ};
+        HIPCHK(c, launch_adj_layer_prologue(s, n_H, x_HI, dL_dgamma, b, n_src, c->d_ctl, nctl, c->N));
+    } else {
+        HIPCHK(c, launch_adj_prologue(s, n_H, x_HI, c->d_nhi, c->d_nbar, n3, dL_dQ, n_src, acc ? 0 : 1, c->d_ctl, nctl,
+                                      c->n_cu));
+    }
     if (!reuse_nhi) ++c->nhi_gen;
-    if (n_src > 0 && !reuse_order) {
-        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, c->R_whole, c->R_oct,
-                                   layers ? 3 : 2, c->d_keys, c->d_ctl, c->d_order, c->d_err));
+    if (n_src > 0 && !reuse_order && !team) {
+        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, c->R_whole, oct_radius(c),
+                                   tmax == 3 ? 3 : 2, c->d_keys, c->d_ctl, c->d_order, c->d_err));
         ++c->order_gen;
     }
     if (prof) HIPCHK(c, hipEventRecord(ev[1], s));
@@ -1383,10 +1474,18 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
         L.rec_cap = layers ? plans[3].rec_cap : 0;
         L.early_exit = early;
         L.sq_table = layers && plans[3].sq_table;
-        for (int t = tmax; t >= 0; --t) {
-            if (t == 2 && layers) continue;
+        if (team) {
+            L.type = 3;
+            L.R_cap = R_max;
+            L.store_stride = plans[3].scratch;
+            L.ring_cap = L.row_cap = L.shell_cap = 0;
+            L.grid = (int)std::min(24L * n_src, slots);   // work-groups of one wave share the pyramids
+            HIPCHK(c, launch_adj_direct(s, L, plans[3].Mcap, plans[3].S, team, (int)n_src));
+        }
+        for (int t = team ? -1 : tmax; t >= 0; --t) {
+            if ((t == 1 || t == 2) && c->big_kind == 3) continue;
             L.type = t;
-            L.R_cap = t == tmax ? R_max : (t == 0 ? c->R_whole : c->R_oct);
+            L.R_cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
             L.ring_cap = plans[t].ring_cap;
             L.row_cap = plans[t].row_cap;
             L.shell_cap = plans[t].Qmax;

@@ -1523,33 +1523,34 @@ __host__ __device__ __forceinline__ bool layer_owned(const LayerPiece &L, int m,
 
 // Walks the cells of a layer rectangle 64 at a time: every lane holds cell
 // g = c * 64 + lane of chunk c, and down() / up() move all lanes to chunk
-// c - 1 / c + 1 without a division (64 = q64 * wv + r64).
+// c - 1 / c + 1 without a division (step = q * wv + r).
 struct RectWalk {
-    int u, v, wv, q64, r64;
+    int u, v, wv, q, r;
     // Quotients by wv from its FP32 reciprocal, taken at the middle between
     // integers: (g + 1/2) / wv lies 1 / (2 wv) or more from any integer, and
     // its error is below 4e-7 times the quotient, so both are exact for rows
     // and widths up to 1000.
-    __host__ __device__ __forceinline__ void init(const LayerRect &r, int g)
+    // From cell g on, in steps of `step` cells (a multiple of 64 up to 1024).
+    __host__ __device__ __forceinline__ void init(const LayerRect &rect, int g, int step = 64)
     {
-        wv = r.wv;
+        wv = rect.wv;
         const float inv = rcp_approx((float)wv);
-        q64 = uniform((int)(64.5f * inv));
-        r64 = 64 - q64 * wv;
+        q = uniform((int)(((float)step + 0.5f) * inv));
+        r = step - q * wv;
         u = (int)(((float)g + 0.5f) * inv);
         v = g - mul24(u, wv);
     }
     __host__ __device__ __forceinline__ void down()
     {
-        const bool b = v < r64;
-        v = v + (b ? wv : 0) - r64;
-        u = u - q64 - (b ? 1 : 0);
+        const bool b = v < r;
+        v = v + (b ? wv : 0) - r;
+        u = u - q - (b ? 1 : 0);
     }
     __host__ __device__ __forceinline__ void up()
     {
-        v += r64;
+        v += r;
         const bool c = v >= wv;
-        u += q64 + (c ? 1 : 0);
+        u += q + (c ? 1 : 0);
         v -= c ? wv : 0;
     }
 };

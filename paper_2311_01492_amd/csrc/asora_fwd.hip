@@ -40,6 +40,7 @@ struct FwdArgs {
     int *err;
     int ring_cap, row_cap;
     int plain_src;          // >= 0: non-persistent launch for this source
+    int src0, items;         // layer pieces, direct: the first source, the number of pyramids (0: from the counters)
     int region_bytes;       // per-wave LDS region (wave kernels)
     double coef_unit;       // sigma0 / (4 pi alpha^2)
     const double *nHI_T;    // n_HI in the [k][i][j] layout (layer pieces with d = k)
@@ -428,16 +429,19 @@ __device__ __forceinline__ void layer_rate_batch(const FwdArgs &A, const LayerQu
 
 // EXTRA: with the entry-column output, the early exit or a coarse table;
 // without, those are compiled out (fewer registers for the common sweep).
-template <bool KEEP, bool HEAT, bool EXTRA>
+// TEAM: swept by the work-group's waves together, each with its own queue; not
+// with the early exit, which would have to agree across the waves.
+template <bool KEEP, bool HEAT, bool EXTRA, bool TEAM>
 __device__ __forceinline__ void sweep_layer_piece(const FwdArgs &A, const SweepLds &W, const LayerQueue<KEEP> &Qa,
-                                                  int src, int p, int lane)
+                                                  Team team, int src, int p, int lane)
 {
+    const bool first = (!TEAM || team.w == 0) && lane == 0;
     const int N = A.N;
     const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
     const float R = A.R ? A.R[src] : A.R_cap;
     if (!(R >= 0.f && R <= A.R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 ||
         sk >= N) {
-        if (lane == 0) atomicOr(A.err, 1);
+        if (first) atomicOr(A.err, 1);
         return;
     }
     const double Q = uniform(A.Q[src]);
@@ -460,7 +464,7 @@ __device__ __forceinline__ void sweep_layer_piece(const FwdArgs &A, const SweepL
     if (KEEP)
         rec = layer_record_at(A.keep + ((size_t)src * 24 + p) * A.keep_piece_bytes, A.keep_cap, 0);
 
-    if (p == 3 * 0 + 2 && lane == 0) {   // the source cell, once per source
+    if (p == 3 * 0 + 2 && first) {   // the source cell, once per source
         const double G = source_cell_rate<!EXTRA>(A.tab, A.tp, A.sigma0, A.alpha, Q, n_s);
         if (G != 0.0) unsafeAtomicAdd(&A.gacc[cs], G);
         if (EXTRA && A.coldens) A.coldens[cs] = 0.0;
@@ -474,17 +478,13 @@ __device__ __forceinline__ void sweep_layer_piece(const FwdArgs &A, const SweepL
     // unless the early exit stops the pyramid at its first opaque layer
     int m_last = Mx;
     if (Mx >= 1) {
-        for (int k = lane; k < W.S; k += 64) {   // the pyramid's index terms
-            lds<uint32_t>(W.geo + (int)sizeof(GeoRow) * k + (int)offsetof(GeoRow, iu)) = layer_idx_u(L, N, k);
-            lds<uint32_t>(W.geo + (int)sizeof(GeoRow) * k + (int)offsetof(GeoRow, iv)) = layer_idx_v(L, N, k);
-        }
-        wave_sync();
+        sweep_index_terms<TEAM>(L, N, W, team, lane);
         // the rate queue: `pend` cells from ring position `head`
         int head = 0, pend = 0;
         long off = 0, choff = 0;   // first cell and chunk of layer m in the record
         bool opq = true;           // every cell of layer m so far leaves opaque
-        sweep_layers(
-            L, X, W, Rsq, Mx, m_last, A.tp.tau_hi, A.lc.inv_hi, lane,
+        sweep_layers<TEAM>(
+            L, X, W, team, Rsq, Mx, m_last, A.tp.tau_hi, A.lc.inv_hi, lane,
             [&](const SweepChunk &k) {
                 const bool owned = k.in & layer_owned(L, k.m, k.u, k.v);
                 const bool want = owned & k.below;
@@ -492,8 +492,8 @@ __device__ __forceinline__ void sweep_layer_piece(const FwdArgs &A, const SweepL
                 if (EXTRA && A.coldens && owned)
                     A.coldens[layer_std_index(L, N, k.m, k.u, k.v)] = entry_tau(k.e_in) * X.inv_s0;
                 const uint64_t mask = ballot(want);
-                if (KEEP && lane == 0) rec.lit[choff + k.c] = mask;
-                if (EXTRA && A.early_exit)
+                if (KEEP && lane == 0 && k.any) rec.lit[choff + k.c] = mask;
+                if (EXTRA && !TEAM && A.early_exit)
                     opq = opq && ballot(k.in && entry_below(k.h, A.lc.opaque, A.lc.inv_opq)) == 0;
                 if (want) {
                     const int q = (head + pend + rank_in(mask)) & (kQueue - 1);
@@ -514,14 +514,14 @@ __device__ __forceinline__ void sweep_layer_piece(const FwdArgs &A, const SweepL
             [&](int m, int total) {
                 off += total;
                 choff += (total + 63) / 64;
-                if (EXTRA && A.early_exit && opq) m_last = m;   // every later cell has a zero rate
+                if (EXTRA && !TEAM && A.early_exit && opq) m_last = m;   // every later cell has a zero rate
                 opq = true;
             });
         wave_sync();
         if (lane < pend) layer_rate_batch<KEEP, HEAT, EXTRA>(A, Qa, head, lane, coef, acc, hacc);
         wave_sync();
     }
-    if (KEEP && lane == 0) rec.lit[A.keep_cap / 64 + A.keep_Mcap] = (uint64_t)m_last;
+    if (KEEP && first) rec.lit[A.keep_cap / 64 + A.keep_Mcap] = (uint64_t)m_last;
 }
 
 // The work-group shares only the table of square roots, when the launch gives
@@ -535,7 +535,8 @@ template <bool KEEP, bool HEAT, bool EXTRA>
 __global__ __launch_bounds__(1024) void fwd_layer(FwdArgs A)
 {
     constexpr int TYPE = 3, npieces = 24;
-    if (A.plain_src < 0 && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
+    const bool direct = A.items > 0;
+    if (!direct && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources of this kind
     for (int k = threadIdx.x; k < A.sq_n; k += blockDim.x) lds<double>(8 * k) = sqrt((double)k);
     __syncthreads();
     const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -548,24 +549,39 @@ __global__ __launch_bounds__(1024) void fwd_layer(FwdArgs A)
     W.sq_n = A.sq_n;
     W.lay = region + LayerQueue<KEEP>::kBytes;
     W.geo = W.lay + 8 * (W.S + 1) * (W.S + 1);
-    // persistent: items from the counters; plain: wave w's item is pyramid w
-    const bool plain = A.plain_src >= 0;
-    const int base = plain ? 0 : A.seg[TYPE];
-    const int nitems = plain ? npieces : (A.seg[TYPE + 1] - base) * npieces;
+    // persistent: items from the counters; direct: one item per wave, pyramids
+    // of the sources from src0 on
+    const int base = direct ? 0 : A.seg[TYPE];
+    const int nitems = direct ? A.items : (A.seg[TYPE + 1] - base) * npieces;
     const int home = (int)(blockIdx.x % kXcds);
     int chunk = home;
     for (;;) {
-        const int item = plain ? (int)blockIdx.x * waves + wave : next_item(A.counter, nitems, home, chunk, lane);
+        const int item = direct ? (int)blockIdx.x * waves + wave : next_item(A.counter, nitems, home, chunk, lane);
         if (item >= nitems) break;
-        const int src = plain ? A.plain_src : uniform(A.order[base + item / npieces]);
-        sweep_layer_piece<KEEP, HEAT, EXTRA>(A, W, Qa, src, item % npieces, lane);
-        if (plain) break;
+        const int src = direct ? A.src0 + item / npieces : uniform(A.order[base + item / npieces]);
+        sweep_layer_piece<KEEP, HEAT, EXTRA, false>(A, W, Qa, Team{0, 1}, src, item % npieces, lane);
+        if (direct) break;
     }
 }
 
-// Per-wave LDS of the layer kernel: the rate queue (its in-cell optical depths
-// in FP64 with keep), the (S + 1) x (S + 1) padded layer buffer, the layer's
-// table of bilinear factors and the pyramid's index terms along u and v.
+// One work-group per pyramid, its waves a team: for calls with so few pyramids
+// that one wave each would leave the chip idle.
+template <bool KEEP, bool HEAT, bool EXTRA>
+__global__ __launch_bounds__(1024) void fwd_team(FwdArgs A)
+{
+    const Team team{uniform((int)threadIdx.x >> 6), (int)blockDim.x >> 6};
+    const int lane = threadIdx.x & 63;
+    SweepLds W;
+    W.S = A.lay_S;
+    W.sq = 0;
+    W.sq_n = 0;
+    W.lay = 0;
+    W.geo = 2 * 8 * (W.S + 1) * (W.S + 1);
+    const LayerQueue<KEEP> Qa((W.geo + 2 * (int)sizeof(GeoRow) * W.S + 15 & ~15) + team.w * LayerQueue<KEEP>::kBytes);
+    const int item = blockIdx.x;
+    sweep_layer_piece<KEEP, HEAT, EXTRA, true>(A, W, Qa, team, A.src0 + item / 24, item % 24, lane);
+}
+
 size_t layer_region_bytes(int S, bool keep)
 {
     const size_t b = (size_t)(keep ? LayerQueue<true>::kBytes : LayerQueue<false>::kBytes) +
@@ -573,14 +589,25 @@ size_t layer_region_bytes(int S, bool keep)
     return (b + 15) & ~(size_t)15;
 }
 
-static const void *layer_fn(bool keep, bool heat, bool extra)
+size_t team_bytes(int S, bool keep, int T)
 {
-    static const void *const f[8] = {
+    const size_t shared = 2 * ((size_t)(S + 1) * (S + 1) * sizeof(double) + (size_t)S * sizeof(GeoRow));
+    return ((shared + 15) & ~(size_t)15) +
+           (size_t)T * (keep ? LayerQueue<true>::kBytes : LayerQueue<false>::kBytes);
+}
+
+static const void *layer_fn(bool keep, bool heat, bool extra, bool team = false)
+{
+    static const void *const f[16] = {
         (const void *)fwd_layer<false, false, false>, (const void *)fwd_layer<false, false, true>,
         (const void *)fwd_layer<false, true, false>,  (const void *)fwd_layer<false, true, true>,
         (const void *)fwd_layer<true, false, false>,  (const void *)fwd_layer<true, false, true>,
-        (const void *)fwd_layer<true, true, false>,   (const void *)fwd_layer<true, true, true>};
-    return f[(keep ? 4 : 0) + (heat ? 2 : 0) + (extra ? 1 : 0)];
+        (const void *)fwd_layer<true, true, false>,   (const void *)fwd_layer<true, true, true>,
+        (const void *)fwd_team<false, false, false>,  (const void *)fwd_team<false, false, true>,
+        (const void *)fwd_team<false, true, false>,   (const void *)fwd_team<false, true, true>,
+        (const void *)fwd_team<true, false, false>,   (const void *)fwd_team<true, false, true>,
+        (const void *)fwd_team<true, true, false>,    (const void *)fwd_team<true, true, true>};
+    return f[(team ? 8 : 0) + (keep ? 4 : 0) + (heat ? 2 : 0) + (extra ? 1 : 0)];
 }
 
 hipError_t layer_occupancy(bool keep, int waves, size_t lds, int *blocks_per_cu)
@@ -588,22 +615,43 @@ hipError_t layer_occupancy(bool keep, int waves, size_t lds, int *blocks_per_cu)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, layer_fn(keep, false, false), waves * 64, lds);
 }
 
+// The instance a layer launch needs beyond its outputs: see EXTRA.
+static bool layer_extra(const FwdArgs &A)
+{
+    return A.coldens || A.early_exit || !A.tp.fine || (A.keep && !A.tp.tame);
+}
+
 hipError_t launch_fwd_layer(hipStream_t st, const FwdLaunch &F, int S, int waves, int grid,
                             int plain_src)
 {
     FwdArgs A = make_args(F);
-    A.plain_src = plain_src;
+    if (plain_src >= 0) {
+        A.src0 = plain_src;
+        A.items = 24;
+        grid = (24 + waves - 1) / waves;
+    }
     A.lay_S = S;
     A.region_bytes = (int)layer_region_bytes(S, A.keep != nullptr);
     const int Rsq = (int)floor((double)F.R_cap * (double)F.R_cap);
     const size_t sqb = F.sq_table ? layer_sqrt_bytes(Rsq) : 0;
     A.sq_n = sqb ? Rsq + 1 : 0;
     const size_t lds = sqb + (size_t)waves * A.region_bytes;
-    if (plain_src >= 0) grid = (24 + waves - 1) / waves;
-    const bool extra = F.coldens || F.early_exit || !F.tp.fine || (A.keep && !F.tp.tame);
     void *args[] = {&A};
-    return hipLaunchKernel(layer_fn(A.keep != nullptr, F.hacc != nullptr, extra), dim3(grid), dim3(64 * waves), args,
-                           lds, st);
+    return hipLaunchKernel(layer_fn(A.keep != nullptr, F.hacc != nullptr, layer_extra(A)), dim3(grid), dim3(64 * waves),
+                           args, lds, st);
+}
+
+// Every pyramid of the n_src sources at once, by T waves each.
+hipError_t launch_fwd_direct(hipStream_t st, const FwdLaunch &F, int S, int T, int n_src)
+{
+    FwdArgs A = make_args(F);
+    A.items = 24 * n_src;
+    A.lay_S = S;
+    const bool keep = A.keep != nullptr;
+    A.region_bytes = (int)layer_region_bytes(S, keep);
+    const size_t lds = T > 1 ? team_bytes(S, keep, T) : (size_t)A.region_bytes;
+    void *args[] = {&A};
+    return hipLaunchKernel(layer_fn(keep, F.hacc != nullptr, layer_extra(A), T > 1), dim3(A.items), dim3(64 * T), args, lds, st);
 }
 
 size_t wave_region_bytes(int ring_cap, int row_cap)
@@ -783,15 +831,17 @@ __global__ void scatter_kernel(const int *keys, long nsrc, int *offs, int *order
     order[pos] = (int)s;
 }
 
-// n_HI and the zeroed accumulator in the [k][i][j] layout used by the layer
-// pieces whose dominant axis is k: one 32 x 32 (j, k) tile of one i plane
-// per work-group, staged through LDS so that both the reads (along k) and the
-// writes (along j) are contiguous.
+// What a call with layer pieces starts from, in one pass over the fields: n_HI
+// and the zeroed accumulators (the rate's, with hacc the heating's) in the
+// standard layout and in the [k][i][j] layout of the pieces whose dominant
+// axis is k, the cleared entry columns, the cleared control block.  One 32 x 32
+// (j, k) tile of one i plane per work-group, staged through LDS so that both
+// the reads (along k) and the transposed writes (along j) are contiguous; the
+// work-groups share the control block.
 constexpr int kTile = 32;
-__global__ __launch_bounds__(256) void transpose_prologue_kernel(const float *__restrict__ nH,
-                                                                 const float *__restrict__ xHI,
-                                                                 double *__restrict__ nHI_T,
-                                                                 double *__restrict__ gacc_T, int N)
+__global__ __launch_bounds__(256) void layer_prologue_kernel(const float *__restrict__ nH,
+                                                             const float *__restrict__ xHI, FieldBufs B, int *ctl,
+                                                             int nctl, int N)
 {
     __shared__ double tile[kTile][kTile + 1];
     const int k0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, i = blockIdx.z;
@@ -800,16 +850,25 @@ __global__ __launch_bounds__(256) void transpose_prologue_kernel(const float *__
         const int j = j0 + jj, k = k0 + tx;
         if (j < N && k < N) {
             const size_t c = ((size_t)i * N + j) * N + k;
-            tile[jj][tx] = (double)nH[c] * (double)xHI[c];   // exact
+            const double n = (double)nH[c] * (double)xHI[c];   // exact
+            tile[jj][tx] = n;
+            B.nHI[c] = n;
+            B.gacc[c] = 0.0;
+            if (B.hacc) B.hacc[c] = 0.0;
+            if (B.coldens) B.coldens[c] = 0.0;
         }
     }
+    const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const long threads = (long)gridDim.x * gridDim.y * gridDim.z * 256;
+    for (long k = block * 256 + threadIdx.x; k < nctl; k += threads) ctl[k] = 0;
     __syncthreads();
     for (int kk = ty; kk < kTile; kk += 8) {
         const int k = k0 + kk, j = j0 + tx;
         if (j < N && k < N) {
             const size_t t = ((size_t)k * N + i) * N + j;
-            nHI_T[t] = tile[tx][kk];
-            gacc_T[t] = 0.0;
+            B.nHI_T[t] = tile[tx][kk];
+            B.gacc_T[t] = 0.0;
+            if (B.hacc_T) B.hacc_T[t] = 0.0;
         }
     }
 }
@@ -868,11 +927,11 @@ hipError_t launch_prologue(hipStream_t st, const float *nH, const float *xHI, do
     return hipGetLastError();
 }
 
-hipError_t launch_transpose_prologue(hipStream_t st, const float *nH, const float *xHI, double *nHI_T,
-                                     double *gacc_T, int N)
+hipError_t launch_layer_prologue(hipStream_t st, const float *nH, const float *xHI, const FieldBufs &B, int *ctl,
+                                 int nctl, int N)
 {
     const dim3 grid((N + kTile - 1) / kTile, (N + kTile - 1) / kTile, N);
-    hipLaunchKernelGGL(transpose_prologue_kernel, grid, dim3(256), 0, st, nH, xHI, nHI_T, gacc_T, N);
+    hipLaunchKernelGGL(layer_prologue_kernel, grid, dim3(256), 0, st, nH, xHI, B, ctl, nctl, N);
     return hipGetLastError();
 }
 
@@ -941,6 +1000,8 @@ static FwdArgs make_args(const FwdLaunch &F)
     A.ring_cap = F.ring_cap;
     A.row_cap = F.row_cap;
     A.plain_src = -1;
+    A.src0 = 0;
+    A.items = 0;
     A.region_bytes = 0;
     A.coef_unit = F.sigma0 / (4.0 * M_PI * F.alpha * F.alpha);
     A.lc = make_layer_const(F.sigma0, F.alpha, F.tau_w, F.tp.tau_hi);
@@ -969,8 +1030,8 @@ hipError_t fwd_configure(size_t max_lds)
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<0>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<1>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    for (int f = 0; f < 8; ++f)
-        (void)hipFuncSetAttribute(layer_fn(f & 4, f & 2, f & 1), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    for (int f = 0; f < 16; ++f)
+        (void)hipFuncSetAttribute(layer_fn(f & 4, f & 2, f & 1, f & 8), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipGetLastError();
     return hipSuccess;
 }

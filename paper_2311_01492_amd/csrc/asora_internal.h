@@ -56,12 +56,18 @@ hipError_t launch_prologue(hipStream_t st, const float *nH, const float *xHI, do
 hipError_t launch_bucketing(hipStream_t st, const float *R, const int32_t *ijk, long nsrc, int N,
                             float R_max, float R_whole, float R_oct, int big_type, int *keys,
                             int *ctl, int *order, int *err);
-hipError_t launch_transpose_prologue(hipStream_t st, const float *nH, const float *xHI, double *nHI_T,
-                                     double *gacc_T, int N);
+// The device fields a layer prologue writes; hacc, hacc_T and coldens may be NULL.
+struct FieldBufs {
+    double *nHI, *nHI_T, *gacc, *gacc_T, *hacc, *hacc_T, *coldens;
+};
+hipError_t launch_layer_prologue(hipStream_t st, const float *nH, const float *xHI, const FieldBufs &B, int *ctl,
+                                 int nctl, int N);
 hipError_t launch_transpose_finalize(hipStream_t st, const double *gacc, const double *gacc_T,
                                      float *gamma, int N, int accumulate);
 hipError_t launch_zero(hipStream_t st, double *p, long n, int n_cu);
 size_t layer_region_bytes(int S, bool keep);
+size_t team_bytes(int S, bool keep, int T);
+hipError_t launch_fwd_direct(hipStream_t st, const FwdLaunch &F, int S, int T, int n_src);
 hipError_t layer_occupancy(bool keep, int waves, size_t lds, int *blocks_per_cu);
 
 // hydrogen chemistry step (asora_chem.hip)
@@ -130,6 +136,12 @@ struct AdjLaunch {
 size_t adj_region_bytes(int ring_cap, int row_cap, int shell_cap);
 hipError_t adj_configure(size_t max_lds);
 hipError_t adj_occupancy(int type, int waves, size_t lds, int *blocks_per_cu);
+// The device fields a layer adjoint starts from (nHI, nHI_T: NULL if still in place).
+struct AdjBufs {
+    double *nHI, *nHI_T, *gbar_T, *nbar, *nbar_T, *qbar;
+};
+hipError_t launch_adj_layer_prologue(hipStream_t st, const float *nH, const float *xHI, const double *gbar,
+                                     const AdjBufs &B, long nsrc, int *ctl, int nctl, int N);
 hipError_t launch_adj_prologue(hipStream_t st, const float *nH, const float *xHI, double *nHI,
                                double *nbar, long n3, double *qbar, long nsrc, int zero_q, int *ctl,
                                int nctl, int n_cu);
@@ -138,9 +150,8 @@ constexpr int kAdjLayerWaves = 16;   // largest work-group of the layer adjoint 
 size_t adj_layer_region_bytes(int S);
 hipError_t adj_layer_occupancy(bool kept, int waves, size_t lds, int *blocks_per_cu);
 hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S);
-hipError_t launch_adj_transpose_prologue(hipStream_t st, const float *nH, const float *xHI,
-                                         const double *gbar, double *nHI_T, double *gbar_T,
-                                         double *nbar_T, int N);
+size_t adj_team_bytes(int S, int T);
+hipError_t launch_adj_direct(hipStream_t st, const AdjLaunch &L, int Mcap, int S, int T, int n_src);
 hipError_t launch_adj_transpose_finalize(hipStream_t st, const double *nbar, const double *nbar_T,
                                          const float *nH, const float *xHI, float *dnH, float *dxHI,
                                          int N, int accumulate);
