@@ -248,6 +248,23 @@ static hipError_t device_scratch(int device, char **out)
     return hipSuccess;
 }
 
+// The kernels' dynamic LDS limits, raised once per device (an attribute call is
+// 3 us; there are two dozen instances).
+static std::mutex g_config_mu;
+static bool g_configured[kMaxDevices];
+
+static hipError_t configure_kernels(int device, size_t max_lds)
+{
+    std::lock_guard<std::mutex> g(g_config_mu);
+    const bool known = device >= 0 && device < kMaxDevices;
+    if (known && g_configured[device]) return hipSuccess;
+    hipError_t e = fwd_configure(max_lds);
+    if (e == hipSuccess) e = adj_configure(max_lds);
+    if (e == hipSuccess) e = he_configure(max_lds);
+    if (e == hipSuccess && known) g_configured[device] = true;
+    return e;
+}
+
 extern "C" asora_status asora_init(asora_ctx **out, int32_t N, double cell_cm, double sigma0_cm2,
                                    double lg_tau_lo, double lg_tau_hi, int32_t n_tab,
                                    const double *P, const double *dPdtau,
@@ -304,12 +321,8 @@ extern "C" asora_status asora_init(asora_ctx **out, int32_t N, double cell_cm, d
     const size_t tab_total = tab_off64 + sizeof(Node64) * n_tab;
     std::vector<unsigned char> tab(tab_total);
     {
-        TabNode *nodes = (TabNode *)tab.data();
-        Node64 *n64 = (Node64 *)(tab.data() + tab_off64);
-        std::vector<double> m64(n_tab);
-        prepare_table(n_tab, lg_tau_lo, lg_tau_hi, P, dPdtau, &c->tp, nodes, m64.data());
-        for (int k = 0; k + 1 < n_tab; ++k) n64[k] = make_node64(nodes, m64.data(), c->tp, k);
-        n64[n_tab - 1] = n64[n_tab - 2];   // (intervals end at the last node: never looked up)
+        prepare_table(n_tab, lg_tau_lo, lg_tau_hi, P, dPdtau, &c->tp, (TabNode *)tab.data(), nullptr,
+                      (Node64 *)(tab.data() + tab_off64));
     }
     c->lg_lo = lg_tau_lo;
     c->lg_hi = lg_tau_hi;
@@ -349,8 +362,7 @@ extern "C" asora_status asora_init(asora_ctx **out, int32_t N, double cell_cm, d
         for (int k = 0; k < 4; ++k)
             if (hipEventCreate(&c->pev[sl][k]) != hipSuccess)
                 return bail(fail(nullptr, ASORA_EHIP, "asora_init: hipEventCreate failed"));
-    if (fwd_configure(c->max_lds) != hipSuccess || adj_configure(c->max_lds) != hipSuccess ||
-        he_configure(c->max_lds) != hipSuccess)
+    if (configure_kernels(device, c->max_lds) != hipSuccess)
         return bail(fail(nullptr, ASORA_EHIP, "asora_init: kernel attribute setup failed"));
     if (device < kMaxDevices) {   // beyond, the context works without asora_raytrace_static
         const hipError_t e = device_scratch(device, &c->d_static);

@@ -192,6 +192,6 @@ int table_blackbody_heat(double T_bb, double index, int n, double lg_lo, double 
 int table_blackbody_band(double T_bb, double index, double e_lo_ev, double e_hi_ev, int n, double lg_lo,
                          double lg_hi, double *P, double *dP);
 void prepare_table(int n, double lg_lo, double lg_hi, const double *P, const double *dP,
-                   TabParams *tp, TabNode *nodes, double *m64);
+                   TabParams *tp, TabNode *nodes, double *m64, Node64 *n64 = nullptr);
 
 }  // namespace asora

@@ -142,9 +142,10 @@ int table_blackbody_band(double T_bb, double index, double e_lo_ev, double e_hi_
 // The table in the form the kernels read (see TabNode): per node ln P, 1/tau,
 // the cubic of the interval that starts there (from the log-log slopes
 // m = tau P'/P of its two ends, formed in FP64) and P; the parameters of the
-// node grid; the slopes themselves in FP64 (m64, may be NULL).
+// node grid; the slopes themselves in FP64 (m64, may be NULL) and the nodes in
+// FP64 (n64, may be NULL).
 void prepare_table(int n, double lg_lo, double lg_hi, const double *P, const double *dP,
-                   TabParams *tp, TabNode *nodes, double *m64)
+                   TabParams *tp, TabNode *nodes, double *m64, Node64 *n64)
 {
     const double ln10 = std::log(10.0);
     tp->n = n;
@@ -178,8 +179,10 @@ void prepare_table(int n, double lg_lo, double lg_hi, const double *P, const dou
         nodes[k].c1 = (float)hm0;
         nodes[k].c2 = (float)c2;
         nodes[k].c3 = (float)c3;
+        if (n64) n64[k] = Node64{nodes[k].it, P[k], hm0, c2, c3, 0.0};
         if (!(std::fabs(hm0) + std::fabs(c2) + std::fabs(c3) <= 0.34)) tp->tame = 0;
     }
+    if (n64) n64[n - 1] = n64[n - 2];   // (intervals end at the last node: never looked up)
 }
 
 }  // namespace asora
