@@ -25,6 +25,7 @@ struct PlanKey {
 struct Plan {
     int ring_cap, row_cap, Qmax;
     int S;              // layer pieces: side of the per-wave layer buffer
+    GroupClasses grp;   // group pieces
     long piece_cells;   // largest number of cells of one piece (adjoint scratch)
     long scratch;       // adjoint: doubles of scratch per wave
     int Mcap;           // layer pieces: largest layer index
@@ -443,29 +444,68 @@ extern "C" asora_status asora_check(asora_ctx *c, void *stream)
 }
 
 // ---------------------------------------------------------------------------
-// Launch planning: on-chip buffer sizes of one piece type for radii <= R_cap.
+// The piece kinds of a call (see Radii).
 //
-// The radius up to which sources are swept by octants.  The octant kind is for
-// the shell pyramids only: the layer pyramids, one wave each on rectangles
-// with a precomputed factor per row, are as fast from the smallest radius
-// where one octant fills a wave on and faster beyond it (128^3, 6400 sources:
-// radius 8, 534 us by octants, 514 by pyramids; radius 14, 1282 and 857; with
-// the adjoint 2378 and 1724, 6205 and 2858).
-constexpr float kOctPlanned = 24.f;   // radii up to which every plan of the octant kind exists
-static float oct_radius(const asora_ctx *c) { return c->big_kind == 3 ? c->R_whole : c->R_oct; }
+// Shell sweeps (large kind 2): whole sources and octants by shells, up to the
+// tuning's radii.
+//
+// Layer sweeps (large kind 3): groups of pyramids up to kGroupR and within the
+// box, kGroup[t] of them to a wave in class t; pyramids beyond.  A pyramid of
+// radius 4 fills a fifth of the lanes of its chunks, one of radius 12 half,
+// one of radius 30 nine tenths, and the more pyramids a chunk runs through the
+// fewer lanes are idle; the classes take as many as leave the LDS room for 15
+// waves a CU.  128^3, all sources of one radius, pyramids -> groups: radius 4,
+// 40000 sources 1865 -> 319 us; 7, 12000, 797 -> 261; 10, 12000, 1030 -> 480;
+// 13, 9000, 1067 -> 699; 20, 9000, 1993 -> 1647; 24, 3200, 1046 -> 1049 (three
+// to a group).  Octants by shells, which these replace, took 1477 us for
+// 20000 sources of radius 8 (pyramids 1390) and 1282 for 6400 of radius 14
+// (857).
+// A call up to a radius beyond the classes has few sources in them in all but
+// work; the launch of their own costs more than it gives below 8192 sources
+// (radii from 4 to 30: 3200 sources, 731 us as pyramids, 756 with groups;
+// 9000, 1805 and 1678).
+//
+// A forward that keeps records for an adjoint, and the adjoint, take kind 0 up
+// to the tuning's whole-source radius (the adjoint sweeps those by shells and
+// keeps no records of them) and everything else as pyramids (6400 sources with
+// the adjoint: radius 8, by octants 2378 us, by pyramids 1724; 14, 6205 and
+// 2858).
+constexpr float kGroupR[3] = {7.f, 12.5f, 22.f};
+constexpr int kGroup[3] = {24, 8, 3};
+constexpr int64_t kGroupsBeside = 8192;
+constexpr float kWholePlanned = 12.f, kOctPlanned = 24.f;   // radii up to which every shell plan of the kinds exists
 
-static int type_of(const asora_ctx *c, float R)
+static Radii radii_of(const asora_ctx *c, bool adjoint, float R_max, int64_t n_src)
 {
-    return R <= c->R_whole ? 0 : (R <= oct_radius(c) ? 1 : 2);
+    if (c->big_kind != 3) return Radii{{c->R_whole, c->R_oct, c->R_oct}};
+    const float box = (float)make_extent(c->N).pos;
+    Radii r;
+    for (int t = 0; t < 3; ++t) {
+        r.r[t] = std::min(adjoint ? std::min(c->R_whole, kWholePlanned) : kGroupR[t], box);
+        if (!adjoint && R_max > kGroupR[2] && n_src < kGroupsBeside) r.r[t] = 0.f;
+    }
+    return r;
 }
 
+// The largest kind of a call up to R_max.
+static int largest_kind(const asora_ctx *c, const Radii &r, float R_max)
+{
+    for (int t = 0; t < 3; ++t)
+        if (R_max <= r.r[t]) return t;
+    return c->big_kind;
+}
+
+// Whether a call has kind t (below its largest kind).
+static bool has_kind(const Radii &r, int t) { return t == 0 || r.r[t] > r.r[t - 1]; }
+
+// ---------------------------------------------------------------------------
+// Launch planning: on-chip buffer sizes of one piece type for radii <= R_cap.
 static asora_status get_layer_plan(asora_ctx *c, float R_cap, Plan *out, bool store = true);
 
 // store = false: the plan is not added to the context's table (no host
 // allocation; the allocation-free entry point plans every call)
-static asora_status get_plan(asora_ctx *c, int type, float R_cap, Plan *out, bool store = true)
+static asora_status get_shell_plan(asora_ctx *c, int type, float R_cap, Plan *out, bool store = true)
 {
-    if (type == 3) return get_layer_plan(c, R_cap, out, store);
     const int Rsq = (int)std::floor((double)R_cap * (double)R_cap);
     const PlanKey key{type, Rsq};
     auto it = c->plans.find(key);
@@ -520,6 +560,62 @@ static asora_status get_plan(asora_ctx *c, int type, float R_cap, Plan *out, boo
     if (store) c->plans[key] = P;
     *out = P;
     return ASORA_OK;
+}
+
+// Pyramids to a group of class t: kGroup, or as few as leave the chip's waves
+// about one (class 2, whose groups take longest: two) of them each (700 sources
+// of radius 8: 6 to a group 120 us, 24 137; 800 of radius 20: 2 to a group 270,
+// 3 317).
+static int group_size(const asora_ctx *c, int t, int64_t n_src)
+{
+    const double most = (t == 2 ? 0.55 : 1.3) * 24.0 * (double)n_src / (16.0 * c->n_cu);
+    int G = kGroup[t];
+    while (G > 1 && (G > most || 24 % G)) --G;
+    return G;
+}
+
+// Group pieces: the classes of a call up to R_max.
+static asora_status get_group_plan(asora_ctx *c, const Radii &r, float R_max, int64_t n_src, Plan *out, bool store)
+{
+    Plan P = Plan();
+    GroupClasses &g = P.grp;
+    for (int t = 0; t < 3 && (t == 0 || r.r[t - 1] < R_max); ++t) {
+        const float R = std::min(r.r[t], R_max);
+        g.R[t] = R;
+        g.Rsq[t] = (int)std::floor((double)R * (double)R);
+        g.S[t] = layer_buffer_side(g.Rsq[t], make_extent(c->N));
+        g.G[t] = group_size(c, t, n_src);
+        g.n = t + 1;
+    }
+    const PlanKey key{16 + g.n, g.Rsq[g.n - 1]};
+    auto it = c->plans.find(key);
+    if (it != c->plans.end() && memcmp(&it->second.grp, &g, sizeof g) == 0) {
+        *out = it->second;
+        return ASORA_OK;
+    }
+    P.waves = c->max_waves;
+    while (P.waves > 1 && group_lds_bytes(g, P.waves) > c->max_lds - 64) --P.waves;
+    P.lds = group_lds_bytes(g, P.waves);
+    int bpc = 0;
+    HIPCHK(c, group_occupancy(P.waves, P.lds, &bpc));
+    P.grid = c->n_cu * (bpc > 0 ? bpc : 1);
+    if (store) c->plans[key] = P;
+    *out = P;
+    return ASORA_OK;
+}
+
+// A tuned radius beyond what its kind's shells can be planned for is refused
+// whether or not the call sweeps shells.
+static asora_status check_shell_radii(asora_ctx *c, float R_max, bool store)
+{
+    if (c->big_kind != 3) return ASORA_OK;
+    asora_status st = ASORA_OK;
+    Plan P;
+    if (c->R_whole > kWholePlanned && R_max > kWholePlanned)
+        st = get_shell_plan(c, 0, std::min(R_max, c->R_whole), &P, store);
+    if (!st && c->R_oct > kOctPlanned && R_max > kOctPlanned)
+        st = get_shell_plan(c, 1, std::min(R_max, c->R_oct), &P, store);
+    return st;
 }
 
 // Waves of a layer sweep's work-group: as many per-wave regions as fit in the
@@ -750,29 +846,28 @@ struct FwdBufs {
     int *ctl, *keys, *order;
 };
 
-// Plans of the piece kinds a forward up to R_max uses (plans[t], t <= *tmax;
-// kind 2 is skipped when the large kind is 3).
-static asora_status forward_plans(asora_ctx *c, float R_max, bool store, Plan plans[4], int *tmax_out)
+// Plans of the piece kinds a forward up to R_max uses: plans[t], t <= *tmax,
+// has_kind; with layer sweeps plans[0] for all group pieces, and plans[3].
+static asora_status forward_plans(asora_ctx *c, const Radii &r, float R_max, int64_t n_src, bool store, Plan plans[4], int *tmax_out)
 {
-    const int tbig = type_of(c, R_max);
-    const int tmax = tbig == 2 ? c->big_kind : tbig;
-    for (int t = 0; t <= tmax; ++t) {
-        if ((t == 1 || t == 2) && c->big_kind == 3) continue;
-        const float cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
-        asora_status st = get_plan(c, t, cap, &plans[t], store);
-        if (st) return st;
-    }
+    const int tmax = largest_kind(c, r, R_max);
     *tmax_out = tmax;
-    // an octant radius beyond what octants can be planned for is refused
-    // whether or not the sweep uses them
-    Plan o;
-    if (c->big_kind == 3 && c->R_oct > kOctPlanned && R_max > kOctPlanned)
-        return get_plan(c, 1, std::min(R_max, c->R_oct), &o, store);
-    return ASORA_OK;
+    asora_status st = check_shell_radii(c, R_max, store);
+    if (st) return st;
+    if (c->big_kind == 3) {
+        if (tmax == 3 && (st = get_layer_plan(c, R_max, &plans[3], store))) return st;
+        return get_group_plan(c, r, R_max, n_src, &plans[0], store);
+    }
+    for (int t = 0; t <= tmax && !st; ++t)
+        if (t == tmax || has_kind(r, t)) st = get_shell_plan(c, t, t == tmax ? R_max : r.r[t], &plans[t], store);
+    return st;
 }
 
-// Radii up to which every plan of the whole kind exists.
-static bool team_radii(const asora_ctx *c) { return c->big_kind == 3 && c->R_whole <= 12.f; }
+// Calls that check_shell_radii may refuse are planned in full.
+static bool team_radii(const asora_ctx *c)
+{
+    return c->big_kind == 3 && c->R_whole <= kWholePlanned && c->R_oct <= kOctPlanned;
+}
 
 // Calls of few sources.  Sorting the sources, the work counters and the
 // launches of the other kinds then cost as much as the sweeps, and with fewer
@@ -783,23 +878,24 @@ static bool team_radii(const asora_ctx *c) { return c->big_kind == 3 && c->R_who
 // has chunks.
 //
 // 0: not such a call; else the waves per pyramid.  The line is where the
-// counters catch up: at 64 pyramids per CU (683 sources on 256 CUs; 128^3).
-// 400 sources: radius 4, 46 us against 100; 8, 61 against 126; 30, 316 against
-// 326; radii from 4 to 30, 185 against 216 (pyramids, from the counters).
-// 1600 sources: radius 4, 98 against 99; 30, 933 against 894.  Waves per
-// pyramid for 16 per CU: more wait for each other at the barriers (85 sources
-// of radius 30: 2 waves 116 us, 4 waves 132, 8 waves 183; 1 wave 190).
+// sorted lists catch up: at 128 pyramids per CU (1365 sources on 256 CUs) for
+// radii that the groups take, else at 64 (128^3).  1000 sources: radius 2, 70
+// us against 95 by groups; 13, 180 against 206; 1600 sources: radius 4, 98
+// against 106; 20, 443 against 415.  Radius 30: 400 sources 316 against 326 by
+// pyramids from the lists, 800 equal, 1600 933 against 894.  Waves per pyramid
+// for 16 per CU: more wait for each other at the barriers (85 sources of
+// radius 30: 2 waves 116 us, 4 waves 132, 8 waves 183; 1 wave 190).
 //
 // Not for calls that ask for a given sweep (ASORA_PLAIN, the shell pyramids),
 // that stop early (the waves would have to agree on the last layer), or whose
 // radii for the other kinds could be beyond what those kinds' plans allow
 // (such calls are refused).
-constexpr long kDirectPerCu = 64, kTeamWavesPerCu = 16;
+constexpr long kDirectPerCu[2] = {128, 64}, kTeamWavesPerCu = 16;
 static int team_of(const asora_ctx *c, int64_t n_src, float R_max, uint32_t flags, bool adjoint, bool keep)
 {
     if (n_src < 1 || (flags & (ASORA_PLAIN | ASORA_EARLY_EXIT)) || !team_radii(c)) return 0;
     const long pieces = 24 * (long)n_src;
-    if (pieces > kDirectPerCu * c->n_cu) return 0;
+    if (pieces > kDirectPerCu[adjoint || keep || R_max > kGroupR[2]] * c->n_cu) return 0;
     const int Rsq = (int)std::floor((double)R_max * (double)R_max);
     if (Rsq > 65535) return 0;
     const int S = layer_buffer_side(Rsq, make_extent(c->N));
@@ -813,7 +909,7 @@ static int team_of(const asora_ctx *c, int64_t n_src, float R_max, uint32_t flag
 
 // The launches of one forward call on buffers B (no allocation).  team: see
 // team_of.
-static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan plans[4], int tmax, int team,
+static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Radii &r, const Plan plans[4], int tmax, int team,
                                    const float *n_H, const float *x_HI, int64_t n_src, const int32_t *src_ijk,
                                    const double *src_Q, const float *src_R, float R_max, float *gamma,
                                    float *heating, double *coldens_in, uint32_t flags, bool keep,
@@ -822,7 +918,7 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
     const bool prof = (flags & ASORA_PROFILE) != 0;
     hipEvent_t *ev = c->pev[c->prof_count % kProfSlots];
     const long n3 = (long)c->N * c->N * c->N;
-    const bool layers = tmax == 3 || team > 0;
+    const bool layers = c->big_kind == 3;
     FwdLaunch F;
     F.N = c->N;
     F.alpha = c->alpha;
@@ -843,11 +939,11 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
     F.nHI_T = B.nhi_T;
     F.gacc_T = B.gacc_T;
     F.keep = keep ? c->d_keep : nullptr;
-    F.keep_piece_bytes = layers ? plans[3].rec_bytes : 0;
-    F.keep_cap = layers ? plans[3].rec_cap : 0;
-    F.keep_Mcap = layers ? plans[3].Mcap : 0;
+    F.keep_piece_bytes = keep ? plans[3].rec_bytes : 0;
+    F.keep_cap = keep ? plans[3].rec_cap : 0;
+    F.keep_Mcap = keep ? plans[3].Mcap : 0;
     F.n64 = c->d_n64;
-    F.sq_table = layers && (keep ? plans[3].ksq_table : plans[3].sq_table);
+    F.sq_table = tmax == 3 && (keep ? plans[3].ksq_table : plans[3].sq_table);
     F.early_exit = (flags & ASORA_EARLY_EXIT) != 0;
     F.tab_h = heating ? c->d_tab_h : nullptr;
     F.hacc = heating ? c->d_hacc : nullptr;
@@ -864,8 +960,8 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
         if (heating) HIPCHK(c, launch_zero(s, c->d_hacc, n3, c->n_cu));
     }
     if (bucketed)
-        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, c->R_whole, oct_radius(c),
-                                   tmax == 3 ? 3 : 2, B.keys, B.ctl, B.order, c->d_err));
+        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, r, c->big_kind, B.keys, B.ctl, B.order,
+                                   c->d_err));
     if (prof) HIPCHK(c, hipEventRecord(ev[1], s));
     if (n_src > 0) {
         if (team > 0) {
@@ -881,6 +977,8 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
                 if (tmax == 3)
                     HIPCHK(c, launch_fwd_layer(s, F, plans[3].S, keep ? plans[3].kwaves : plans[3].waves, 0,
                                                (int)k));
+                else if (layers)
+                    HIPCHK(c, launch_fwd_group(s, F, plans[0].grp, plans[0].waves, 0, (int)k));
                 else if (plans[tmax].wave_mode)
                     HIPCHK(c, launch_fwd_wave(s, F, plans[tmax].waves, 0, (int)k));
                 else
@@ -888,15 +986,18 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Plan pl
             }
         } else {
             for (int t = tmax; t >= 0; --t) {
-                if ((t == 1 || t == 2) && c->big_kind == 3) continue;
+                if (t != tmax && !has_kind(r, t)) continue;
                 F.type = t;
-                F.R_cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
+                F.R_cap = t == tmax ? R_max : r.r[t];
                 F.ring_cap = plans[t].ring_cap;
                 F.row_cap = plans[t].row_cap;
                 if (t == 3)
                     HIPCHK(c, launch_fwd_layer(s, F, plans[3].S, keep ? plans[3].kwaves : plans[3].waves,
                                                keep ? plans[3].kgrid : plans[3].grid, -1));
-                else if (plans[t].wave_mode)
+                else if (layers) {
+                    HIPCHK(c, launch_fwd_group(s, F, plans[0].grp, plans[0].waves, plans[0].grid, -1));
+                    break;   // all group pieces
+                } else if (plans[t].wave_mode)
                     HIPCHK(c, launch_fwd_wave(s, F, plans[t].waves, plans[t].grid, -1));
                 else
                     HIPCHK(c, launch_fwd_persistent(s, F, plans[t].grid));
@@ -940,10 +1041,11 @@ static asora_status forward(asora_ctx *c, const float *n_H, const float *x_HI, i
     const long n3 = (long)c->N * c->N * c->N;
     Plan plans[4];
     int tmax = 0;
-    if ((st = forward_plans(c, R_max, true, plans, &tmax))) return st;
+    const Radii r = radii_of(c, (flags & ASORA_STORE) != 0, R_max, n_src);
+    if ((st = forward_plans(c, r, R_max, n_src, true, plans, &tmax))) return st;
     int team = team_of(c, n_src, R_max, flags, false, (flags & ASORA_STORE) && tmax == 3);
-    if (team && tmax != 3 && get_plan(c, 3, R_max, &plans[3])) team = 0;
-    const bool layers = tmax == 3 || team > 0;
+    if (team && tmax != 3 && get_layer_plan(c, R_max, &plans[3])) team = 0;
+    const bool layers = c->big_kind == 3;
     if ((st = ensure_src_cap(c, n_src))) return st;
     if (layers && (st = ensure_layer_buffers(c))) return st;
     if (heating) {
@@ -963,7 +1065,7 @@ static asora_status forward(asora_ctx *c, const float *n_H, const float *x_HI, i
     const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN) && !team;
     if (bucketed) ++c->order_gen;
     const FwdBufs B{c->d_nhi, c->d_gacc, c->d_nhi_T, c->d_gacc_T, c->d_ctl, c->d_keys, c->d_order};
-    if ((st = forward_launch(c, B, plans, tmax, team, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma,
+    if ((st = forward_launch(c, B, r, plans, tmax, team, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma,
                              heating, coldens_in, flags, keep, s)))
         return st;
     if (keep) {
@@ -1099,7 +1201,7 @@ extern "C" asora_status asora_raytrace_helium(asora_ctx *c, const float *n_H, co
     HIPCHK(c, launch_layer_prologue(s, n_He, x_HeI, fHe, c->d_ctl, 0, c->N));
     const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN);
     if (bucketed) {
-        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, -1.f, -1.f, 3, c->d_keys, c->d_ctl,
+        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, Radii{{-1.f, -1.f, -1.f}}, 3, c->d_keys, c->d_ctl,
                                    c->d_order, c->d_err));
         ++c->order_gen;
     }
@@ -1177,14 +1279,15 @@ extern "C" asora_status asora_raytrace_static(asora_ctx *c, const float *n_H, co
     HIPCHK(c, hipSetDevice(c->device));
     Plan plans[4];
     int tmax = 0;
-    int team = c->R_oct <= kOctPlanned ? team_of(c, n_src, R_max, flags, false, false) : 0;
-    if (team && get_plan(c, 3, R_max, &plans[3], false)) team = 0;
-    if (!team && (st = forward_plans(c, R_max, false, plans, &tmax))) return st;
+    const Radii r = radii_of(c, false, R_max, n_src);
+    int team = team_of(c, n_src, R_max, flags, false, false);
+    if (team && get_layer_plan(c, R_max, &plans[3], false)) team = 0;
+    if (!team && (st = forward_plans(c, r, R_max, n_src, false, plans, &tmax))) return st;
     char *base = c->d_static;
     const FwdBufs B{(double *)base, (double *)(base + kStaticGrid), (double *)(base + 2 * kStaticGrid),
                     (double *)(base + 3 * kStaticGrid), (int *)(base + kStaticOffCtl), (int *)(base + kStaticOffKeys),
                     (int *)(base + kStaticOffOrder)};
-    return forward_launch(c, B, plans, tmax, team, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma, nullptr,
+    return forward_launch(c, B, r, plans, tmax, team, n_H, x_HI, n_src, src_ijk, src_Q, src_R, R_max, gamma, nullptr,
                           coldens_in, flags, false, (hipStream_t)stream);
 }
 
@@ -1279,7 +1382,7 @@ static asora_status get_adj_plan(asora_ctx *c, int type, float R_cap, Plan *out)
         return ASORA_OK;
     }
     Plan P;
-    asora_status st = get_plan(c, type, R_cap, &P);   // ring/row/cell sizes
+    asora_status st = get_shell_plan(c, type, R_cap, &P);   // ring/row/cell sizes
     if (st) return st;
     if (P.row_cap > 256)
         return fail(c, ASORA_ENOSYS,
@@ -1375,8 +1478,8 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
     HIPCHK(c, hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)stream;
     const long n3 = (long)c->N * c->N * c->N;
-    const int tbig = type_of(c, R_max);
-    const int tmax = tbig == 2 ? c->big_kind : tbig;
+    const Radii r = radii_of(c, true, R_max, n_src);
+    const int tmax = largest_kind(c, r, R_max);
     // ASORA_STORE: the records kept by the forward call with these inputs
     // (and the same early-exit choice: records of an early-exit forward end at
     // the opaque layers)
@@ -1399,8 +1502,8 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
         return ASORA_OK;
     };
     for (int t = 0; t <= tmax; ++t) {
-        if ((t == 1 || t == 2) && c->big_kind == 3) continue;
-        const float cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
+        if (t != tmax && !has_kind(r, t)) continue;
+        const float cap = t == tmax ? R_max : r.r[t];
         if (t == 3) {
             if ((st = layer_need(cap))) return st;
             continue;
@@ -1409,9 +1512,14 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
         const size_t need = (size_t)plans[t].grid * plans[t].waves * (size_t)plans[t].scratch;
         store_need = need > store_need ? need : store_need;
     }
-    if (c->big_kind == 3 && c->R_oct > kOctPlanned && R_max > kOctPlanned &&   // see forward_plans
-        (st = get_adj_plan(c, 1, std::min(R_max, c->R_oct), &plans[1])))
-        return st;
+    if (c->big_kind == 3) {   // see check_shell_radii
+        Plan o;
+        if (c->R_whole > kWholePlanned && R_max > kWholePlanned &&
+            (st = get_adj_plan(c, 0, std::min(R_max, c->R_whole), &o)))
+            return st;
+        if (c->R_oct > kOctPlanned && R_max > kOctPlanned && (st = get_adj_plan(c, 1, std::min(R_max, c->R_oct), &o)))
+            return st;
+    }
     // few sources: see team_of.  The records go to the scratch of the
     // persistent form, which any call up to this radius allocates whatever its
     // number of sources; records kept by a forward are usable if it kept every
@@ -1452,8 +1560,8 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
     }
     if (!reuse_nhi) ++c->nhi_gen;
     if (n_src > 0 && !reuse_order && !team) {
-        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, c->R_whole, oct_radius(c),
-                                   tmax == 3 ? 3 : 2, c->d_keys, c->d_ctl, c->d_order, c->d_err));
+        HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, r, c->big_kind, c->d_keys, c->d_ctl,
+                                   c->d_order, c->d_err));
         ++c->order_gen;
     }
     if (prof) HIPCHK(c, hipEventRecord(ev[1], s));
@@ -1495,9 +1603,9 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
             HIPCHK(c, launch_adj_direct(s, L, plans[3].Mcap, plans[3].S, team, (int)n_src));
         }
         for (int t = team ? -1 : tmax; t >= 0; --t) {
-            if ((t == 1 || t == 2) && c->big_kind == 3) continue;
+            if (t != tmax && !has_kind(r, t)) continue;
             L.type = t;
-            L.R_cap = t == tmax ? R_max : (t == 0 ? c->R_whole : oct_radius(c));
+            L.R_cap = t == tmax ? R_max : r.r[t];
             L.ring_cap = plans[t].ring_cap;
             L.row_cap = plans[t].row_cap;
             L.shell_cap = plans[t].Qmax;

@@ -42,6 +42,8 @@ struct FwdArgs {
     int plain_src;          // >= 0: non-persistent launch for this source
     int src0, items;         // layer pieces, direct: the first source, the number of pyramids (0: from the counters)
     int region_bytes;       // per-wave LDS region (wave kernels)
+    GroupClasses grp;       // group pieces
+    int grp_shared;         // bytes of their work-group tables
     double coef_unit;       // sigma0 / (4 pi alpha^2)
     const double *nHI_T;    // n_HI in the [k][i][j] layout (layer pieces with d = k)
     double *gacc_T;         // Gamma accumulator in the [k][i][j] layout
@@ -404,7 +406,9 @@ struct LayerQueue {
 
 // One batch of queued cells, from ring position head: the rate added to Gamma,
 // from the FP32 divided difference, with KEEP from the FP64 one.
-template <bool KEEP, bool HEAT, bool EXTRA>
+// BOTH: cells marked kQueueT belong to the transposed accumulators.
+constexpr int kQueueT = 0x8000;
+template <bool KEEP, bool HEAT, bool EXTRA, bool BOTH = false>
 __device__ __forceinline__ void layer_rate_batch(const FwdArgs &A, const LayerQueue<KEEP> &Qa, int head, int lane,
                                                  double coef, double *acc, double *hacc)
 {
@@ -412,7 +416,14 @@ __device__ __forceinline__ void layer_rate_batch(const FwdArgs &A, const LayerQu
     const double ta = entry_tau(lds<double>(Qa.e + 8 * pos));
     const double dt = (double)lds<typename LayerQueue<KEEP>::dt_t>(Qa.dt + (int)sizeof(typename LayerQueue<KEEP>::dt_t) * pos);
     const uint32_t cp = lds<uint32_t>(Qa.cp + 4 * pos);
-    const int r2 = lds<uint16_t>(Qa.r2 + 2 * pos);
+    int r2 = lds<uint16_t>(Qa.r2 + 2 * pos);
+    if (BOTH) {
+        if (r2 & kQueueT) {
+            acc = A.gacc_T;
+            hacc = A.hacc_T;
+        }
+        r2 &= kQueueT - 1;
+    }
     if (!KEEP) {
         const float nd = EXTRA ? neg_divdiff(A.tab, A.tp, ta, dt) : neg_divdiff_fine(A.tab, A.tp, ta, dt);
         if (nd > 0.f) {
@@ -582,6 +593,156 @@ __global__ __launch_bounds__(1024) void fwd_team(FwdArgs A)
     sweep_layer_piece<KEEP, HEAT, EXTRA, true>(A, W, Qa, team, A.src0 + item / 24, item % 24, lane);
 }
 
+// ---- group pieces --------------------------------------------------------
+// One wave sweeps W.G pyramids of a source together (sweep_group), for sources
+// too small for a pyramid's layers to fill a wave.
+template <bool HEAT, bool EXTRA>
+__device__ __forceinline__ void sweep_group_piece(const FwdArgs &A, const GroupLds &W, const LayerQueue<false> &Qa,
+                                                  float R_cap, int src, int part, int lane)
+{
+    const int N = A.N;
+    const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
+    const float R = A.R ? A.R[src] : R_cap;
+    if (!(R >= 0.f && R <= R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 ||
+        sk >= N) {
+        if (lane == 0) atomicOr(A.err, 1);
+        return;
+    }
+    const double Q = uniform(A.Q[src]);
+    const int Rsq = uniform((int)floor((double)R * (double)R));
+    const uint32_t cs = ((uint32_t)si * (uint32_t)N + (uint32_t)sj) * (uint32_t)N + (uint32_t)sk;
+    const double n_s = uniform(A.nHI[cs]);
+    LayerX X;
+    X.N = N;
+    X.reading = A.reading;
+    X.tau_w = A.tau_w;
+    X.sigma0 = A.sigma0;
+    X.alpha = A.alpha;
+    layer_x_source(X, A.lc, n_s);
+    X.nHI = A.nHI;
+    const double coef = uniform(Q * A.coef_unit);
+    if (part == 0 && lane == 0) {   // the source cell, once per source
+        const double G = source_cell_rate<!EXTRA>(A.tab, A.tp, A.sigma0, A.alpha, Q, n_s);
+        if (G != 0.0) unsafeAtomicAdd(&A.gacc[cs], G);
+        if (EXTRA && A.coldens) A.coldens[cs] = 0.0;
+        if (HEAT) {
+            const double H = source_cell_rate<!EXTRA>(A.tab_h, heat_params(A), A.sigma0, A.alpha, Q, n_s);
+            if (H != 0.0) unsafeAtomicAdd(&A.hacc[cs], H);
+        }
+    }
+    const int Mx = uniform(isqrt_floor(Rsq));   // within the box: see radii_of
+    if (Mx < 1) return;
+    group_tables(W, part * W.G, si, sj, sk, N, lane);
+    int head = 0, pend = 0;   // the rate queue
+    sweep_group(X, A.nHI_T, W, Rsq, Mx, A.tp.tau_hi, A.lc.inv_hi, lane, [&](const GroupChunk &k) {
+        const bool owned = k.in & group_owned(k.flags, k.m, k.u, k.v);
+        const bool want = owned & k.below;
+        if (EXTRA && A.coldens && owned) {
+            uint32_t c = k.cell;
+            if (k.flags & kGroupT) {   // [k][i][j] to [i][j][k]
+                const uint32_t n = (uint32_t)N, ck = c / (n * n), cij = c % (n * n);
+                c = cij * n + ck;
+            }
+            A.coldens[c] = entry_tau(k.e_in) * X.inv_s0;
+        }
+        const uint64_t mask = ballot(want);
+        if (want) {
+            const int q = (head + pend + rank_in(mask)) & (kQueue - 1);
+            lds<double>(Qa.e + 8 * q) = k.e_in;
+            lds<float>(Qa.dt + 4 * q) = (float)k.dt;
+            lds<uint32_t>(Qa.cp + 4 * q) = k.cell;
+            lds<uint16_t>(Qa.r2 + 2 * q) = (uint16_t)(k.r2 | (k.flags & kGroupT ? kQueueT : 0));
+        }
+        pend += __popcll(mask);
+        if (pend >= 64) {
+            wave_sync();
+            layer_rate_batch<false, HEAT, EXTRA, true>(A, Qa, head, lane, coef, A.gacc, A.hacc);
+            head = (head + 64) & (kQueue - 1);
+            pend -= 64;
+        }
+    });
+    wave_sync();
+    if (lane < pend) layer_rate_batch<false, HEAT, EXTRA, true>(A, Qa, head, lane, coef, A.gacc, A.hacc);
+    wave_sync();
+}
+
+// Bytes of the work-group's tables and of one wave's region.
+static size_t group_shared_bytes(const GroupClasses &c)
+{
+    const int Rsq = c.Rsq[c.n - 1], M = isqrt_floor(Rsq), S = c.S[c.n - 1];
+    return ((size_t)(Rsq + 1) * sizeof(double) + (size_t)M * S * sizeof(Geo) + 15) & ~(size_t)15;
+}
+static size_t group_wave_bytes(const GroupClasses &c)
+{
+    size_t most = 0;
+    for (int t = 0; t < c.n; ++t) {
+        const size_t b = (size_t)c.G[t] * ((size_t)(c.S[t] + 1) * (c.S[t] + 1) * sizeof(double) + sizeof(GroupRow)) +
+                         12 * (size_t)(isqrt_floor(c.Rsq[t]) + 1) * sizeof(uint32_t);
+        most = b > most ? b : most;
+    }
+    return ((size_t)LayerQueue<false>::kBytes + most + 31) & ~(size_t)15;
+}
+size_t group_lds_bytes(const GroupClasses &c, int waves)
+{
+    return group_shared_bytes(c) + (size_t)waves * group_wave_bytes(c);
+}
+
+// The classes of a call in one launch, the largest radii first: a class's last
+// sources run beside the next one's first.
+template <bool HEAT, bool EXTRA>
+__global__ __launch_bounds__(1024) void fwd_group(FwdArgs A)
+{
+    const bool direct = A.items > 0;
+    if (!direct && A.seg[A.grp.n] == A.seg[0]) return;   // no sources of these kinds
+    const int Rsq = A.grp.Rsq[A.grp.n - 1], M = isqrt_floor(Rsq), S0 = A.grp.S[A.grp.n - 1];
+    GroupLds W;
+    W.sq = 0;
+    W.geo = 8 * (Rsq + 1);
+    W.geo_S = S0;
+    for (int k = threadIdx.x; k <= Rsq; k += blockDim.x) lds<double>(8 * k) = sqrt((double)k);
+    for (int k = threadIdx.x; k < M * S0; k += blockDim.x) {
+        const int m = k / S0 + 1;
+        lds<Geo>(W.geo + (int)sizeof(Geo) * k) = layer_geo(m, rcp_f64((double)m), k % S0);
+    }
+    __syncthreads();
+    const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int waves = blockDim.x >> 6;
+    const LayerQueue<false> Qa(A.grp_shared + wave * A.region_bytes);
+    W.lay = Qa.e + LayerQueue<false>::kBytes;
+    const int home = (int)(blockIdx.x % kXcds);
+    for (int t = A.grp.n - 1; t >= 0; --t) {
+        W.S = A.grp.S[t];
+        W.K = isqrt_floor(A.grp.Rsq[t]) + 1;
+        W.G = A.grp.G[t];
+        W.row = (W.lay + W.G * 8 * (W.S + 1) * (W.S + 1) + 15) & ~15;
+        W.term = W.row + W.G * (int)sizeof(GroupRow);
+        const int npieces = 24 / W.G;
+        const int base = direct ? 0 : A.seg[t];
+        const int nitems = direct ? A.items : (A.seg[t + 1] - base) * npieces;
+        int chunk = home;
+        for (;;) {
+            const int item = direct ? (int)blockIdx.x * waves + wave
+                                    : next_item(A.counter + kXcds * kCounterPad * t, nitems, home, chunk, lane);
+            if (item >= nitems) break;
+            const int src = direct ? A.src0 + item / npieces : uniform(A.order[base + item / npieces]);
+            sweep_group_piece<HEAT, EXTRA>(A, W, Qa, A.grp.R[t], src, item % npieces, lane);
+            if (direct) break;
+        }
+        if (direct) break;
+    }
+}
+
+static const void *group_fn(bool heat, bool extra)
+{
+    return heat ? (extra ? (const void *)fwd_group<true, true> : (const void *)fwd_group<true, false>)
+                : (extra ? (const void *)fwd_group<false, true> : (const void *)fwd_group<false, false>);
+}
+
+hipError_t group_occupancy(int waves, size_t lds, int *blocks_per_cu)
+{
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, group_fn(false, false), waves * 64, lds);
+}
+
 size_t layer_region_bytes(int S, bool keep)
 {
     const size_t b = (size_t)(keep ? LayerQueue<true>::kBytes : LayerQueue<false>::kBytes) +
@@ -639,6 +800,25 @@ hipError_t launch_fwd_layer(hipStream_t st, const FwdLaunch &F, int S, int waves
     void *args[] = {&A};
     return hipLaunchKernel(layer_fn(A.keep != nullptr, F.hacc != nullptr, layer_extra(A)), dim3(grid), dim3(64 * waves),
                            args, lds, st);
+}
+
+// Group pieces; plain_src: the source is of the largest class.
+hipError_t launch_fwd_group(hipStream_t st, const FwdLaunch &F, const GroupClasses &grp, int waves, int grid,
+                            int plain_src)
+{
+    FwdArgs A = make_args(F);
+    A.grp = grp;
+    if (plain_src >= 0) {
+        A.src0 = plain_src;
+        A.items = 24 / grp.G[grp.n - 1];
+        grid = (A.items + waves - 1) / waves;
+    }
+    A.counter = F.ctl + kCtlCounter;   // of class 0
+    A.region_bytes = (int)group_wave_bytes(grp);
+    A.grp_shared = (int)group_shared_bytes(grp);
+    void *args[] = {&A};
+    return hipLaunchKernel(group_fn(F.hacc != nullptr, F.coldens || !F.tp.fine), dim3(grid), dim3(64 * waves), args,
+                           group_lds_bytes(grp, waves), st);
 }
 
 // Every pyramid of the n_src sources at once, by T waves each.
@@ -761,8 +941,7 @@ __device__ __forceinline__ int block_morton(int i, int j, int k, int N)
 // in Morton order, so that sources swept at the same time lie close together
 // and share cached field and accumulator lines.
 __global__ void classify_kernel(const float *R, const int32_t *ijk, long nsrc, int N, float R_max,
-                                float R_whole, float R_oct, int big_type, int *keys, int *hist,
-                                int *err)
+                                Radii radii, int big_type, int *keys, int *hist, int *err)
 {
     const long s = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (s >= nsrc) return;
@@ -773,7 +952,7 @@ __global__ void classify_kernel(const float *R, const int32_t *ijk, long nsrc, i
         atomicOr(err, 1);
         key = kTypes * kSBins;   // not scheduled
     } else {
-        const int type = r <= R_whole ? 0 : (r <= R_oct ? 1 : big_type);
+        const int type = r <= radii.r[0] ? 0 : (r <= radii.r[1] ? 1 : (r <= radii.r[2] ? 2 : big_type));
         key = type * kSBins + block_morton(i, j, k, N);
         atomicAdd(&hist[key], 1);
     }
@@ -945,14 +1124,13 @@ hipError_t launch_transpose_finalize(hipStream_t st, const double *gacc, const d
 }
 
 hipError_t launch_bucketing(hipStream_t st, const float *R, const int32_t *ijk, long nsrc, int N,
-                            float R_max, float R_whole, float R_oct, int big_type, int *keys,
-                            int *ctl, int *order, int *err)
+                            float R_max, const Radii &radii, int big_type, int *keys, int *ctl, int *order, int *err)
 {
     int *hist = ctl + kCtlHist, *offs = ctl + kCtlOffs, *seg = ctl + kCtlSeg;
     const int b = (int)((nsrc + 255) / 256);
     if (nsrc > 0) {
         hipLaunchKernelGGL(classify_kernel, dim3(b), dim3(256), 0, st, R, ijk, nsrc, N, R_max,
-                           R_whole, R_oct, big_type, keys, hist, err);
+                           radii, big_type, keys, hist, err);
     }
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, st, hist, offs, seg);
     if (nsrc > 0)
@@ -1002,6 +1180,7 @@ static FwdArgs make_args(const FwdLaunch &F)
     A.plain_src = -1;
     A.src0 = 0;
     A.items = 0;
+    A.grp = GroupClasses();
     A.region_bytes = 0;
     A.coef_unit = F.sigma0 / (4.0 * M_PI * F.alpha * F.alpha);
     A.lc = make_layer_const(F.sigma0, F.alpha, F.tau_w, F.tp.tau_hi);
@@ -1030,6 +1209,8 @@ hipError_t fwd_configure(size_t max_lds)
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<0>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<1>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipFuncSetAttribute((const void *)fwd_wave_heat<2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    for (int f = 0; f < 4; ++f)
+        (void)hipFuncSetAttribute(group_fn(f & 2, f & 1), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     for (int f = 0; f < 16; ++f)
         (void)hipFuncSetAttribute(layer_fn(f & 4, f & 2, f & 1, f & 8), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipGetLastError();

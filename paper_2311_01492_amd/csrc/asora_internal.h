@@ -18,6 +18,20 @@ constexpr int kCtlHist = kCtlSeg + kCounterPad;  // kTypes*kSBins histogram
 constexpr int kCtlOffs = kCtlHist + kTypes * kSBins;  // kTypes*kSBins scatter offsets
 constexpr int kCtlSize = kCtlOffs + kTypes * kSBins;
 
+// Largest radii of kinds 0, 1, 2 of a call (a kind whose radius is that of the
+// kind before it has no sources); larger sources are of the large kind.
+struct Radii {
+    float r[3];
+};
+
+// Group pieces: per class (kinds 0 .. n - 1 of the call) the largest radius and
+// its square, the layer buffer's side, the pyramids to a wave.
+struct GroupClasses {
+    int n;
+    float R[3];
+    int Rsq[3], S[3], G[3];
+};
+
 struct FwdLaunch {
     int N;
     double alpha, sigma0;
@@ -54,8 +68,7 @@ struct FwdLaunch {
 hipError_t launch_prologue(hipStream_t st, const float *nH, const float *xHI, double *nHI,
                            double *gacc, double *coldens, long n3, int *ctl, int nctl, int n_cu);
 hipError_t launch_bucketing(hipStream_t st, const float *R, const int32_t *ijk, long nsrc, int N,
-                            float R_max, float R_whole, float R_oct, int big_type, int *keys,
-                            int *ctl, int *order, int *err);
+                            float R_max, const Radii &radii, int big_type, int *keys, int *ctl, int *order, int *err);
 // The device fields a layer prologue writes; hacc, hacc_T and coldens may be NULL.
 struct FieldBufs {
     double *nHI, *nHI_T, *gacc, *gacc_T, *hacc, *hacc_T, *coldens;
@@ -68,6 +81,10 @@ hipError_t launch_zero(hipStream_t st, double *p, long n, int n_cu);
 size_t layer_region_bytes(int S, bool keep);
 size_t team_bytes(int S, bool keep, int T);
 hipError_t launch_fwd_direct(hipStream_t st, const FwdLaunch &F, int S, int T, int n_src);
+size_t group_lds_bytes(const GroupClasses &c, int waves);
+hipError_t group_occupancy(int waves, size_t lds, int *blocks_per_cu);
+hipError_t launch_fwd_group(hipStream_t st, const FwdLaunch &F, const GroupClasses &grp, int waves, int grid,
+                            int plain_src);
 hipError_t layer_occupancy(bool keep, int waves, size_t lds, int *blocks_per_cu);
 
 // hydrogen chemistry step (asora_chem.hip)

@@ -197,4 +197,156 @@ __device__ __forceinline__ void sweep_layers(const LayerPiece &L, const LayerX &
     }
 }
 
+// ---- groups of pyramids ---------------------------------------------------
+// A layer of a small pyramid has fewer cells than a wave has lanes, so a wave
+// sweeps G pyramids of a source (G a divisor of 24) together: a group's layer
+// is the G rectangles one after the other, in chunks of 64 cells across their
+// borders.  The radius is within the box on every side, so that the rectangles
+// are alike.
+//
+// What differs from pyramid to pyramid is looked up per lane: GroupRow, and
+// the index terms of the axes.  What depends on the layer alone (the factors,
+// the roots) is the same for every source and held once per work-group.
+struct alignas(16) GroupRow {
+    int d, u, v;   // byte offsets of the pyramid's index terms along d, u, v
+    int flags;     // kGroup...
+};
+constexpr int kGroupNegU = 1, kGroupNegV = 2, kGroupTieU = 4, kGroupTieV = 8, kGroupT = 16;
+
+// Byte offsets: G layer buffers of (S + 1)^2 doubles, G GroupRows, twelve
+// tables of K index terms (axis, sign, layout); shared: the factors of layers
+// 1 .. M (geo_S each), the roots of r^2.
+struct GroupLds {
+    int lay, row, term, geo, sq;
+    int S, K, G;
+    int geo_S;   // row stride of the table of factors
+};
+
+struct GroupChunk {
+    int m;
+    bool in;
+    int u, v, r2, flags;
+    uint32_t cell;      // index in the pyramid's layout
+    double dt, e_in, h;
+    bool below;
+};
+
+// The index terms of a source's axes and the rows of pyramids p0 .. p0 + G - 1.
+__device__ __forceinline__ void group_tables(const GroupLds &W, int p0, int si, int sj, int sk, int N, int lane)
+{
+    const uint32_t n = (uint32_t)N, nn = n * n;
+    for (int k = lane; k < W.K; k += 64) {
+        for (int a = 0; a < 6; ++a) {   // axis, sign
+            const int ax = a >> 1, s = ax == 0 ? si : (ax == 1 ? sj : sk);
+            const uint32_t w = (uint32_t)wrap(a & 1 ? s - k : s + k, N);
+            // standard [i][j][k], transposed [k][i][j]
+            lds<uint32_t>(W.term + 4 * (W.K * (2 * a) + k)) = w * (ax == 0 ? nn : (ax == 1 ? n : 1u));
+            lds<uint32_t>(W.term + 4 * (W.K * (2 * a + 1) + k)) = w * (ax == 0 ? n : (ax == 1 ? 1u : nn));
+        }
+    }
+    if (lane < W.G) {
+        const int p = p0 + lane, oct = p / 3, d = p % 3, au = d == 0 ? 1 : 0, av = d == 2 ? 1 : 2, t = d == 2 ? 1 : 0;
+        auto base = [&](int ax) { return W.term + 4 * W.K * (2 * (2 * ax + ((oct >> ax) & 1)) + t); };
+        GroupRow r;
+        r.d = base(d);
+        r.u = base(au);
+        r.v = base(av);
+        // as in make_layer_piece
+        r.flags = ((oct >> au) & 1 ? kGroupNegU : 0) | ((oct >> av) & 1 ? kGroupNegV : 0) | (d == 0 ? kGroupTieU : 0) |
+                  (d != 2 ? kGroupTieV : 0) | (t ? kGroupT : 0);
+        lds<GroupRow>(W.row + (int)sizeof(GroupRow) * lane) = r;
+    }
+}
+
+// layer_owned of a cell of a group.
+__device__ __forceinline__ bool group_owned(int flags, int m, int u, int v)
+{
+    const int u0 = flags & kGroupNegU, v0 = (flags & kGroupNegV) >> 1;
+    return ((unsigned)(u - u0) < (unsigned)(m + 1 - u0 - ((flags & kGroupTieU) >> 2))) &
+           ((unsigned)(v - v0) < (unsigned)(m + 1 - v0 - ((flags & kGroupTieV) >> 3)));
+}
+
+// Sweeps layers 1 .. Mx of a group; nHI_T: X.nHI in the transposed layout.  In
+// place, as one wave's sweep_layers: a pyramid's cells follow each other in
+// (u, v) order, and chunks go from the last to the first.
+template <class Chunk>
+__device__ __forceinline__ void sweep_group(const LayerX &X, const double *nHI_T, const GroupLds &W, int Rsq, int Mx,
+                                            double tau_hi, double inv_hi, int lane, Chunk chunk)
+{
+    const int P = W.S + 1, P8 = 8 * P, PP8 = P8 * P;
+    for (int k = lane; k < W.G * P * P; k += 64) lds<double>(W.lay + 8 * k) = 0.0;
+    wave_sync();
+    LayerRect r;
+    float inv_t = 0.f, inv_w = 0.f;
+    int cells = 0, m2 = 0, mf = 0, gbase = 0;   // of the layer of the chunk fetched last
+    int p8 = 0, u = 0, v = 0, r2 = 0, flags = 0;
+    uint32_t cp = 0;
+    bool act = false;
+    double nhi = 0.0;
+    auto enter = [&](int m) {
+        r = layer_rect_uniform(Mx, Mx, Rsq, m);
+        inv_t = rcp_approx((float)r.total);
+        inv_w = rcp_approx((float)r.wv);
+        cells = W.G * r.total;
+        m2 = m * m;
+        mf = 4 * m;
+        gbase = W.geo + (int)sizeof(Geo) * W.geo_S * (m - 1);
+    };
+    // (the quotients are exact as in RectWalk::init: at most 24 rectangles)
+    auto fetch = [&](int c) {
+        const int g = c * 64 + lane;
+        int pl = (int)(((float)g + 0.5f) * inv_t);
+        const int l = g - mul24(pl, r.total);
+        u = (int)(((float)l + 0.5f) * inv_w);
+        v = l - mul24(u, r.wv);
+        int uv2 = mul24(u, u) + mul24(v, v);
+        act = (g < cells) & (uv2 <= r.rem);
+        pl = act ? pl : 0;
+        u = act ? u : 0;
+        v = act ? v : 0;
+        uv2 = act ? uv2 : 0;
+        r2 = m2 + uv2;
+        p8 = mul24(pl, PP8);
+        const GroupRow row = lds<GroupRow>(W.row + (int)sizeof(GroupRow) * pl);
+        flags = row.flags;
+        cp = lds<uint32_t>(row.d + mf) + lds<uint32_t>(row.u + 4 * u) + lds<uint32_t>(row.v + 4 * v);
+        nhi = (flags & kGroupT ? nHI_T : X.nHI)[cp];
+    };
+    enter(1);
+    fetch((cells + 63) / 64 - 1);
+    for (int m = 1; m <= Mx; ++m) {
+        const double am = X.sa * rcp_f64((double)m);
+        for (int c = (cells + 63) / 64 - 1; c >= 0; --c) {
+            GroupChunk k;
+            k.m = m;
+            k.in = act;
+            k.u = u;
+            k.v = v;
+            k.r2 = r2;
+            k.flags = flags;
+            k.cell = cp;
+            const int s = p8 + mul24(u, P8) + 8 * v + W.lay, s1 = s + P8;
+            const int ku = gbase + (int)sizeof(Geo) * u, kv = gbase + (int)sizeof(Geo) * v;
+            const double dens = nhi;
+            if (c > 0) {
+                fetch(c - 1);
+            } else if (m < Mx) {
+                enter(m + 1);
+                fetch((cells + 63) / 64 - 1);
+            }
+            const double h3 = lds<double>(s), h1 = lds<double>(s + 8);
+            const double h2 = lds<double>(s1), h0 = lds<double>(s1 + 8);
+            const Geo fu = lds<Geo>(ku), fv = lds<Geo>(kv);
+            const double ads = lds<double>(W.sq + 8 * k.r2) * am;
+            k.dt = dens * ads;
+            const bool thick = ballot(!all_thick(h0, h1, h2, h3)) == 0;
+            k.below = layer_cell_core(X, m, thick, fu, fv, ads, k.dt, h0, h1, h2, h3, tau_hi, inv_hi, &k.e_in, &k.h);
+            if (k.in) lds<double>(s1 + 8) = k.h;
+            asm volatile("" : "+v"(nhi));   // see sweep_layers
+            chunk(k);
+            wave_sync();
+        }
+    }
+}
+
 }  // namespace asora
