@@ -877,25 +877,36 @@ static bool team_radii(const asora_ctx *c)
 // launch, with as many waves to a pyramid as the chip has room for and a layer
 // has chunks.
 //
-// 0: not such a call; else the waves per pyramid.  The line is where the
-// sorted lists catch up: at 128 pyramids per CU (1365 sources on 256 CUs) for
-// radii that the groups take, else at 64 (128^3).  1000 sources: radius 2, 70
-// us against 95 by groups; 13, 180 against 206; 1600 sources: radius 4, 98
-// against 106; 20, 443 against 415.  Radius 30: 400 sources 316 against 326 by
-// pyramids from the lists, 800 equal, 1600 933 against 894.  Waves per pyramid
-// for 16 per CU: more wait for each other at the barriers (85 sources of
-// radius 30: 2 waves 116 us, 4 waves 132, 8 waves 183; 1 wave 190).
+// 0: not such a call; else the waves per pyramid.  The lines are where the
+// sorted lists catch up (256 CUs, 128^3, all sources of one radius; us a call,
+// such a call against the lists):
+//   forward, radii that the groups take, 128 pyramids per CU (1365 sources):
+//     1000 sources of radius 2, 57 and 96; 13, 167 and 203; 20, 307 and 321;
+//     1360 of radius 4, 88 and 104; 20, 390 and 378
+//   forward, larger radii, 48 per CU: 400 of radius 30, 318 and 323; 680, 463
+//     and 457
+//   adjoint and keeping forward, radii up to 15, 64 per CU: with the forward,
+//     680 of radius 2, 129 and 163; 13, 477 and 518
+//   the same, larger radii, 24 per CU: 170 of radius 20, 303 and 394; 400, kept
+//     records, 533 and 519; 170 of radius 30, 618 and 664; 400, 1140 and 1070
+// Waves per pyramid for 16 per CU: more wait for each other at the barriers (85
+// sources of radius 30: 2 waves 116, 4 waves 132, 8 waves 183; 1 wave 190).
 //
 // Not for calls that ask for a given sweep (ASORA_PLAIN, the shell pyramids),
 // that stop early (the waves would have to agree on the last layer), or whose
 // radii for the other kinds could be beyond what those kinds' plans allow
 // (such calls are refused).
-constexpr long kDirectPerCu[2] = {128, 64}, kTeamWavesPerCu = 16;
+constexpr long kTeamWavesPerCu = 16, kHeDirectPerCu = 64;
+static long direct_per_cu(bool adjoint, float R_max)
+{
+    return adjoint ? (R_max <= 15.f ? 64 : 24) : (R_max <= kGroupR[2] ? 128 : 48);
+}
+
 static int team_of(const asora_ctx *c, int64_t n_src, float R_max, uint32_t flags, bool adjoint, bool keep)
 {
     if (n_src < 1 || (flags & (ASORA_PLAIN | ASORA_EARLY_EXIT)) || !team_radii(c)) return 0;
     const long pieces = 24 * (long)n_src;
-    if (pieces > kDirectPerCu[adjoint || keep || R_max > kGroupR[2]] * c->n_cu) return 0;
+    if (pieces > direct_per_cu(adjoint || keep, R_max) * c->n_cu) return 0;
     const int Rsq = (int)std::floor((double)R_max * (double)R_max);
     if (Rsq > 65535) return 0;
     const int S = layer_buffer_side(Rsq, make_extent(c->N));
@@ -953,8 +964,9 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Radii &
     if (prof) HIPCHK(c, hipEventRecord(ev[0], s));
     const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN) && !team;
     if (layers) {
-        const FieldBufs f{B.nhi, B.nhi_T, B.gacc, B.gacc_T, F.hacc, F.hacc_T, coldens_in};
-        HIPCHK(c, launch_layer_prologue(s, n_H, x_HI, f, B.ctl, bucketed ? kCtlSize : 0, c->N));
+        const FieldPair f{{n_H, nullptr}, {x_HI, nullptr},
+                          {{B.nhi, B.nhi_T, B.gacc, B.gacc_T, F.hacc, F.hacc_T, coldens_in}, {}}};
+        HIPCHK(c, launch_layer_prologue(s, f, B.ctl, bucketed ? kCtlSize : 0, c->N));
     } else {
         HIPCHK(c, launch_prologue(s, n_H, x_HI, B.nhi, B.gacc, coldens_in, n3, B.ctl, kCtlSize, c->n_cu));
         if (heating) HIPCHK(c, launch_zero(s, c->d_hacc, n3, c->n_cu));
@@ -1005,14 +1017,12 @@ static asora_status forward_launch(asora_ctx *c, const FwdBufs &B, const Radii &
         }
     }
     if (prof) HIPCHK(c, hipEventRecord(ev[2], s));
-    if (layers)
-        HIPCHK(c, launch_transpose_finalize(s, B.gacc, B.gacc_T, gamma, c->N, (flags & ASORA_ACCUMULATE) ? 1 : 0));
-    else
+    if (layers) {
+        const FinalPair f{{B.gacc, F.hacc}, {B.gacc_T, F.hacc_T}, {gamma, heating}};
+        HIPCHK(c, launch_transpose_finalize(s, f, c->N, (flags & ASORA_ACCUMULATE) ? 1 : 0));
+    } else
         HIPCHK(c, launch_finalize(s, B.gacc, gamma, n3, (flags & ASORA_ACCUMULATE) ? 1 : 0, c->n_cu));
-    if (heating && layers)
-        HIPCHK(c, launch_transpose_finalize(s, c->d_hacc, c->d_hacc_T, heating, c->N,
-                                            (flags & ASORA_ACCUMULATE) ? 1 : 0));
-    else if (heating)
+    if (heating && !layers)
         HIPCHK(c, launch_finalize(s, c->d_hacc, heating, n3, (flags & ASORA_ACCUMULATE) ? 1 : 0, c->n_cu));
     if (prof) {
         HIPCHK(c, hipEventRecord(ev[3], s));
@@ -1195,11 +1205,15 @@ extern "C" asora_status asora_raytrace_helium(asora_ctx *c, const float *n_H, co
     // n_HI, n_HeI and zeroed accumulators in both layouts; every source as layer pyramids
     ++c->nhi_gen;
     if (prof) HIPCHK(c, hipEventRecord(ev[0], s));
-    const FieldBufs fH{c->d_nhi, c->d_nhi_T, c->d_gacc, c->d_gacc_T, nullptr, nullptr, nullptr};
-    const FieldBufs fHe{c->d_nhe, c->d_nhe_T, c->d_ghe, c->d_ghe_T, nullptr, nullptr, nullptr};
-    HIPCHK(c, launch_layer_prologue(s, n_H, x_HI, fH, c->d_ctl, kCtlSize, c->N));
-    HIPCHK(c, launch_layer_prologue(s, n_He, x_HeI, fHe, c->d_ctl, 0, c->N));
-    const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN);
+    // few sources: every pyramid in one launch, as team_of (radii 5 to 20 on
+    // 128^3: 30 sources 114 us against 198 from the sorted lists, 300 206
+    // against 252, 600 278 against 332)
+    const bool direct = n_src > 0 && !(flags & ASORA_PLAIN) && 24 * n_src <= kHeDirectPerCu * c->n_cu;
+    const bool bucketed = n_src > 0 && !(flags & ASORA_PLAIN) && !direct;
+    const FieldPair f{{n_H, n_He}, {x_HI, x_HeI},
+                      {{c->d_nhi, c->d_nhi_T, c->d_gacc, c->d_gacc_T, nullptr, nullptr, nullptr},
+                       {c->d_nhe, c->d_nhe_T, c->d_ghe, c->d_ghe_T, nullptr, nullptr, nullptr}}};
+    HIPCHK(c, launch_layer_prologue(s, f, c->d_ctl, bucketed ? kCtlSize : 0, c->N));
     if (bucketed) {
         HIPCHK(c, launch_bucketing(s, src_R, src_ijk, n_src, c->N, R_max, Radii{{-1.f, -1.f, -1.f}}, 3, c->d_keys, c->d_ctl,
                                    c->d_order, c->d_err));
@@ -1239,14 +1253,23 @@ extern "C" asora_status asora_raytrace_helium(asora_ctx *c, const float *n_H, co
         H.sq_table = plan.sq_table;
         if (flags & ASORA_PLAIN) {
             for (long k = 0; k < n_src; ++k)
-                HIPCHK(c, launch_fwd_layer_he(s, H, plan.S, plan.waves, 0, (int)k));
+                HIPCHK(c, launch_fwd_layer_he(s, H, plan.S, plan.waves, 0, (int)k, 1, 1));
+        } else if (direct) {
+            H.sq_table = false;
+            // (twice the waves of team_of: a batch of the rates of several
+            // bands waits for more loads; 100 sources of radii 5 to 30: 1
+            // wave 331 us, 3 waves 228, 6 waves 317)
+            const long room = 2 * kTeamWavesPerCu * c->n_cu / (24 * n_src), chunks = (plan.S * plan.S + 63) / 64;
+            int T = (int)std::max(1L, std::min(std::min(room, chunks), 16L));
+            while (T > 1 && he_team_bytes(plan.S, T) > c->max_lds - 64) --T;
+            HIPCHK(c, launch_fwd_layer_he(s, H, plan.S, 1, 0, 0, (int)n_src, T));
         } else {
-            HIPCHK(c, launch_fwd_layer_he(s, H, plan.S, plan.waves, plan.grid, -1));
+            HIPCHK(c, launch_fwd_layer_he(s, H, plan.S, plan.waves, plan.grid, 0, 0, 1));
         }
     }
     if (prof) HIPCHK(c, hipEventRecord(ev[2], s));
-    HIPCHK(c, launch_transpose_finalize(s, c->d_gacc, c->d_gacc_T, gamma_HI, c->N, acc));
-    HIPCHK(c, launch_transpose_finalize(s, c->d_ghe, c->d_ghe_T, gamma_HeI, c->N, acc));
+    const FinalPair out{{c->d_gacc, c->d_ghe}, {c->d_gacc_T, c->d_ghe_T}, {gamma_HI, gamma_HeI}};
+    HIPCHK(c, launch_transpose_finalize(s, out, c->N, acc));
     if (prof) {
         HIPCHK(c, hipEventRecord(ev[3], s));
         c->prof_count++;

@@ -1016,14 +1016,16 @@ __global__ void scatter_kernel(const int *keys, long nsrc, int *offs, int *order
 // axis is k, the cleared entry columns, the cleared control block.  One 32 x 32
 // (j, k) tile of one i plane per work-group, staged through LDS so that both
 // the reads (along k) and the transposed writes (along j) are contiguous; the
-// work-groups share the control block.
+// work-groups share the control block.  The planes of a second absorber's field
+// follow those of the first.
 constexpr int kTile = 32;
-__global__ __launch_bounds__(256) void layer_prologue_kernel(const float *__restrict__ nH,
-                                                             const float *__restrict__ xHI, FieldBufs B, int *ctl,
-                                                             int nctl, int N)
+__global__ __launch_bounds__(256) void layer_prologue_kernel(FieldPair F, int *ctl, int nctl, int N)
 {
     __shared__ double tile[kTile][kTile + 1];
-    const int k0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, i = blockIdx.z;
+    const int k0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, s = blockIdx.z >= N ? 1 : 0;
+    const int i = blockIdx.z - s * N;
+    const float *__restrict__ nH = F.n[s], *__restrict__ xHI = F.x[s];
+    const FieldBufs B = F.b[s];
     const int tx = threadIdx.x & (kTile - 1), ty = threadIdx.x / kTile;   // 32 x 8
     for (int jj = ty; jj < kTile; jj += 8) {
         const int j = j0 + jj, k = k0 + tx;
@@ -1052,14 +1054,15 @@ __global__ __launch_bounds__(256) void layer_prologue_kernel(const float *__rest
     }
 }
 
-// Gamma = accumulator + transposed accumulator, in the standard layout.
-__global__ __launch_bounds__(256) void transpose_finalize_kernel(const double *__restrict__ gacc,
-                                                                 const double *__restrict__ gacc_T,
-                                                                 float *__restrict__ gamma, int N,
-                                                                 int accumulate)
+// Gamma = accumulator + transposed accumulator, in the standard layout; the
+// planes of a second output follow those of the first.
+__global__ __launch_bounds__(256) void transpose_finalize_kernel(FinalPair F, int N, int accumulate)
 {
     __shared__ double tile[kTile][kTile + 1];
-    const int k0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, i = blockIdx.z;
+    const int k0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, s = blockIdx.z >= N ? 1 : 0;
+    const int i = blockIdx.z - s * N;
+    const double *__restrict__ gacc = F.acc[s], *__restrict__ gacc_T = F.acc_T[s];
+    float *__restrict__ gamma = F.out[s];
     const int tx = threadIdx.x & (kTile - 1), ty = threadIdx.x / kTile;
     for (int kk = ty; kk < kTile; kk += 8) {
         const int k = k0 + kk, j = j0 + tx;
@@ -1106,20 +1109,17 @@ hipError_t launch_prologue(hipStream_t st, const float *nH, const float *xHI, do
     return hipGetLastError();
 }
 
-hipError_t launch_layer_prologue(hipStream_t st, const float *nH, const float *xHI, const FieldBufs &B, int *ctl,
-                                 int nctl, int N)
+hipError_t launch_layer_prologue(hipStream_t st, const FieldPair &F, int *ctl, int nctl, int N)
 {
-    const dim3 grid((N + kTile - 1) / kTile, (N + kTile - 1) / kTile, N);
-    hipLaunchKernelGGL(layer_prologue_kernel, grid, dim3(256), 0, st, nH, xHI, B, ctl, nctl, N);
+    const dim3 grid((N + kTile - 1) / kTile, (N + kTile - 1) / kTile, F.n[1] ? 2 * N : N);
+    hipLaunchKernelGGL(layer_prologue_kernel, grid, dim3(256), 0, st, F, ctl, nctl, N);
     return hipGetLastError();
 }
 
-hipError_t launch_transpose_finalize(hipStream_t st, const double *gacc, const double *gacc_T,
-                                     float *gamma, int N, int accumulate)
+hipError_t launch_transpose_finalize(hipStream_t st, const FinalPair &F, int N, int accumulate)
 {
-    const dim3 grid((N + kTile - 1) / kTile, (N + kTile - 1) / kTile, N);
-    hipLaunchKernelGGL(transpose_finalize_kernel, grid, dim3(256), 0, st, gacc, gacc_T, gamma, N,
-                       accumulate);
+    const dim3 grid((N + kTile - 1) / kTile, (N + kTile - 1) / kTile, F.out[1] ? 2 * N : N);
+    hipLaunchKernelGGL(transpose_finalize_kernel, grid, dim3(256), 0, st, F, N, accumulate);
     return hipGetLastError();
 }
 

@@ -17,6 +17,7 @@
 // rate; the tables are read through the caches.
 #include "asora_dev.h"
 #include "asora_internal.h"
+#include "asora_sweep.h"
 
 namespace asora {
 
@@ -42,7 +43,7 @@ struct HeArgs {
     const int *seg;
     int *counter;
     int *err;
-    int plain_src;
+    int src0, items;    // direct: the first source, the number of pyramids (0: from the counters)
     int lay_S;
     int region_bytes;
     LayerConst lc;
@@ -55,28 +56,37 @@ struct HeArgs {
 // are recomputed by the batch exactly as the sweep formed them, which keeps
 // the queue, and so the LDS per wave, small.
 constexpr int kHeQueue = 128;
-struct HeQueue {
-    double *e, *NinHe;   // entry HI optical depth (as a layer-buffer entry), entry HeI column
-    uint32_t *cp;
-    uint32_t *mr;
+
+// LDS byte offsets of a wave: the queue's entry HI optical depth (as a
+// layer-buffer entry), entry HeI column, cell index and mr; the two layer
+// buffers; the table of GeoRows; the work-group's roots (at 0).
+struct HeLds {
+    int e, NinHe, cp, mr;
+    int lay, layHe, geo;
+    int S, sq_n;
 };
+
+__host__ __device__ constexpr int he_queue_bytes() { return kHeQueue * (int)(2 * sizeof(double) + 2 * sizeof(uint32_t)); }
 
 // Rates of one queued cell (one lane): every band's divided difference,
 // shared between the species by their cross-sections.  nH, nHe: the fields
-// in the piece's layout.
-__device__ __forceinline__ void he_rate(const HeArgs &A, const HeQueue &Qa, int pos, double coef, const double *sq,
-                                        const double *nH, const double *nHe, double inv_s0, double *gH, double *gHe)
+// in the piece's layout.  FINE: every band's table is.
+template <bool FINE>
+__device__ __forceinline__ void he_rate(const HeArgs &A, const HeLds &W, int pos, double coef, const double *nH,
+                                        const double *nHe, double inv_s0, double *gH, double *gHe)
 {
-    const double NH = entry_tau(Qa.e[pos]) * inv_s0, NHe = Qa.NinHe[pos];
-    const uint32_t cp = Qa.cp[pos], mr = Qa.mr[pos];
+    const double NH = entry_tau(lds<double>(W.e + 8 * pos)) * inv_s0, NHe = lds<double>(W.NinHe + 8 * pos);
+    const uint32_t cp = lds<uint32_t>(W.cp + 4 * pos), mr = lds<uint32_t>(W.mr + 4 * pos);
     const int r2 = (int)(mr & 0xffffu), m = (int)(mr >> 16);
-    const double ds = (A.sq_n ? sq[r2] : sqrt_fast((double)r2)) * rcp_f64((double)m);
-    const double dH = nH[cp] * A.alpha * ds, dHe = nHe[cp] * A.alpha * ds;
+    const double n1 = nH[cp], n2 = nHe[cp];
+    const double ds = (W.sq_n ? lds<double>(8 * r2) : sqrt_fast((double)r2)) * rcp_f64((double)m);
+    const double dH = n1 * A.alpha * ds, dHe = n2 * A.alpha * ds;
     double sumH = 0.0, sumHe = 0.0;
     for (int b = 0; b < A.nb; ++b) {
         const double T = A.sH[b] * NH + A.sHe[b] * NHe;
         const double dT = A.sH[b] * dH + A.sHe[b] * dHe;
-        const double nd = (double)neg_divdiff(A.tab + (size_t)b * A.n_tab, A.tp[b], T, dT);
+        const TabNode *tab = A.tab + (size_t)b * A.n_tab;
+        const double nd = (double)(FINE ? neg_divdiff_fine(tab, A.tp[b], T, dT) : neg_divdiff(tab, A.tp[b], T, dT));
         sumH += A.sH[b] * nd;
         sumHe += A.sHe[b] * nd;
     }
@@ -101,18 +111,23 @@ __device__ void he_source_cell(const HeArgs &A, uint32_t cs, double Q)
     if (GHe != 0.0) unsafeAtomicAdd(&A.gHe[cs], k * GHe);
 }
 
-__device__ void sweep_layer_piece_he(const HeArgs &A, const double *sq, double *lay, double *layHe, Geo *geo,
-                                     uint32_t *iu, uint32_t *iv, const HeQueue &Qa, int src, int p, int lane)
+// As sweep_layers, with the helium field and buffer beside the hydrogen ones:
+// by one wave in place, or by a team (layers of odd m use the second of each
+// buffer and table, `odd` bytes further on).
+template <bool FINE, bool TEAM>
+__device__ __forceinline__ void sweep_layer_piece_he(const HeArgs &A, const HeLds &W, Team team, int src, int p, int lane)
 {
+    const int w0 = TEAM ? team.w : 0, T = TEAM ? team.T : 1, tid = w0 * 64 + lane, nt = T * 64;
+    const bool first = w0 == 0 && lane == 0;
     const int N = A.N;
-    const int si = A.ijk[3 * src], sj = A.ijk[3 * src + 1], sk = A.ijk[3 * src + 2];
+    const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
     const float R = A.R ? A.R[src] : A.R_cap;
     if (!(R >= 0.f && R <= A.R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 || sk >= N) {
-        if (lane == 0) atomicOr(A.err, 1);
+        if (first) atomicOr(A.err, 1);
         return;
     }
-    const double Q = A.Q[src];
-    const int Rsq = (int)floor((double)R * (double)R);
+    const double Q = uniform(A.Q[src]);
+    const int Rsq = uniform((int)floor((double)R * (double)R));
     const LayerPiece L = make_layer_piece(p, si, sj, sk, N, A.ex);
     const uint32_t cs = ((uint32_t)si * (uint32_t)N + (uint32_t)sj) * (uint32_t)N + (uint32_t)sk;
     LayerX X;
@@ -123,157 +138,205 @@ __device__ void sweep_layer_piece_he(const HeArgs &A, const double *sq, double *
     X.alpha = A.alpha;
     layer_x_source(X, A.lc, uniform(A.nHI[cs]));
     X.nHI = L.transposed ? A.nHI_T : A.nHI;
-    const double half_he = A.nHeI[cs] * A.alpha * 0.5;
+    const double half_he = uniform(A.nHeI[cs]) * A.alpha * 0.5;
     const double *nHe = L.transposed ? A.nHeI_T : A.nHeI;
     double *gH = L.transposed ? A.gH_T : A.gH;
     double *gHe = L.transposed ? A.gHe_T : A.gHe;
     const double coef = uniform(Q * A.coef_unit);
-    const int S = A.lay_S;
-    if (p == 3 * 0 + 2 && lane == 0) he_source_cell(A, cs, Q);   // once per source
-    const int Mx = min(isqrt_floor(Rsq), L.ext_d);
-    const int P = S + 1;
-    for (int k = lane; k < P * P; k += 64) {
-        lay[k] = 0.0;
-        layHe[k] = 0.0;
+    if (p == 3 * 0 + 2 && first) he_source_cell(A, cs, Q);   // once per source
+    const int Mx = min(uniform(isqrt_floor(Rsq)), L.ext_d);
+    if (Mx < 1) return;
+    const int S = W.S, P = S + 1, P8 = 8 * P, He = W.layHe - W.lay;
+    const int odd = 2 * P8 * P, geo_odd = (int)sizeof(GeoRow) * S;   // HI and HeI buffers of odd layers
+    for (int k = tid; k < (TEAM ? 4 : 2) * P * P; k += nt) lds<double>(W.lay + 8 * k) = 0.0;
+    const SweepLds G{W.lay, W.geo, 0, W.sq_n, S};
+    sweep_index_terms<TEAM>(L, N, G, team, lane);
+    auto factors = [&](int m, double inv_m) {
+        const int base = W.geo + (TEAM && (m & 1) ? geo_odd : 0);
+        for (int k = tid; k < S; k += nt) lds<Geo>(base + mul24(k, (int)sizeof(GeoRow))) = layer_geo(m, inv_m, k);
+    };
+    auto rounds = [&](int total) { return TEAM ? ((total + 63) / 64 + T - 1) / T : (total + 63) / 64; };
+    LayerRect r;
+    RectWalk w;
+    uint32_t idx_d = 0, cp = 0;
+    int m2 = 0, u = 0, v = 0, r2 = 0, gu = 0, gv = 0, gbase = W.geo;
+    bool act = false;
+    double n1 = 0.0, n2 = 0.0;
+    auto enter = [&](int m) {
+        r = layer_rect_uniform(L.ext_u, L.ext_v, Rsq, m);
+        m2 = m * m;
+        idx_d = layer_idx_d(L, N, m);
+        if (TEAM) gbase = W.geo + (m & 1 ? geo_odd : 0);
+        w.init(r, ((rounds(r.total) - 1) * T + w0) * 64 + lane, nt);
+    };
+    auto fetch = [&]() {
+        const int uv2 = mul24(w.u, w.u) + mul24(w.v, w.v);
+        act = (w.u < r.nu) & (uv2 <= r.rem);
+        u = act ? w.u : 0;
+        v = act ? w.v : 0;
+        r2 = m2 + (act ? uv2 : 0);
+        gu = mul24(u, (int)sizeof(GeoRow)) + gbase;
+        gv = mul24(v, (int)sizeof(GeoRow)) + gbase;
+        cp = idx_d + lds<uint32_t>(gu + (int)offsetof(GeoRow, iu)) + lds<uint32_t>(gv + (int)offsetof(GeoRow, iv));
+        n1 = X.nHI[cp];
+        n2 = nHe[cp];
+    };
+    enter(1);
+    fetch();
+    if (TEAM) {
+        factors(1, 1.0);
+        __syncthreads();
     }
-    for (int k = lane; k < S; k += 64) {
-        iu[k] = layer_idx_u(L, N, k);
-        iv[k] = layer_idx_v(L, N, k);
-    }
-    wave_sync();
-    int head = 0, tail = 0;
+    int head = 0, pend = 0;   // the rate queue
     for (int m = 1; m <= Mx; ++m) {
-        const LayerRect r = layer_rect(L.ext_u, L.ext_v, Rsq, m);
         const double inv_m = rcp_f64((double)m);
-        const int nch = (r.total + 63) / 64;
-        for (int k = lane; k < S; k += 64) geo[k] = layer_geo(m, inv_m, k);
-        wave_sync();
-        RectWalk w;
-        w.init(r, (nch - 1) * 64 + lane);
-        const int m2 = mul24(m, m);
-        const uint32_t idx_d = layer_idx_d(L, N, m);
-        for (int c = nch - 1; c >= 0; --c, w.down()) {
-            const int g = c * 64 + lane;
-            const int u = w.u, v = w.v;
-            const int uv2 = mul24(u, u) + mul24(v, v);
-            const bool act = g < r.total && uv2 <= r.rem;
-            const int pos = layer_slot(u, v, P);
-            double h[4] = {0.0, 0.0, 0.0, 0.0}, e_in = 0.0, hout = 0.0, NinHe = 0.0, dNHe = 0.0;
-            uint32_t cp = 0;
-            const int r2 = m2 + uv2;
-            if (act) h[0] = lay[pos], h[1] = lay[pos - P], h[2] = lay[pos - 1], h[3] = lay[pos - P - 1];
-            const bool thick = __ballot(!all_thick(h[0], h[1], h[2], h[3])) == 0;
-            if (act) {
-                cp = idx_d + iu[u] + iv[v];
-                const double ds = (A.sq_n ? sq[r2] : sqrt_fast((double)r2)) * inv_m;
-                const double ads = X.sa * ds;
-                layer_cell_core(X, m, thick, geo[u], geo[v], ads, X.nHI[cp] * ads, h[0], h[1], h[2], h[3], 0.0,
-                                INFINITY, &e_in, &hout);
-                // the helium column with the same weights: N_He = sum s f M_He / sum s f
-                if (m == 1) {
-                    NinHe = X.reading == 0 ? half_he * ds : half_he;
-                } else {
-                    const double Mh[4] = {layHe[pos], layHe[pos - P], layHe[pos - 1], layHe[pos - P - 1]};
-                    const double sw[4] = {geo[u].om * geo[v].om, geo[u].a * geo[v].om, geo[u].om * geo[v].a,
-                                          geo[u].a * geo[v].a};
-                    double num = 0.0, W = 0.0;
-#pragma unroll
-                    for (int n = 0; n < 4; ++n) {
-                        const double wn = sw[n] * (h[n] > 0.0 ? h[n] : X.inv_tw);
-                        num += wn * Mh[n];
-                        W += wn;
-                    }
-                    NinHe = num * rcp_f64(W);
-                }
-                dNHe = nHe[cp] * A.alpha * ds;
+        if (TEAM) {
+            if (m < Mx) factors(m + 1, rcp_f64((double)(m + 1)));
+        } else {
+            factors(m, inv_m);
+            wave_sync();
+        }
+        const int from = W.lay + (TEAM && !(m & 1) ? odd : 0), to = W.lay + (TEAM && (m & 1) ? odd : 0);
+        for (int c = rounds(r.total) - 1; c >= 0; --c) {
+            const bool in = act;
+            const int ku = gu, kv = gv, r2c = r2, uc = u, vc = v;
+            const uint32_t cell = cp;
+            const double d1 = n1, d2 = n2;
+            if (c > 0) {
+                w.down();
+                fetch();
+            } else if (m < Mx) {
+                enter(m + 1);
+                fetch();
             }
-            wave_sync();   // every read of layer m - 1 before the writes below
-            bool want = false;
-            if (act) {
-                lay[pos] = hout;
-                layHe[pos] = NinHe + dNHe;
-                if (layer_owned(L, m, u, v)) {
-                    const double Nin = entry_tau(e_in) * X.inv_s0;
-                    for (int b = 0; b < A.nb; ++b)
-                        want = want || A.sH[b] * Nin + A.sHe[b] * NinHe < A.tp[b].tau_hi;
-                }
+            const int s = mul24(uc, P8) + 8 * vc, q = s + from, q1 = q + P8;
+            const double h3 = lds<double>(q), h1 = lds<double>(q + 8);
+            const double h2 = lds<double>(q1), h0 = lds<double>(q1 + 8);
+            const double M3 = lds<double>(q + He), M1 = lds<double>(q + He + 8);
+            const double M2 = lds<double>(q1 + He), M0 = lds<double>(q1 + He + 8);
+            const Geo fu = lds<Geo>(ku), fv = lds<Geo>(kv);
+            const double ds = (W.sq_n ? lds<double>(8 * r2c) : sqrt_fast((double)r2c)) * inv_m;
+            const double ads = X.sa * ds;
+            const bool thick = ballot(!all_thick(h0, h1, h2, h3)) == 0;
+            double e_in, hout, NinHe;
+            layer_cell_core(X, m, thick, fu, fv, ads, d1 * ads, h0, h1, h2, h3, 0.0, INFINITY, &e_in, &hout);
+            // the helium column with the same weights: N_He = sum s f M_He / sum s f
+            if (m == 1) {
+                NinHe = X.reading == 0 ? half_he * ds : half_he;
+            } else {
+                const double w0 = fu.om * fv.om * (h0 > 0.0 ? h0 : X.inv_tw);
+                const double w1 = fu.a * fv.om * (h1 > 0.0 ? h1 : X.inv_tw);
+                const double w2 = fu.om * fv.a * (h2 > 0.0 ? h2 : X.inv_tw);
+                const double w3 = fu.a * fv.a * (h3 > 0.0 ? h3 : X.inv_tw);
+                NinHe = (w0 * M0 + w1 * M1 + w2 * M2 + w3 * M3) * rcp_f64(w0 + w1 + w2 + w3);
             }
-            const uint64_t mask = __ballot(want);
+            if (in) {
+                lds<double>(s + to + P8 + 8) = hout;
+                lds<double>(s + to + P8 + He + 8) = NinHe + d2 * A.alpha * ds;
+            }
+            const double Nin = entry_tau(e_in) * X.inv_s0;
+            bool below = false;
+            for (int b = 0; b < A.nb; ++b) below |= A.sH[b] * Nin + A.sHe[b] * NinHe < A.tp[b].tau_hi;
+            const bool want = in & below & layer_owned(L, m, uc, vc);
+            asm volatile("" : "+v"(n1), "+v"(n2));   // see sweep_layers
+            const uint64_t mask = ballot(want);
             if (want) {
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                const int q = (tail + rank) & (kHeQueue - 1);
-                Qa.e[q] = e_in;
-                Qa.NinHe[q] = NinHe;
-                Qa.cp[q] = cp;
-                Qa.mr[q] = ((uint32_t)m << 16) | (uint32_t)r2;
+                const int k = (head + pend + rank_in(mask)) & (kHeQueue - 1);
+                lds<double>(W.e + 8 * k) = e_in;
+                lds<double>(W.NinHe + 8 * k) = NinHe;
+                lds<uint32_t>(W.cp + 4 * k) = cell;
+                lds<uint32_t>(W.mr + 4 * k) = ((uint32_t)m << 16) | (uint32_t)r2c;
             }
-            tail += __popcll(mask);
-            if (tail - head >= 64) {
+            pend += __popcll(mask);
+            if (pend >= 64) {
                 wave_sync();
-                he_rate(A, Qa, (head + lane) & (kHeQueue - 1), coef, sq, X.nHI, nHe, X.inv_s0, gH, gHe);
-                head += 64;
+                he_rate<FINE>(A, W, (head + lane) & (kHeQueue - 1), coef, X.nHI, nHe, X.inv_s0, gH, gHe);
+                head = (head + 64) & (kHeQueue - 1);
+                pend -= 64;
             }
             wave_sync();
         }
+        if (TEAM) __syncthreads();
     }
-    if (tail > head) {
-        wave_sync();
-        if (lane < tail - head) he_rate(A, Qa, (head + lane) & (kHeQueue - 1), coef, sq, X.nHI, nHe, X.inv_s0, gH, gHe);
-        wave_sync();
-    }
+    wave_sync();
+    if (lane < pend) he_rate<FINE>(A, W, (head + lane) & (kHeQueue - 1), coef, X.nHI, nHe, X.inv_s0, gH, gHe);
+    wave_sync();
 }
 
+template <bool FINE>
 __global__ __launch_bounds__(1024) void fwd_layer_he(HeArgs A)
 {
-    extern __shared__ __align__(16) char smem[];
     constexpr int TYPE = 3, npieces = 24;
-    if (A.plain_src < 0 && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources
-    double *sq = (double *)smem;
-    for (int k = threadIdx.x; k < A.sq_n; k += blockDim.x) sq[k] = sqrt((double)k);
+    const bool direct = A.items > 0;
+    if (!direct && A.seg[TYPE + 1] == A.seg[TYPE]) return;   // no sources
+    for (int k = threadIdx.x; k < A.sq_n; k += blockDim.x) lds<double>(8 * k) = sqrt((double)k);
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int waves = blockDim.x >> 6;
-    char *region = smem + (A.sq_n ? layer_sqrt_bytes(A.sq_n - 1) : 0) + (size_t)wave * A.region_bytes;
-    HeQueue Qa;
-    Qa.e = (double *)region;
-    Qa.NinHe = Qa.e + kHeQueue;
-    Qa.cp = (uint32_t *)(Qa.NinHe + kHeQueue);
-    Qa.mr = Qa.cp + kHeQueue;
-    const size_t PP = (size_t)(A.lay_S + 1) * (A.lay_S + 1);
-    double *lay = (double *)(Qa.mr + kHeQueue);   // kHeQueue is even: aligned
-    double *layHe = lay + PP;
-    Geo *geo = (Geo *)(layHe + PP);
-    uint32_t *iu = (uint32_t *)(geo + A.lay_S);
-    uint32_t *iv = iu + A.lay_S;
-    if (A.plain_src >= 0) {
-        const int item = blockIdx.x * waves + wave;
-        if (item < npieces) sweep_layer_piece_he(A, sq, lay, layHe, geo, iu, iv, Qa, A.plain_src, item, lane);
-        return;
-    }
-    const int base = A.seg[TYPE];
-    const int nitems = (A.seg[TYPE + 1] - base) * npieces;
+    HeLds W;
+    W.S = A.lay_S;
+    W.sq_n = A.sq_n;
+    W.e = (A.sq_n ? (int)layer_sqrt_bytes(A.sq_n - 1) : 0) + wave * A.region_bytes;
+    W.NinHe = W.e + 8 * kHeQueue;
+    W.cp = W.NinHe + 8 * kHeQueue;
+    W.mr = W.cp + 4 * kHeQueue;
+    W.lay = W.e + he_queue_bytes();
+    W.layHe = W.lay + 8 * (W.S + 1) * (W.S + 1);
+    W.geo = W.layHe + 8 * (W.S + 1) * (W.S + 1);
+    const int base = direct ? 0 : A.seg[TYPE];
+    const int nitems = direct ? A.items : (A.seg[TYPE + 1] - base) * npieces;
     const int home = (int)(blockIdx.x % kXcds);
     int chunk = home;
     for (;;) {
-        const int item = next_item(A.counter, nitems, home, chunk, lane);
+        const int item = direct ? (int)blockIdx.x * waves + wave : next_item(A.counter, nitems, home, chunk, lane);
         if (item >= nitems) break;
-        const int src = A.order[base + item / npieces];
-        sweep_layer_piece_he(A, sq, lay, layHe, geo, iu, iv, Qa, src, item % npieces, lane);
+        const int src = direct ? A.src0 + item / npieces : uniform(A.order[base + item / npieces]);
+        sweep_layer_piece_he<FINE, false>(A, W, Team{0, 1}, src, item % npieces, lane);
+        if (direct) break;
     }
 }
 
+// Bytes of a team's buffers and tables (the queues follow).
+__host__ __device__ constexpr size_t he_team_shared_bytes(int S)
+{
+    return (2 * (2 * (size_t)(S + 1) * (S + 1) * sizeof(double) + (size_t)S * sizeof(GeoRow)) + 15) & ~(size_t)15;
+}
+
+// One work-group per pyramid, its waves a team (see fwd_team).
+template <bool FINE>
+__global__ __launch_bounds__(1024) void fwd_team_he(HeArgs A)
+{
+    const Team team{uniform((int)threadIdx.x >> 6), (int)blockDim.x >> 6};
+    HeLds W;
+    W.S = A.lay_S;
+    W.sq_n = 0;
+    W.lay = 0;
+    W.layHe = 8 * (W.S + 1) * (W.S + 1);
+    W.geo = 4 * 8 * (W.S + 1) * (W.S + 1);
+    W.e = (int)he_team_shared_bytes(W.S) + team.w * he_queue_bytes();
+    W.NinHe = W.e + 8 * kHeQueue;
+    W.cp = W.NinHe + 8 * kHeQueue;
+    W.mr = W.cp + 4 * kHeQueue;
+    const int item = blockIdx.x;
+    sweep_layer_piece_he<FINE, true>(A, W, team, A.src0 + item / 24, item % 24, threadIdx.x & 63);
+}
+
+size_t he_team_bytes(int S, int T) { return he_team_shared_bytes(S) + (size_t)T * he_queue_bytes(); }
+
 size_t he_region_bytes(int S)
 {
-    const size_t b = (size_t)kHeQueue * (2 * sizeof(double) + 2 * sizeof(uint32_t)) +
-                     2 * (size_t)(S + 1) * (S + 1) * sizeof(double) + (size_t)S * sizeof(Geo) +
-                     2 * (size_t)S * sizeof(uint32_t);
+    const size_t b = (size_t)he_queue_bytes() + 2 * (size_t)(S + 1) * (S + 1) * sizeof(double) +
+                     (size_t)S * sizeof(GeoRow);
     return (b + 15) & ~(size_t)15;
 }
 
 hipError_t he_configure(size_t max_lds)
 {
-    (void)hipFuncSetAttribute((const void *)fwd_layer_he, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)fwd_layer_he<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)max_lds - 64);
+    for (const void *f : {(const void *)fwd_team_he<false>, (const void *)fwd_team_he<true>})
+        (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds - 64);
+    (void)hipFuncSetAttribute((const void *)fwd_layer_he<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)max_lds - 64);
     (void)hipGetLastError();
     return hipSuccess;
@@ -281,10 +344,13 @@ hipError_t he_configure(size_t max_lds)
 
 hipError_t he_occupancy(int waves, size_t lds, int *blocks_per_cu)
 {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void *)fwd_layer_he, waves * 64, lds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void *)fwd_layer_he<true>, waves * 64, lds);
 }
 
-hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int waves, int grid, int plain_src)
+// n_direct > 0: the pyramids of that many sources from src0 on (by `team` waves
+// each if that is more than 1), else all sources of the call from the counters.
+hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int waves, int grid, int src0, int n_direct,
+                               int team)
 {
     HeArgs A;
     A.N = H.N;
@@ -317,7 +383,8 @@ hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int wav
     A.seg = H.ctl + kCtlSeg;
     A.counter = H.ctl + kCtlCounter + kXcds * kCounterPad * 3;
     A.err = H.err;
-    A.plain_src = plain_src;
+    A.src0 = src0;
+    A.items = 24 * n_direct;
     A.lc = make_layer_const(H.sigma0, H.alpha, H.tau_w, 1.0);   // (every band has its own tau_hi)
     A.lay_S = S;
     A.region_bytes = (int)he_region_bytes(S);
@@ -326,9 +393,15 @@ hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int wav
     A.sq_n = sqb ? Rsq + 1 : 0;
     A.coef_unit = 1.0 / (4.0 * M_PI * H.alpha * H.alpha);
     const size_t lds = sqb + (size_t)waves * A.region_bytes;
-    if (plain_src >= 0) grid = (24 + waves - 1) / waves;
-    hipLaunchKernelGGL(fwd_layer_he, dim3(grid), dim3(64 * waves), lds, st, A);
-    return hipGetLastError();
+    bool fine = true;
+    for (int b = 0; b < H.nb; ++b) fine = fine && H.tp[b].fine;
+    void *args[] = {&A};
+    if (team > 1)
+        return hipLaunchKernel(fine ? (const void *)fwd_team_he<true> : (const void *)fwd_team_he<false>, dim3(A.items),
+                               dim3(64 * team), args, he_team_bytes(S, team), st);
+    if (n_direct > 0) grid = (A.items + waves - 1) / waves;
+    return hipLaunchKernel(fine ? (const void *)fwd_layer_he<true> : (const void *)fwd_layer_he<false>, dim3(grid),
+                           dim3(64 * waves), args, lds, st);
 }
 
 }  // namespace asora

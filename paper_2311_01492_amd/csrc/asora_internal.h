@@ -73,10 +73,18 @@ hipError_t launch_bucketing(hipStream_t st, const float *R, const int32_t *ijk, 
 struct FieldBufs {
     double *nHI, *nHI_T, *gacc, *gacc_T, *hacc, *hacc_T, *coldens;
 };
-hipError_t launch_layer_prologue(hipStream_t st, const float *nH, const float *xHI, const FieldBufs &B, int *ctl,
-                                 int nctl, int N);
-hipError_t launch_transpose_finalize(hipStream_t st, const double *gacc, const double *gacc_T,
-                                     float *gamma, int N, int accumulate);
+// One or two absorbers' densities and neutral fractions (n[1] NULL: one).
+struct FieldPair {
+    const float *n[2], *x[2];
+    FieldBufs b[2];
+};
+hipError_t launch_layer_prologue(hipStream_t st, const FieldPair &F, int *ctl, int nctl, int N);
+// One or two accumulators in both layouts and their outputs (out[1] NULL: one).
+struct FinalPair {
+    const double *acc[2], *acc_T[2];
+    float *out[2];
+};
+hipError_t launch_transpose_finalize(hipStream_t st, const FinalPair &F, int N, int accumulate);
 hipError_t launch_zero(hipStream_t st, double *p, long n, int n_cu);
 size_t layer_region_bytes(int S, bool keep);
 size_t team_bytes(int S, bool keep, int T);
@@ -199,7 +207,9 @@ struct HeLaunch {
 size_t he_region_bytes(int S);
 hipError_t he_configure(size_t max_lds);
 hipError_t he_occupancy(int waves, size_t lds, int *blocks_per_cu);
-hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int waves, int grid, int plain_src);
+hipError_t launch_fwd_layer_he(hipStream_t st, const HeLaunch &H, int S, int waves, int grid, int src0, int n_direct,
+                               int team);
+size_t he_team_bytes(int S, int T);
 
 // host table builders (asora_tables.cpp)
 int table_blackbody(double T_bb, double index, int n, double lg_lo, double lg_hi, double *P,
