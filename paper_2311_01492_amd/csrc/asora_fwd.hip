@@ -424,18 +424,21 @@ __device__ __forceinline__ void layer_rate_batch(const FwdArgs &A, const LayerQu
         }
         r2 &= kQueueT - 1;
     }
+    // (the heating is evaluated before the first atomic: a table's nodes that
+    // are loaded after it arrive after it)
+    float nh = 0.f;
+    if (HEAT) nh = EXTRA ? neg_divdiff(A.tab_h, heat_params(A), ta, dt) : neg_divdiff_fine(A.tab_h, heat_params(A), ta, dt);
+    double G;
     if (!KEEP) {
         const float nd = EXTRA ? neg_divdiff(A.tab, A.tp, ta, dt) : neg_divdiff_fine(A.tab, A.tp, ta, dt);
-        if (nd > 0.f) {
-            const double G = coef * (double)(nd * rcp_approx((float)r2));
-            unsafeAtomicAdd(&acc[cp], G);
-        }
+        G = coef * (double)(nd * rcp_approx((float)r2));
     } else {
         const TabParams tp = reload_arg<TabParams>(offsetof(FwdArgs, tp));
-        const double G = coef * rcp_f64((double)r2) * neg_divdiff64<!EXTRA>(NodeArray{A.n64}, tp, ta, dt);
-        if (G > 0.0) unsafeAtomicAdd(&acc[cp], G);
+        G = coef * rcp_f64((double)r2) * neg_divdiff64<!EXTRA>(NodeArray{A.n64}, tp, ta, dt);
     }
-    if (HEAT) add_heating(A, hacc, cp, ta, dt, r2, coef);
+    if (HEAT) asm volatile("" : "+v"(nh), "+v"(G));
+    if (G > 0.0) unsafeAtomicAdd(&acc[cp], G);
+    if (HEAT && nh > 0.f) unsafeAtomicAdd(&hacc[cp], coef * (double)(nh * rcp_approx((float)r2)));
 }
 
 // EXTRA: with the entry-column output, the early exit or a coarse table;
