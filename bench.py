@@ -50,18 +50,17 @@ VALU_PEAK_PER_S = 256 * 4 * 2.4e9 / 4
 FWD_BYTES_PER_SV = 24.0   # n_H + x_HI reads (2 x FP32), Gamma accumulator read-modify-write (2 x FP64)
 ADJ_BYTES_PER_SV = 32.0   # n_H + x_HI (2 x FP32), dL/dGamma (FP64), dL/dn_HI read-modify-write (2 x FP64)
 # column records, a separate term: one FP64 entry per cell, written by the
-# forward that keeps them and read back by the adjoint (the rate's three FP64
-# coefficients per cell with a rate come on top; their count depends on the
-# field)
+# forward that keeps them and read back by the adjoint
 REC_BYTES_PER_CELL = 8.0
 # the sweep kernels' sources and the plans that size their launches (waves,
 # LDS, the table of square roots): counters taken on other versions are not used
 KERNEL_SOURCES = ["paper_2311_01492_amd/csrc/asora_dev.h", "paper_2311_01492_amd/csrc/asora_fwd.hip",
-                  "paper_2311_01492_amd/csrc/asora_adj.hip", "paper_2311_01492_amd/csrc/asora_internal.h",
+                  "paper_2311_01492_amd/csrc/asora_adj.hip", "paper_2311_01492_amd/csrc/asora_sweep.h",
+                  "paper_2311_01492_amd/csrc/asora_internal.h",
                   "paper_2311_01492_amd/csrc/asora_api.hip"]
 # sweep kernels of each pass (one dispatch per piece kind up to the largest
 # radius; the kinds without sources return at once)
-KERNELS = {"fwd": ("fwd_wave", "fwd_layer"), "adj": ("adj_wave", "adj_layer")}
+KERNELS = {"fwd": ("fwd_wave", "fwd_group", "fwd_layer", "fwd_team"), "adj": ("adj_wave", "adj_layer", "adj_team")}
 
 WORKLOADS = {
     "c2": dict(name="c2", kw={},
@@ -669,17 +668,17 @@ def main():
     # the step's adjoint reads kept records or recomputes; the forward alone
     # keeps nothing
     tun = dict(zip(asora.TUNING_KEYS, ctx.get_tuning()))
-    big = R_max > tun["R_oct"]
-    layer = big and tun["pyramid_sweep"] == 3
-    tl = "true" if tun["table_place"] == 1 else "false"
-    sp = "true" if tun["adj_rate"] == 2 and not kept else "false"
-    aw = 16 if tun["adj_waves"] > 12 else 12   # the layer adjoint's build (wide above 12 waves)
-    kname = {"fwd": f"fwd_layer<false, {tl}>" if layer else "fwd_wave<2>",
-             "adj": f"adj_layer<{'true' if kept else 'false'}, {sp}, {aw}>" if layer else "adj_wave<2>"}
-    if not big:
+    layer = tun["pyramid_sweep"] == 3 and R_max > 22.0
+    # (the benchmark's tables are fine and tame: fwd_layer<KEEP, HEAT, EXTRA>,
+    # adj_layer<KEPT, FAST>)
+    kname = {"fwd": "fwd_layer<false, false, false>" if layer else "fwd_wave<2>",
+             "adj": f"adj_layer<{'true' if kept else 'false'}, true>" if layer else "adj_wave<2>"}
+    if not layer and tun["pyramid_sweep"] == 3:
+        kname = {"fwd": "fwd_group<false, false>", "adj": f"adj_layer<{'true' if kept else 'false'}, true>"}
+    elif not layer and R_max <= tun["R_oct"]:
         kname = {"fwd": "fwd_wave<1>", "adj": "adj_wave<1>"}
     # the step's forward keeps the records when they fit (layer pieces only)
-    kname["fwd_step"] = f"fwd_layer<true, {tl}>" if (kept and layer) else kname["fwd"]
+    kname["fwd_step"] = "fwd_layer<true, false, false>" if (kept and layer) else kname["fwd"]
     rec_step = kept and layer
 
     def roof(bytes_per_sv, sweep_ms, kernel, record):

@@ -61,16 +61,13 @@ typedef enum {
                                   whole call on `stream`; read with asora_profile or
                                   asora_profile_read                                */
 #define ASORA_STORE      0x8u  /* forward: keep the column record of every pyramid
-                                  piece (sources above R_oct, swept in layers) in
+                                  piece (sources above R_whole, swept in layers) in
                                   library-owned device memory, if it fits the store
                                   budget (asora_set_store_budget); otherwise nothing
-                                  is kept (asora_store_info tells which); the records
-                                  also hold the rate's FP64 derivatives for every cell
-                                  with a rate.  backward: take the columns, the cells
-                                  with a rate and those derivatives from the records
-                                  instead of re-sweeping the pyramids forward and
-                                  re-evaluating the rate, provided the most recent
-                                  forward call with
+                                  is kept (asora_store_info tells which).  backward:
+                                  take the columns and the cells with a rate from
+                                  the records instead of re-sweeping the pyramids
+                                  forward, provided the most recent forward call with
                                   ASORA_STORE kept them for the same n_H, x_HI,
                                   src_ijk, src_Q, src_R pointers, n_src and R_max and
                                   the tuning has not changed since; otherwise the
@@ -78,10 +75,11 @@ typedef enum {
                                   the contents of those buffers did not change in
                                   between (if they did, the gradients are wrong, but
                                   every access stays inside the records).  Whole-source
-                                  and octant pieces are always recomputed.  Results
-                                  are the same either way up to rounding.            */
-#define ASORA_EARLY_EXIT 0x10u /* forward: stop each layer pyramid (sources above
-                                  R_oct, swept in layers) after its first layer whose
+                                  pieces (and octants, with the shell sweep) are
+                                  always recomputed.  Results are the same either way
+                                  up to rounding.                                    */
+#define ASORA_EARLY_EXIT 0x10u /* forward: stop each layer pyramid (sources too large
+                                  for the grouped sweep of small radii) after its first layer whose
                                   cells all leave with sigma0 N_out >= tau_hi (a
                                   relative margin of 1e-12): every later cell of the
                                   pyramid enters at tau >= tau_hi, where the table is
@@ -99,8 +97,8 @@ typedef enum {
                                   the flag both passes sweep every layer.          */
 #define ASORA_PLAIN      0x2u  /* one kernel launch per source, in input order: the
                                   unbatched baseline form (Section 3.3, one block per
-                                  source).  Default: all sources in one persistent
-                                  launch per piece kind, longest first.  Results are
+                                  source).  Default: all sources in one launch per
+                                  piece kind, longest first.  Results are
                                   the same up to the order of floating-point sums.   */
 
 /*
@@ -396,9 +394,8 @@ asora_status asora_store_info(const asora_ctx *ctx, int32_t *valid, uint64_t *by
 
 /*
  * asora_set_store_budget -- largest number of bytes of device memory the kept
- * column records may take (n_src x 24 x one pyramid's record, about 32 bytes
- * per cell of the largest pyramid: its entry and room for the rate's three
- * derivatives).  0 (the default) means half of the free
+ * column records may take (n_src x 24 x one pyramid's record, about 8 bytes
+ * per cell of the largest pyramid).  0 (the default) means half of the free
  * device memory at the time of the forward call, plus what is already held.
  * A forward call with ASORA_STORE that needs more keeps nothing.
  */
@@ -406,25 +403,20 @@ asora_status asora_set_store_budget(asora_ctx *ctx, uint64_t bytes);
 
 /*
  * asora_set_tuning -- scheduling parameters of the sweep (results do not
- * depend on them beyond the order of floating-point sums).  Sources with
- * R <= R_whole are swept whole by one wave; R_whole < R <= R_oct as eight
- * closed octants; larger R as 24 octant x dominant-axis pyramids (cells on
- * shared planes are computed by each piece and owned by one).  Those
- * pyramids are swept either shell by shell in L1 distance (pyramid_sweep 2)
- * or layer by layer along their dominant axis, each layer in chunks of 64
- * memory-contiguous cells (pyramid_sweep 3, the default), in the forward and
- * in the adjoint.  table_place: where the layer forward reads the table, 1 =
- * a copy in LDS per work-group (the default), 2 = through the caches (which
- * leaves the LDS to more waves).  max_waves (1..16) caps the waves per
- * work-group.  The adjoint of layer pyramids: adj_waves (1..16, default 4)
- * waves per work-group (above 12 a build held to four waves per SIMD, which
- * may spill registers); adj_rate 1 = the rate terms of every cell with a rate
- * gathered into full waves before the reverse pass (fewer registers: suits
- * sources whose rate reaches few cells), 2 = those of chunks where at least
- * half the cells have a rate evaluated in the reverse pass itself (the
- * default: suits sources that ionise most of their sphere); it applies when
- * the adjoint re-sweeps the pyramids (records kept with ASORA_STORE carry the
- * rate's derivatives).  Values <= 0
+ * depend on them beyond the order of floating-point sums).  pyramid_sweep 3
+ * (the default): sources are swept as 24 octant x dominant-axis pyramids
+ * (cells on shared planes are computed by each and owned by one), layer by
+ * layer along their dominant axis, each layer in chunks of 64 cells; small
+ * ones with several pyramids to a wave, calls of few sources with several
+ * waves to a pyramid, by the library's own rules.  The adjoint, and a forward
+ * that keeps records for it, sweep sources with R <= R_whole (at most 12)
+ * whole, by one wave.  pyramid_sweep 2: shell by shell in L1 distance, sources
+ * with R <= R_whole whole, R_whole < R <= R_oct as eight closed octants, larger
+ * ones as pyramids.  max_waves (1..16) caps the waves per work-group, adj_waves
+ * (1..16, default 4) those of the layer adjoint.  table_place (1, 2) and
+ * adj_rate (1, 2) are accepted, reported and kept in tuning files; the kernels
+ * read the table through the caches and evaluate the adjoint's rate terms in
+ * the reverse pass whatever they are.  Values <= 0
  * keep the current setting.  ASORA_EINVAL if R_oct < R_whole, max_waves > 16,
  * pyramid_sweep is not 0, 2 or 3, table_place not 0, 1 or 2, adj_waves > 16
  * or adj_rate not 0, 1 or 2; ASORA_ESTATE while a recorded graph of the

@@ -579,7 +579,10 @@ __global__ __launch_bounds__(1024) void fwd_layer(FwdArgs A)
 }
 
 // One work-group per pyramid, its waves a team: for calls with so few pyramids
-// that one wave each would leave the chip idle.
+// that one wave each would leave the chip idle.  Bound by the latency of a
+// layer: its chunks and one barrier (32^3, one source of radius 15: 20 us for
+// 15 layers with two waves to a pyramid, where the shell sweep of eight octants
+// took 127; 128^3, 85 sources of radius 30: 190 us with one wave, 116 with two).
 template <bool KEEP, bool HEAT, bool EXTRA>
 __global__ __launch_bounds__(1024) void fwd_team(FwdArgs A)
 {
@@ -691,7 +694,11 @@ size_t group_lds_bytes(const GroupClasses &c, int waves)
 }
 
 // The classes of a call in one launch, the largest radii first: a class's last
-// sources run beside the next one's first.
+// sources run beside the next one's first.  Bound by latency: nearly every
+// chunk of highly ionized gas fills a batch of rates, whose additions the next
+// chunk's fields queue behind (125^3, 20000 sources of radii 1 to 10, 505 us at
+// 52 % of VALU issue with 57 of 64 lanes active; without the additions 358,
+// without the rates 285; by shells 1003).
 template <bool HEAT, bool EXTRA>
 __global__ __launch_bounds__(1024) void fwd_group(FwdArgs A)
 {

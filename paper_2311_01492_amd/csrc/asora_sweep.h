@@ -93,7 +93,10 @@ struct SweepChunk {
 // round past the last chunk has no active lane.
 //
 // The sweep is bound by instruction issue, then by the latency of a chunk's
-// dependent chain.  So the chunks of all layers form one sequence, a chunk's
+// dependent chain (250^3, 40000 sources of radii 5 to 40, forward: 24.9 ms with
+// columns converted to optical depths in every cell and fields loaded where
+// they are used, 17.5 ms in this form; 12.4 ms of it without the rates).  So
+// the chunks of all layers form one sequence, a chunk's
 // field values are fetched one chunk ahead, and lanes without a cell repeat
 // cell (0, 0) instead of being masked off (only the writes are masked).
 template <bool TEAM, class Chunk, class LayerEnd>
