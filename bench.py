@@ -60,7 +60,7 @@ KERNEL_SOURCES = ["paper_2311_01492_amd/csrc/asora_dev.h", "paper_2311_01492_amd
                   "paper_2311_01492_amd/csrc/asora_api.hip"]
 # sweep kernels of each pass (one dispatch per piece kind up to the largest
 # radius; the kinds without sources return at once)
-KERNELS = {"fwd": ("fwd_wave", "fwd_group", "fwd_layer", "fwd_team"), "adj": ("adj_wave", "adj_layer", "adj_team")}
+KERNELS = {"fwd": ("fwd_wave", "fwd_group", "fwd_layer", "fwd_team"), "adj": ("adj_wave", "adj_group", "adj_layer", "adj_team")}
 
 WORKLOADS = {
     "c2": dict(name="c2", kw={},

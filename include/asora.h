@@ -61,7 +61,7 @@ typedef enum {
                                   whole call on `stream`; read with asora_profile or
                                   asora_profile_read                                */
 #define ASORA_STORE      0x8u  /* forward: keep the column record of every pyramid
-                                  piece (sources above R_whole, swept in layers) in
+                                  piece (sources too large for the grouped sweep) in
                                   library-owned device memory, if it fits the store
                                   budget (asora_set_store_budget); otherwise nothing
                                   is kept (asora_store_info tells which).  backward:
@@ -74,10 +74,9 @@ typedef enum {
                                   adjoint recomputes them.  The caller guarantees that
                                   the contents of those buffers did not change in
                                   between (if they did, the gradients are wrong, but
-                                  every access stays inside the records).  Whole-source
-                                  pieces (and octants, with the shell sweep) are
-                                  always recomputed.  Results are the same either way
-                                  up to rounding.                                    */
+                                  every access stays inside the records).  Small sources
+                                  (and the shell sweeps) are always recomputed.
+                                  Results are the same either way up to rounding.    */
 #define ASORA_EARLY_EXIT 0x10u /* forward: stop each layer pyramid (sources too large
                                   for the grouped sweep of small radii) after its first layer whose
                                   cells all leave with sigma0 N_out >= tau_hi (a
@@ -408,15 +407,14 @@ asora_status asora_set_store_budget(asora_ctx *ctx, uint64_t bytes);
  * (cells on shared planes are computed by each and owned by one), layer by
  * layer along their dominant axis, each layer in chunks of 64 cells; small
  * ones with several pyramids to a wave, calls of few sources with several
- * waves to a pyramid, by the library's own rules.  The adjoint, and a forward
- * that keeps records for it, sweep sources with R <= R_whole (at most 12)
- * whole, by one wave.  pyramid_sweep 2: shell by shell in L1 distance, sources
- * with R <= R_whole whole, R_whole < R <= R_oct as eight closed octants, larger
- * ones as pyramids.  max_waves (1..16) caps the waves per work-group, adj_waves
- * (1..16, default 4) those of the layer adjoint.  table_place (1, 2) and
- * adj_rate (1, 2) are accepted, reported and kept in tuning files; the kernels
- * read the table through the caches and evaluate the adjoint's rate terms in
- * the reverse pass whatever they are.  Values <= 0
+ * waves to a pyramid, by the library's own rules.  pyramid_sweep 2: shell by
+ * shell in L1 distance, sources with R <= R_whole whole, R_whole < R <= R_oct as
+ * eight closed octants, larger ones as pyramids.  max_waves (1..16) caps the
+ * waves per work-group, adj_waves (1..16, default 4) those of the layer
+ * adjoint.  table_place (1, 2) and adj_rate (1, 2) are accepted, reported and
+ * kept in tuning files; the kernels read the table through the caches and
+ * evaluate the adjoint's rate terms in the reverse pass whatever they are.
+ * Values <= 0
  * keep the current setting.  ASORA_EINVAL if R_oct < R_whole, max_waves > 16,
  * pyramid_sweep is not 0, 2 or 3, table_place not 0, 1 or 2, adj_waves > 16
  * or adj_rate not 0, 1 or 2; ASORA_ESTATE while a recorded graph of the

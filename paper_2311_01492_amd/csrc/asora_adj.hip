@@ -59,6 +59,9 @@ struct AdjArgs {
     LayerConst lc;
     int sq_n;                // layer pieces: entries of the work-group's LDS table of sqrt(r^2); 0: none
     int items;               // layer pieces, direct: the number of pyramids (0: from the counters)
+    int type;
+    GroupClasses grp;        // group pieces: one class
+    int grp_shared;          // bytes of their work-group tables
 };
 
 template <int TYPE>
@@ -304,6 +307,76 @@ struct AdjLds {
     int *flag;      // TEAM: see adjoint_layer_piece
 };
 
+// The reverse pass of one cell: the adjoint Tin of its exit column and, with gb
+// = dL/dGamma (0: no rate), its rate's terms; what it pushes to its neighbours
+// in layer m - 1 (entries e0 .. e3), its entry column's and its own adjoint and
+// its share of dL/dQ.
+struct AdjCell {
+    double b0, b1, b2, b3;   // pushes
+    double Tin, Tn, q;
+};
+
+template <bool FAST>
+__device__ __forceinline__ void adjoint_cell(const AdjArgs &A, const LayerX &X, const NodeArray &nodes, int m,
+                                             double coef, double ads, int r2, const Geo &gu, const Geo &gv, double e0,
+                                             double e1, double e2, double e3, double gb, double nhi, double Tin,
+                                             AdjCell &C)
+{
+    C.q = 0.0;
+    const double s0 = gu.om * gv.om, s1 = gu.a * gv.om, s2 = gu.om * gv.a, s3 = gu.a * gv.a;
+    // t_in, and the derivatives b_n of t_in by the neighbours' t
+    double t, b0, b1, b2, b3;
+    if (m == 1) {
+        t = X.reading == 0 ? X.half_n * (X.sigma0 * ads) : X.half_tau;
+        b0 = b1 = b2 = b3 = 0.0;
+    } else if (__ballot(!all_thick(e0, e1, e2, e3)) == 0) {
+        // all thick: t_in = 1 / W, W = sum s e; b = s e^2 / W^2
+        b0 = s0 * e0;
+        b1 = s1 * e1;
+        b2 = s2 * e2;
+        b3 = s3 * e3;
+        t = rcp_f64((b0 + b1) + (b2 + b3));
+        const double k = t * t;
+        b0 *= e0 * k;
+        b1 *= e1 * k;
+        b2 *= e2 * k;
+        b3 *= e3 * k;
+    } else {
+        // f = e or 1 / tau_w; b = s f / W, for a thick neighbour times t_in f
+        const double f0 = e0 > 0.0 ? e0 : X.inv_tw, f1 = e1 > 0.0 ? e1 : X.inv_tw;
+        const double f2 = e2 > 0.0 ? e2 : X.inv_tw, f3 = e3 > 0.0 ? e3 : X.inv_tw;
+        b0 = s0 * f0;
+        b1 = s1 * f1;
+        b2 = s2 * f2;
+        b3 = s3 * f3;
+        const double iW = rcp_f64((b0 + b1) + (b2 + b3));
+        t = iW * (s0 * (e0 > 0.0 ? 1.0 : -e0 * X.inv_tw) + s1 * (e1 > 0.0 ? 1.0 : -e1 * X.inv_tw) +
+                  s2 * (e2 > 0.0 ? 1.0 : -e2 * X.inv_tw) + s3 * (e3 > 0.0 ? 1.0 : -e3 * X.inv_tw));
+        b0 *= iW * (e0 > 0.0 ? t * e0 : 1.0);
+        b1 *= iW * (e1 > 0.0 ? t * e1 : 1.0);
+        b2 *= iW * (e2 > 0.0 ? t * e2 : 1.0);
+        b3 *= iW * (e3 > 0.0 ? t * e3 : 1.0);
+    }
+    // N_out = N_in + dN: both receive the exit column's adjoint,
+    // and the rate adds its own parts
+    double Tn = Tin;
+    if (gb != 0.0) {
+        double D, Da, Ddt;
+        const TabParams tp = reload_arg<TabParams>(offsetof(AdjArgs, tp));
+        rate_derivs_nodes<FAST>(nodes, tp, t, nhi * (X.sigma0 * ads), &D, &Da, &Ddt);
+        const double k = -gb * coef * rcp_f64((double)r2);
+        C.q = k * D;
+        Tin += k * Da * X.sigma0;
+        Tn += k * Ddt * X.sigma0;
+    }
+    C.b0 = Tin * b0;
+    C.b1 = Tin * b1;
+    C.b2 = Tin * b2;
+    C.b3 = Tin * b3;
+    C.Tin = Tin;
+    C.Tn = Tn;
+}
+
 // TEAM: the work-group's waves take a layer's chunks in turn, in both passes.
 // In (R) a layer's slots are taken from one buffer and the pushes go to the
 // other; W.flag[3] tells all waves that a layer had a push, in turn (a flag is
@@ -483,62 +556,19 @@ __device__ __forceinline__ void adjoint_layer_piece(const AdjArgs &A, const AdjL
                     gb = gbar[cp];
                     nhi = X.nHI[cp];
                 }
-                const double s0 = gu.om * gv.om, s1 = gu.a * gv.om, s2 = gu.om * gv.a, s3 = gu.a * gv.a;
-                // t_in, and the derivatives b_n of t_in by the neighbours' t
-                double t, b0, b1, b2, b3;
-                if (m == 1) {
-                    t = X.reading == 0 ? X.half_n * (X.sigma0 * ads) : X.half_tau;
-                    b0 = b1 = b2 = b3 = 0.0;
-                } else if (__ballot(!all_thick(e0, e1, e2, e3)) == 0) {
-                    // all thick: t_in = 1 / W, W = sum s e; b = s e^2 / W^2
-                    b0 = s0 * e0;
-                    b1 = s1 * e1;
-                    b2 = s2 * e2;
-                    b3 = s3 * e3;
-                    t = rcp_f64((b0 + b1) + (b2 + b3));
-                    const double k = t * t;
-                    b0 *= e0 * k;
-                    b1 *= e1 * k;
-                    b2 *= e2 * k;
-                    b3 *= e3 * k;
-                } else {
-                    // f = e or 1 / tau_w; b = s f / W, for a thick neighbour times t_in f
-                    const double f0 = e0 > 0.0 ? e0 : X.inv_tw, f1 = e1 > 0.0 ? e1 : X.inv_tw;
-                    const double f2 = e2 > 0.0 ? e2 : X.inv_tw, f3 = e3 > 0.0 ? e3 : X.inv_tw;
-                    b0 = s0 * f0;
-                    b1 = s1 * f1;
-                    b2 = s2 * f2;
-                    b3 = s3 * f3;
-                    const double iW = rcp_f64((b0 + b1) + (b2 + b3));
-                    t = iW * (s0 * (e0 > 0.0 ? 1.0 : -e0 * X.inv_tw) + s1 * (e1 > 0.0 ? 1.0 : -e1 * X.inv_tw) +
-                              s2 * (e2 > 0.0 ? 1.0 : -e2 * X.inv_tw) + s3 * (e3 > 0.0 ? 1.0 : -e3 * X.inv_tw));
-                    b0 *= iW * (e0 > 0.0 ? t * e0 : 1.0);
-                    b1 *= iW * (e1 > 0.0 ? t * e1 : 1.0);
-                    b2 *= iW * (e2 > 0.0 ? t * e2 : 1.0);
-                    b3 *= iW * (e3 > 0.0 ? t * e3 : 1.0);
-                }
-                // N_out = N_in + dN: both receive the exit column's adjoint,
-                // and the rate adds its own parts
-                double Tn = Tin;
-                if (gb != 0.0) {
-                    double D, Da, Ddt;
-                    const TabParams tp = reload_arg<TabParams>(offsetof(AdjArgs, tp));
-                    rate_derivs_nodes<FAST>(nodes, tp, t, nhi * (X.sigma0 * ads), &D, &Da, &Ddt);
-                    const double k = -gb * coef * rcp_f64((double)r2);
-                    qb += k * D;
-                    Tin += k * Da * X.sigma0;
-                    Tn += k * Ddt * X.sigma0;
-                }
+                AdjCell C;
+                adjoint_cell<FAST>(A, X, nodes, m, coef, ads, r2, gu, gv, e0, e1, e2, e3, gb, nhi, Tin, C);
+                qb += C.q;
                 if (m >= 2) {
                     double *ra = give + mul24(ua, S), *rb = give + mul24(ub, S);
-                    atomicAdd(&ra[va], Tin * b0);
-                    atomicAdd(&rb[va], Tin * b1);
-                    atomicAdd(&ra[vb], Tin * b2);
-                    atomicAdd(&rb[vb], Tin * b3);
+                    atomicAdd(&ra[va], C.b0);
+                    atomicAdd(&rb[va], C.b1);
+                    atomicAdd(&ra[vb], C.b2);
+                    atomicAdd(&rb[vb], C.b3);
                 } else {
-                    nb_src += Tin * (X.reading == 0 ? ads * 0.5 : X.alpha * 0.5);
+                    nb_src += C.Tin * (X.reading == 0 ? ads * 0.5 : X.alpha * 0.5);
                 }
-                const double nb = Tn * ads;
+                const double nb = C.Tn * ads;
                 if (nb != 0.0) unsafeAtomicAdd(&nbar[cp], nb);
             }
             wave_sync();
@@ -631,6 +661,221 @@ __global__ __launch_bounds__(64 * kAdjLayerWaves) void adj_team(AdjArgs A)
     char *scratch = (char *)(A.store + (size_t)blockIdx.x * A.store_stride);
     const int item = blockIdx.x;
     adjoint_layer_piece<KEPT, FAST, true>(A, W, team, scratch, item / 24, item % 24, threadIdx.x & 63);
+}
+
+// ---- group pieces --------------------------------------------------------
+// Several pyramids of a small source by one wave, as sweep_group: both passes
+// of adjoint_layer_piece over layers whose rectangles follow each other, slots
+// and record entries numbered alike.  Never with kept records (the forward
+// keeps none of these sources).
+template <bool FAST>
+__device__ __forceinline__ void adjoint_group_piece(const AdjArgs &A, const GroupLds &W, int qT, int quv, char *scratch,
+                                                    int src, int part, int lane)
+{
+    const int N = A.N;
+    const int si = uniform(A.ijk[3 * src]), sj = uniform(A.ijk[3 * src + 1]), sk = uniform(A.ijk[3 * src + 2]);
+    const float R = A.R ? A.R[src] : A.R_cap;
+    if (!(R >= 0.f && R <= A.R_cap) || si < 0 || si >= N || sj < 0 || sj >= N || sk < 0 ||
+        sk >= N) {
+        if (lane == 0) atomicOr(A.err, 1);
+        return;
+    }
+    const double Q = uniform(A.Q[src]);
+    const int Rsq = uniform((int)floor((double)R * (double)R));
+    const uint32_t cs = ((uint32_t)si * (uint32_t)N + (uint32_t)sj) * (uint32_t)N + (uint32_t)sk;
+    const double n_s = uniform(A.nHI[cs]);
+    LayerX X;
+    X.N = N;
+    X.reading = A.reading;
+    X.tau_w = A.tau_w;
+    X.sigma0 = A.sigma0;
+    X.alpha = A.alpha;
+    layer_x_source(X, A.lc, n_s);
+    X.nHI = A.nHI;
+    const double coef = uniform(Q * A.coef_unit);
+    const LayerRecord rec = layer_record_at(scratch, A.rec_cap, 0);
+    const int Mx = uniform(isqrt_floor(Rsq));   // within the box: see radii_of
+    const int P = W.S + 1, P8 = 8 * P, PP8 = P8 * P;
+    const NodeArray nodes{A.n64};
+    double nb_src = 0.0, qb = 0.0;
+    if (Mx >= 1) {
+        group_tables(W, part * W.G, si, sj, sk, N, lane);
+        // ---- (F)
+        long off = 0, choff = 0;
+        sweep_group(X, A.nHI_T, W, Rsq, Mx, A.tp.tau_hi, A.lc.inv_hi, lane, [&](const GroupChunk &k) {
+            if (k.in) rec.h[off + k.c * 64 + lane] = k.h;
+            const uint64_t mask = ballot(k.in & k.below & group_owned(k.flags, k.m, k.u, k.v));
+            if (lane == 0) rec.lit[choff + k.c] = mask;
+            if (k.c == 0) {
+                off += k.cells;
+                choff += (k.cells + 63) / 64;
+            }
+        });
+        wave_sync_global();
+        for (int k = lane; k < W.G * P * P; k += 64) lds<double>(W.lay + 8 * k) = 0.0;   // the adjoint slots
+        wave_sync_global();
+        // ---- (R)
+        bool pushed = false;   // a cell of layer m + 1 pushed to layer m's slots
+        for (int m = Mx; m >= 1; --m) {
+            const LayerRect r = layer_rect_uniform(Mx, Mx, Rsq, m);
+            const int cells = W.G * r.total, nch = (cells + 63) / 64;   // at most 16 chunks (kGroup)
+            off -= cells;
+            choff -= nch;
+            const uint64_t masks = load_masks(rec, choff, 0, nch, lane);
+            if (!pushed && __ballot(masks != 0) == 0) continue;   // no rate depends on this layer
+            const LayerRect rp = layer_rect_uniform(Mx, Mx, Rsq, m >= 2 ? m - 1 : 1);
+            const double *Hprev = rec.h + (m >= 2 ? off - W.G * rp.total : 0);
+            const float inv_t = rcp_approx((float)r.total), inv_w = rcp_approx((float)r.wv);
+            const double am = X.alpha * rcp_f64((double)m);
+            const int m2 = m * m, geo = W.geo + (int)sizeof(Geo) * W.geo_S * (m - 1);
+            int qh = 0, qn = 0;   // the queue: qn cells from ring position qh
+            bool any = false;
+            // chunks 0 .. nch - 1, then a last round for the cells left in the queue
+            for (int c = 0; c <= nch; ++c) {
+                if (c < nch) {
+                    const int g = c * 64 + lane;
+                    const int pl = (int)(((float)g + 0.5f) * inv_t), l = g - mul24(pl, r.total);
+                    const int u = (int)(((float)l + 0.5f) * inv_w), v = l - mul24(u, r.wv);
+                    const bool act = (g < cells) & (mul24(u, u) + mul24(v, v) <= r.rem);
+                    const bool lit = act && ((mask_of_chunk(masks, c) >> lane) & 1);
+                    double Tin = 0.0;
+                    if (pushed && act) {
+                        const int slot = W.lay + mul24(pl, PP8) + mul24(u, P8) + 8 * v;
+                        Tin = lds<double>(slot);
+                        lds<double>(slot) = 0.0;
+                    }
+                    const uint64_t need = __ballot(lit || Tin != 0.0);
+                    if (need == 0) continue;
+                    any = true;
+                    wave_sync();
+                    if (lit || Tin != 0.0) {
+                        const int k = (qh + qn + rank_in(need)) & (kAdjQueue - 1);
+                        lds<double>(qT + 8 * k) = Tin;
+                        lds<int>(quv + 4 * k) = u | (v << 8) | (pl << 16) | (lit ? 1 << 24 : 0);
+                    }
+                    qn += __popcll(need);
+                    wave_sync();
+                    if (qn < 64) continue;
+                }
+                const int cnt = qn < 64 ? qn : 64;
+                const int at = (qh + lane) & (kAdjQueue - 1);
+                qh = (qh + cnt) & (kAdjQueue - 1);
+                qn -= cnt;
+                if (lane < cnt) {
+                    const int uv = lds<int>(quv + 4 * at);
+                    double Tin = lds<double>(qT + 8 * at);
+                    const int u = uv & 0xff, v = (uv >> 8) & 0xff, pl = (uv >> 16) & 0xff;
+                    const bool lit = (uv >> 24) != 0;
+                    const GroupRow row = lds<GroupRow>(W.row + (int)sizeof(GroupRow) * pl);
+                    const bool tr = (row.flags & kGroupT) != 0;
+                    const uint32_t cp = lds<uint32_t>(row.d + 4 * m) + lds<uint32_t>(row.u + 4 * u) +
+                                        lds<uint32_t>(row.v + 4 * v);
+                    const int r2 = m2 + mul24(u, u) + mul24(v, v);
+                    const double ads = lds<double>(W.sq + 8 * r2) * am;   // alpha ds
+                    const Geo gu = lds<Geo>(geo + (int)sizeof(Geo) * u), gv = lds<Geo>(geo + (int)sizeof(Geo) * v);
+                    const int ua = u < m ? u : m - 1, ub = u > 0 ? u - 1 : 0;
+                    const int va = v < m ? v : m - 1, vb = v > 0 ? v - 1 : 0;
+                    double e0 = 0.0, e1 = 0.0, e2 = 0.0, e3 = 0.0;
+                    if (m >= 2) {
+                        const double *base = Hprev + mul24(pl, rp.total);
+                        const double *ra = base + mul24(ua, rp.wv), *rb = base + mul24(ub, rp.wv);
+                        e0 = ra[va];
+                        e1 = rb[va];
+                        e2 = ra[vb];
+                        e3 = rb[vb];
+                    }
+                    double gb = 0.0, nhi = 0.0;
+                    if (lit) {
+                        gb = (tr ? A.gbar_T : A.gbar)[cp];
+                        nhi = (tr ? A.nHI_T : A.nHI)[cp];
+                    }
+                    AdjCell C;
+                    adjoint_cell<FAST>(A, X, nodes, m, coef, ads, r2, gu, gv, e0, e1, e2, e3, gb, nhi, Tin, C);
+                    qb += C.q;
+                    if (m >= 2) {
+                        const int base = W.lay + mul24(pl, PP8);
+                        const int ra = base + mul24(ua, P8), rb = base + mul24(ub, P8);
+                        atomicAdd(&lds<double>(ra + 8 * va), C.b0);
+                        atomicAdd(&lds<double>(rb + 8 * va), C.b1);
+                        atomicAdd(&lds<double>(ra + 8 * vb), C.b2);
+                        atomicAdd(&lds<double>(rb + 8 * vb), C.b3);
+                    } else {
+                        nb_src += C.Tin * (X.reading == 0 ? ads * 0.5 : X.alpha * 0.5);
+                    }
+                    const double nb = C.Tn * ads;
+                    if (nb != 0.0) unsafeAtomicAdd(&(tr ? A.nbar_T : A.nbar)[cp], nb);
+                }
+                wave_sync();
+            }
+            pushed = any;
+        }
+    }
+    if (part == 0 && lane == 0) {   // the source cell, once per source
+        double nb, q1;
+        source_cell_adjoint_nodes<FAST>(nodes, A.tp, A.sigma0, A.alpha, Q, n_s, A.gbar[cs], &nb, &q1);
+        nb_src += nb;
+        qb += q1;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        nb_src += __shfl_xor(nb_src, o, 64);
+        qb += __shfl_xor(qb, o, 64);
+    }
+    if (lane == 0) {
+        if (nb_src != 0.0) unsafeAtomicAdd(&A.nbar[cs], nb_src);
+        if (qb != 0.0) unsafeAtomicAdd(&A.qbar[src], qb / Q);
+    }
+}
+
+// Bytes of the work-group's tables and of a wave's region (one class).
+static size_t adj_group_shared_bytes(const GroupClasses &c)
+{
+    return ((size_t)(c.Rsq[0] + 1) * sizeof(double) + (size_t)isqrt_floor(c.Rsq[0]) * c.S[0] * sizeof(Geo) + 15) & ~(size_t)15;
+}
+static size_t adj_group_wave_bytes(const GroupClasses &c)
+{
+    return ((size_t)c.G[0] * ((size_t)(c.S[0] + 1) * (c.S[0] + 1) * sizeof(double) + sizeof(GroupRow)) +
+            12 * (size_t)(isqrt_floor(c.Rsq[0]) + 1) * sizeof(uint32_t) + kAdjQueue * (sizeof(double) + sizeof(int)) + 31) &
+           ~(size_t)15;
+}
+size_t adj_group_lds_bytes(const GroupClasses &c, int waves)
+{
+    return adj_group_shared_bytes(c) + (size_t)waves * adj_group_wave_bytes(c);
+}
+
+template <bool FAST>
+__global__ __launch_bounds__(1024) void adj_group(AdjArgs A)
+{
+    if (A.seg[A.type + 1] == A.seg[A.type]) return;   // no sources of this kind
+    const int Rsq = A.grp.Rsq[0], M = isqrt_floor(Rsq);
+    GroupLds W;
+    W.S = W.geo_S = A.grp.S[0];
+    W.K = M + 1;
+    W.G = A.grp.G[0];
+    W.sq = 0;
+    W.geo = 8 * (Rsq + 1);
+    for (int k = threadIdx.x; k <= Rsq; k += blockDim.x) lds<double>(8 * k) = sqrt((double)k);
+    for (int k = threadIdx.x; k < M * W.S; k += blockDim.x) {
+        const int m = k / W.S + 1;
+        lds<Geo>(W.geo + (int)sizeof(Geo) * k) = layer_geo(m, rcp_f64((double)m), k % W.S);
+    }
+    __syncthreads();
+    const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int waves = blockDim.x >> 6;
+    const int qT = A.grp_shared + wave * A.region_bytes, quv = qT + 8 * kAdjQueue;
+    W.lay = quv + 4 * kAdjQueue;
+    W.row = (W.lay + W.G * 8 * (W.S + 1) * (W.S + 1) + 15) & ~15;
+    W.term = W.row + W.G * (int)sizeof(GroupRow);
+    char *scratch = (char *)(A.store + (size_t)(blockIdx.x * waves + wave) * A.store_stride);
+    const int npieces = 24 / W.G, base = A.seg[A.type], nitems = (A.seg[A.type + 1] - base) * npieces;
+    const int home = (int)(blockIdx.x % kXcds);
+    int chunk = home;
+    for (;;) {
+        const int item = next_item(A.counter, nitems, home, chunk, lane);
+        if (item >= nitems) break;
+        const int src = uniform(A.order[base + item / npieces]);
+        adjoint_group_piece<FAST>(A, W, qT, quv, scratch, src, item % npieces, lane);
+    }
 }
 
 // What an adjoint with layer pieces starts from, in one pass over the fields.
@@ -764,6 +1009,8 @@ hipError_t adj_configure(size_t max_lds)
     const int dyn = (int)max_lds - 64;
     for (int t = 0; t < 3; ++t)
         (void)hipFuncSetAttribute(adj_fn(t), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+    for (int f = 0; f < 2; ++f)
+        (void)hipFuncSetAttribute(f ? (const void *)adj_group<true> : (const void *)adj_group<false>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     for (int f = 0; f < 8; ++f)
         (void)hipFuncSetAttribute(adj_layer_fn(f & 2, f & 1, f & 4), hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     (void)hipGetLastError();
@@ -827,6 +1074,9 @@ static AdjArgs make_adj_args(const AdjLaunch &L)
     A.lc = make_layer_const(L.sigma0, L.alpha, L.tau_w, L.tp.tau_hi);
     A.sq_n = 0;
     A.items = 0;
+    A.type = L.type;
+    A.grp = L.grp;
+    A.grp_shared = 0;
     return A;
 }
 
@@ -870,6 +1120,23 @@ hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S)
     const size_t lds = sqb + (size_t)L.waves * A.region_bytes;
     void *args[] = {&A};
     return hipLaunchKernel(adj_layer_fn(A.kept != nullptr, A.tp.fine && A.tp.tame), dim3(L.grid), dim3(64 * L.waves), args, lds, st);
+}
+
+static const void *adj_group_fn(bool fast) { return fast ? (const void *)adj_group<true> : (const void *)adj_group<false>; }
+
+hipError_t adj_group_occupancy(int waves, size_t lds, int *blocks_per_cu)
+{
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, adj_group_fn(true), waves * 64, lds);
+}
+
+hipError_t launch_adj_group(hipStream_t st, const AdjLaunch &L)
+{
+    AdjArgs A = make_adj_args(L);
+    A.region_bytes = (int)adj_group_wave_bytes(L.grp);
+    A.grp_shared = (int)adj_group_shared_bytes(L.grp);
+    void *args[] = {&A};
+    return hipLaunchKernel(adj_group_fn(A.tp.fine && A.tp.tame), dim3(L.grid), dim3(64 * L.waves), args,
+                           adj_group_lds_bytes(L.grp, L.waves), st);
 }
 
 size_t adj_team_bytes(int S, int T)

@@ -465,14 +465,17 @@ extern "C" asora_status asora_check(asora_ctx *c, void *stream)
 // (radii from 4 to 30: 3200 sources, 731 us as pyramids, 756 with groups;
 // 9000, 1805 and 1678).
 //
-// A forward that keeps records for an adjoint, and the adjoint, take kind 0 up
-// to the tuning's whole-source radius (the adjoint sweeps those by shells and
-// keeps no records of them) and everything else as pyramids (6400 sources with
-// the adjoint: radius 8, by octants 2378 us, by pyramids 1724; 14, 6205 and
-// 2858).
+// A forward that keeps records for an adjoint, and the adjoint, take the first
+// two classes as groups (without records: their columns are recomputed) and
+// everything else as pyramids.  Forward and adjoint, 128^3, 20000 sources:
+// radius 4, whole by shells 748 us, by groups 513; 8, by pyramids 3936 and
+// 1456; 12, 5701 and 2853.  Below 4096 sources a launch per class costs more
+// than it gives beside larger sources (1400 of radii 2 to 20: 870 by pyramids,
+// 930), and calls of small sources alone are swept whole by shells (1400 of
+// radius 2: 167, by groups 204; 4, 208 and 239; 6400 of radius 4, 351 and 298).
 constexpr float kGroupR[3] = {7.f, 12.5f, 22.f};
 constexpr int kGroup[3] = {24, 8, 3};
-constexpr int64_t kGroupsBeside = 8192;
+constexpr int64_t kGroupsBeside = 8192, kAdjGroups = 4096;
 constexpr float kWholePlanned = 12.f, kOctPlanned = 24.f;   // radii up to which every shell plan of the kinds exists
 
 static Radii radii_of(const asora_ctx *c, bool adjoint, float R_max, int64_t n_src)
@@ -481,8 +484,8 @@ static Radii radii_of(const asora_ctx *c, bool adjoint, float R_max, int64_t n_s
     const float box = (float)make_extent(c->N).pos;
     Radii r;
     for (int t = 0; t < 3; ++t) {
-        r.r[t] = std::min(adjoint ? std::min(c->R_whole, kWholePlanned) : kGroupR[t], box);
-        if (!adjoint && R_max > kGroupR[2] && n_src < kGroupsBeside) r.r[t] = 0.f;
+        r.r[t] = std::min(kGroupR[adjoint && t == 2 ? 1 : t], box);
+        if (adjoint ? R_max > kGroupR[1] && n_src < kAdjGroups : R_max > kGroupR[2] && n_src < kGroupsBeside) r.r[t] = 0.f;
     }
     return r;
 }
@@ -1429,6 +1432,39 @@ static asora_status get_adj_plan(asora_ctx *c, int type, float R_cap, Plan *out)
     return ASORA_OK;
 }
 
+// Adjoint group pieces (kinds 0 and 1 with layer sweeps; a layer is at most 16
+// chunks), their record in the wave's scratch.
+static asora_status get_adj_group_plan(asora_ctx *c, int t, float R_cap, int64_t n_src, Plan *out)
+{
+    const int Rsq = (int)std::floor((double)R_cap * (double)R_cap), G = group_size(c, t, n_src);
+    const PlanKey key{16 + G, Rsq};
+    auto it = c->adj_plans.find(key);
+    if (it != c->adj_plans.end()) {
+        *out = it->second;
+        return ASORA_OK;
+    }
+    const Extent ex = make_extent(c->N);
+    Plan P = Plan();
+    GroupClasses &g = P.grp;
+    g.n = 1;
+    g.R[0] = R_cap;
+    g.Rsq[0] = Rsq;
+    g.S[0] = layer_buffer_side(Rsq, ex);
+    g.G[0] = G;
+    P.rec_cap = g.G[0] * std::max(1L, layer_piece_capacity(Rsq, ex));
+    P.Mcap = isqrt_floor(Rsq);
+    P.scratch = (long)(layer_record_bytes(P.rec_cap, P.Mcap, false) / sizeof(double));
+    P.waves = c->max_waves;
+    while (P.waves > 1 && adj_group_lds_bytes(g, P.waves) > c->max_lds - 64) --P.waves;
+    P.lds = adj_group_lds_bytes(g, P.waves);
+    int bpc = 0;
+    HIPCHK(c, adj_group_occupancy(P.waves, P.lds, &bpc));
+    P.grid = c->n_cu * (bpc > 0 ? bpc : 1);
+    c->adj_plans[key] = P;
+    *out = P;
+    return ASORA_OK;
+}
+
 // Adjoint layer pieces: one layer buffer and a small queue per wave in LDS; a
 // pyramid column record and the rate's entry-column terms in the wave's
 // scratch.
@@ -1510,6 +1546,8 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
                       c->keep_Rmax == R_max && c->keep_sig[0] == n_H && c->keep_sig[1] == x_HI &&
                       c->keep_sig[2] == src_ijk && c->keep_sig[3] == src_Q && c->keep_sig[4] == src_R &&
                       c->keep_early == early;
+    // small sources alone, whole by shells (see radii_of)
+    const bool whole = tmax == 0 && n_src < kAdjGroups;
     Plan plans[4];
     size_t store_need = 0;
     // room for both forms of the layer pieces (kept records or not), see
@@ -1531,7 +1569,20 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
             if ((st = layer_need(cap))) return st;
             continue;
         }
-        if ((st = get_adj_plan(c, t, cap, &plans[t]))) return st;
+        if (c->big_kind == 3) {   // room for the largest groups and the shells, whatever the number of sources
+            Plan o, w;
+            if ((st = get_adj_group_plan(c, t, cap, kMaxSources, &o))) return st;
+            store_need = std::max(store_need, (size_t)o.grid * o.waves * (size_t)o.scratch);
+            if (tmax == 0 && (st = get_adj_plan(c, 0, cap, &w))) return st;
+            if (tmax == 0) store_need = std::max(store_need, (size_t)w.grid * w.waves * (size_t)w.scratch);
+            if (whole)
+                plans[t] = w;
+            else
+                st = get_adj_group_plan(c, t, cap, n_src, &plans[t]);
+        } else {
+            st = get_adj_plan(c, t, cap, &plans[t]);
+        }
+        if (st) return st;
         const size_t need = (size_t)plans[t].grid * plans[t].waves * (size_t)plans[t].scratch;
         store_need = need > store_need ? need : store_need;
     }
@@ -1552,7 +1603,7 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
     if (kept && !c->keep_all) team = 0;
     const long slots = team ? (long)plans[3].grid * plans[3].waves : 0;
     if (team > 1 && 24L * n_src > slots) team = 1;
-    const bool layers = tmax == 3 || team > 0;
+    const bool layers = c->big_kind == 3 && (!whole || team > 0);
     if ((st = ensure_src_cap(c, n_src))) return st;
     if (layers && (st = ensure_adj_layer_buffers(c))) return st;
     if (!c->d_nbar) HIPCHK(c, hipMalloc(&c->d_nbar, sizeof(double) * n3));
@@ -1613,10 +1664,12 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
         L.gbar_T = c->d_gbar_T;
         L.nbar_T = c->d_nbar_T;
         L.kept = kept ? c->d_keep : nullptr;
-        L.rec_piece_bytes = layers ? plans[3].rec_bytes : 0;
-        L.rec_cap = layers ? plans[3].rec_cap : 0;
+        const bool pyramids = tmax == 3 || team > 0;
+        L.rec_piece_bytes = pyramids ? plans[3].rec_bytes : 0;
+        L.rec_cap = pyramids ? plans[3].rec_cap : 0;
+        L.grp = GroupClasses();
         L.early_exit = early;
-        L.sq_table = layers && plans[3].sq_table;
+        L.sq_table = pyramids && plans[3].sq_table;
         if (team) {
             L.type = 3;
             L.R_cap = R_max;
@@ -1636,7 +1689,11 @@ extern "C" asora_status asora_raytrace_backward(asora_ctx *c, const float *n_H, 
             L.grid = plans[t].grid;
             L.store_stride = plans[t].scratch;
             if (t == 3) HIPCHK(c, launch_adj_layer(s, L, plans[3].Mcap, plans[3].S));
-            else HIPCHK(c, launch_adj_wave(s, L));
+            else if (layers) {
+                L.grp = plans[t].grp;
+                L.rec_cap = plans[t].rec_cap;
+                HIPCHK(c, launch_adj_group(s, L));
+            } else HIPCHK(c, launch_adj_wave(s, L));
         }
     }
     if (prof) HIPCHK(c, hipEventRecord(ev[2], s));

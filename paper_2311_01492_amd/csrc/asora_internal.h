@@ -156,6 +156,7 @@ struct AdjLaunch {
     long rec_cap;             // cells per pyramid record
     bool early_exit;          // layer pieces: stop at the first opaque layer
     bool sq_table;            // layer pieces: the work-group's LDS table of sqrt(r^2) (else per cell)
+    GroupClasses grp;         // group pieces: one class
 };
 
 size_t adj_region_bytes(int ring_cap, int row_cap, int shell_cap);
@@ -176,6 +177,9 @@ size_t adj_layer_region_bytes(int S);
 hipError_t adj_layer_occupancy(bool kept, int waves, size_t lds, int *blocks_per_cu);
 hipError_t launch_adj_layer(hipStream_t st, const AdjLaunch &L, int Mcap, int S);
 size_t adj_team_bytes(int S, int T);
+size_t adj_group_lds_bytes(const GroupClasses &c, int waves);
+hipError_t adj_group_occupancy(int waves, size_t lds, int *blocks_per_cu);
+hipError_t launch_adj_group(hipStream_t st, const AdjLaunch &L);
 hipError_t launch_adj_direct(hipStream_t st, const AdjLaunch &L, int Mcap, int S, int T, int n_src);
 hipError_t launch_adj_transpose_finalize(hipStream_t st, const double *nbar, const double *nbar_T,
                                          const float *nH, const float *xHI, float *dnH, float *dxHI,

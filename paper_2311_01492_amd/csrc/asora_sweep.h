@@ -226,7 +226,7 @@ struct GroupLds {
 };
 
 struct GroupChunk {
-    int m;
+    int m, c, cells;    // layer, chunk, the layer's cells
     bool in;
     int u, v, r2, flags;
     uint32_t cell;      // index in the pyramid's layout
@@ -319,9 +319,12 @@ __device__ __forceinline__ void sweep_group(const LayerX &X, const double *nHI_T
     fetch((cells + 63) / 64 - 1);
     for (int m = 1; m <= Mx; ++m) {
         const double am = X.sa * rcp_f64((double)m);
-        for (int c = (cells + 63) / 64 - 1; c >= 0; --c) {
+        const int total = cells;
+        for (int c = (total + 63) / 64 - 1; c >= 0; --c) {
             GroupChunk k;
             k.m = m;
+            k.c = c;
+            k.cells = total;
             k.in = act;
             k.u = u;
             k.v = v;

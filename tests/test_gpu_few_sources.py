@@ -3,7 +3,7 @@ waves to a pyramid where the chip has room; calls of many take the sources from
 sorted lists, small ones in groups of pyramids.  All of these, at the counts
 where the number of waves to a pyramid changes (256 CUs: 7, 85, 170 sources),
 where the lists begin (256, 512, 682 and 1365), where the groups change (to 24 pyramids at
-3151) and where they come in beside pyramids (8192), on odd
+3151) and where they come in beside pyramids or for shells (4096, 8192), on odd
 and even grids and up to radii beyond half the box, against the shell sweeps of
 the same sources.  Rates are FP32 in every form (1e-5, as against the oracle);
 kept records and recomputed ones give the same FP64 sums, rounded once to the
@@ -55,7 +55,7 @@ def _np(x):
     (1, 16, 0.9), (1, 17, 1.0), (1, 24, 18.0), (2, 23, 9.5), (7, 24, 11.9), (8, 21, 14.0), (85, 24, 5.0),
     (86, 25, 13.0), (170, 24, 11.0), (171, 25, 3.0), (256, 34, 16.1), (257, 34, 16.1), (512, 47, 22.9), (682, 20, 9.0), (683, 21, 9.0),
     (800, 20, 5.5), (800, 21, 9.7), (800, 33, 16.0),
-    (1365, 16, 6.0), (1400, 18, 7.1), (1400, 29, 13.9), (3500, 26, 12.5), (4200, 48, 23.0), (8200, 50, 23.9)])
+    (1365, 16, 6.0), (4100, 20, 6.9), (1400, 18, 7.1), (1400, 29, 13.9), (3500, 26, 12.5), (4200, 48, 23.0), (8200, 50, 23.9)])
 def test_every_count_against_shell_sweeps(asora, n_src, N, R_hi):
     print("case few sources", n_src, N, R_hi, flush=True)
     w, src, gbar = _inputs(N, n_src, R_hi, 31 + n_src)
